@@ -238,7 +238,8 @@ int validate_bv(const sell_bv *v) {
 
 // y = alpha (A x - gamma x) + beta y, dots, chain; no argument checks (callers check).
 int aug_impl(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const sell_spmv_opts &o,
-             bool aug, hipStream_t s, double *partials_out, int32_t *nblocks_out, const Workspace *ws_in) {
+             bool aug, hipStream_t s, double *partials_out, int32_t *nblocks_out, const Workspace *ws_in,
+             const sell_bv *Yin) {
     if (nblocks_out) *nblocks_out = 0;
     const int b = X->ncols;
     const bool dots = aug && (o.flags & SELL_SPMV_DOTS);
@@ -303,6 +304,7 @@ int aug_impl(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const 
         bv_strides(Y, a.yrs, a.ycs);
         a.X = elem_ptr(X, 0, sl.first);
         a.Y = elem_ptr(Y, 0, sl.first);
+        if (Yin) a.yi_off = elem_ptr(Yin, 0, sl.first) - static_cast<char *>(a.Y);
         a.scratch = ws->scratch;
         a.stage = staged ? 1 : 0;
         if (staged) {

@@ -8,9 +8,14 @@
 //    The forward pass keeps the pair (v_kK, v_kK+1) every K steps; the backward pass walks
 //    the segments from the last to the first, recomputes each segment's vectors from its
 //    checkpoint and runs the adjoint recurrence
-//        w_m += 2 A~^T w_m+1,   w_m-1 -= w_m+1,   dval += (2/s) outer(w_m+1, v_m)
-//    (A~^T w via the forward kernel on the SELL copy of A^T, fused with the scaling, the shift
-//    and the accumulation in one augmented product), ending with the first step v_1 = A~ v_0.
+//        w_m = 2 A~^T w_m+1 - w_m+2,   dval += (2/s) outer(w_m+1, v_m)
+//    (A~^T w via the forward kernel on the SELL copy of A^T), ending with the first step
+//    w_0 = A~^T w_1 - w_2,  dval += (1/s) outer(w_1, v_0).
+//    Every step of a recurrence is one launch: the augmented product reads the vector of two
+//    steps before from one block and writes the new one to another, so nothing is copied between
+//    them, and the vectors that a checkpoint or the result needs are written in place. The outer
+//    products of several steps share a launch (16 columns' worth), which then reads and writes
+//    the gradient once for all of them.
 #include <algorithm>
 #include <cmath>
 #include <utility>
@@ -75,15 +80,20 @@ sell_bv block(void *p, int64_t n, int b, int dt) {
     return v;
 }
 
-// y <- alpha (M x - c x) + beta y  (beta == 0: y not read)
-int shifted_product(const sell_mat *M, const sell_bv &x, sell_bv &y, double alpha, double c, double beta,
+// y <- alpha (M x - c x) - w  (w == nullptr: no w; w may be y itself)
+int shifted_product(const sell_mat *M, const sell_bv &x, sell_bv &y, double alpha, double c, const sell_bv *w,
                     hipStream_t s) {
     sell_spmv_opts o = SELL_SPMV_OPTS_INIT;
-    o.flags = SELL_SPMV_SCALE | SELL_SPMV_SHIFT | (beta != 0.0 ? SELL_SPMV_AXPBY : 0u);
+    o.flags = SELL_SPMV_SCALE | SELL_SPMV_SHIFT | (w ? SELL_SPMV_AXPBY : 0u);
     o.alpha = alpha;
     o.gamma = c;
-    o.beta = beta;
-    return aug_impl(M, &x, &y, nullptr, o, true, s);
+    o.beta = w ? -1.0 : 0.0;
+    return aug_impl(M, &x, &y, nullptr, o, true, s, nullptr, nullptr, nullptr, w);
+}
+
+bool overlap(const void *p, const void *q, size_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + bytes && b < a + bytes;
 }
 
 }  // namespace
@@ -101,12 +111,12 @@ int sell_grad_values(const sell_mat *A, const sell_bv *G, const sell_bv *X, doub
     if (A->h.nnz == 0) return SELL_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((rc = ensure_update_maps(const_cast<sell_mat *>(A), s))) return rc;
-    Temps T(s);
-    double *dsell = nullptr;
-    if ((rc = T.alloc(reinterpret_cast<void **>(&dsell), size_t(A->h.stored) * sizeof(double)))) return rc;
-    if ((rc = launch_fill(dsell, SELL_F64, A->h.stored, 1, 1, 1, 0.0, s))) return rc;
-    if ((rc = launch_grad_accum(A, G->ptr, G->ld, X->ptr, X->ld, G->dt, b, alpha, dsell, s))) return rc;
-    return launch_sell_to_csr(A, dsell, accumulate ? 1 : 0, dval, s);
+    GradPairs p;
+    p.n = 1;
+    p.g[0] = G->ptr;
+    p.x[0] = X->ptr;
+    p.c[0] = alpha;
+    return launch_grad(A, p, G->ld, X->ld, G->dt, b, accumulate ? 1 : 0, dval, s);
 }
 
 int sell_cheb_forward(const sell_mat *A, const sell_bv *X, sell_bv *Y, int64_t N, double scale, double c,
@@ -127,24 +137,36 @@ int sell_cheb_forward(const sell_mat *A, const sell_bv *X, sell_bv *Y, int64_t N
     Temps T(s);
     void *p0, *p1;
     if ((rc = T.alloc(&p0, vb)) || (rc = T.alloc(&p1, vb))) return rc;
-    sell_bv V0 = block(p0, n, b, dt), V1 = block(p1, n, b, dt);
     char *ck = static_cast<char *>(ckpt);
-    if ((rc = launch_copy(&V0, X, s))) return rc;
-    if ((rc = shifted_product(A, V0, V1, 1.0 / scale, c, 0.0, s))) return rc;  // v1 = A~ v0
-    auto save = [&](int64_t k) -> int {
-        if (!ck) return SELL_OK;
-        HIPCHK(hipMemcpyAsync(ck + size_t(2 * k) * vb, V0.ptr, vb, hipMemcpyDeviceToDevice, s));
-        HIPCHK(hipMemcpyAsync(ck + size_t(2 * k + 1) * vb, V1.ptr, vb, hipMemcpyDeviceToDevice, s));
-        return SELL_OK;
+    const int64_t nseg = (N + K - 1) / K;
+    // the block of v_i in the checkpoints (-1: none); with K = 1 also v_i as the second of the pair before
+    auto first = [&](int64_t i) { return ck && i % K == 0 && i / K < nseg ? 2 * (i / K) : int64_t(-1); };
+    auto second = [&](int64_t i) {
+        return ck && i > 0 && (i - 1) % K == 0 && (i - 1) / K < nseg ? 2 * ((i - 1) / K) + 1 : int64_t(-1);
     };
-    if ((rc = save(0))) return rc;
-    for (int64_t m = 1; m < N; ++m) {
-        // v_m+1 = 2 A~ v_m - v_m-1, written over v_m-1
-        if ((rc = shifted_product(A, V1, V0, 2.0 / scale, c, -1.0, s))) return rc;
-        std::swap(V0, V1);  // (V0, V1) = (v_m, v_m+1)
-        if (m % K == 0 && (rc = save(m / K))) return rc;
+    auto at = [&](int64_t slot) { return block(ck + size_t(slot) * vb, n, b, dt); };
+    if (first(0) >= 0) {
+        sell_bv c0 = at(first(0));
+        if ((rc = launch_copy(&c0, X, s))) return rc;
     }
-    return launch_copy(Y, &V1, s);
+    // v_i goes to its checkpoint block, v_N to Y (where a checkpoint does not want it, and X is not
+    // in its way), every other v_i to the work block that does not hold v_i-1; v_i-2, which the
+    // step reads element by element as it writes v_i, may be in that one
+    sell_bv prev = *X, cur = *X;
+    for (int64_t i = 1; i <= N; ++i) {
+        const int64_t sl = first(i) >= 0 ? first(i) : second(i);
+        sell_bv out = sl >= 0                                       ? at(sl)
+                      : i == N && !overlap(X->ptr, Y->ptr, vb) ? *Y
+                                                                    : block(cur.ptr == p0 ? p1 : p0, n, b, dt);
+        if ((rc = shifted_product(A, cur, out, (i == 1 ? 1.0 : 2.0) / scale, c, i == 1 ? nullptr : &prev, s))) return rc;
+        if (first(i) >= 0 && second(i) >= 0) {
+            sell_bv again = at(second(i));
+            if ((rc = launch_copy(&again, &out, s))) return rc;
+        }
+        prev = cur;
+        cur = out;
+    }
+    return cur.ptr == Y->ptr ? SELL_OK : launch_copy(Y, &cur, s);
 }
 
 int sell_cheb_filter(const sell_mat *A, const sell_bv *X, sell_bv *Z, int64_t N, const double *coef, double scale,
@@ -170,7 +192,6 @@ int sell_cheb_filter(const sell_mat *A, const sell_bv *X, sell_bv *Z, int64_t N,
     void *p0, *p1;
     if ((rc = T.alloc(&p0, vb)) || (rc = T.alloc(&p1, vb))) return rc;
     sell_bv V0 = block(p0, n, b, dt), V1 = block(p1, n, b, dt);
-    if ((rc = launch_copy(&V0, X, s))) return rc;
     // every step: one augmented product forming v_m+1 with the chained z = z + coef_m+1 v_m+1
     sell_spmv_opts o = SELL_SPMV_OPTS_INIT;
     o.flags = SELL_SPMV_SCALE | SELL_SPMV_SHIFT | SELL_SPMV_CHAIN;
@@ -178,14 +199,14 @@ int sell_cheb_filter(const sell_mat *A, const sell_bv *X, sell_bv *Z, int64_t N,
     o.gamma = c;
     o.delta = 1.0;
     o.eta = coef[1];
-    if ((rc = aug_impl(A, &V0, &V1, Z, o, true, s))) return rc;  // v_1 = A~ v_0
+    if ((rc = aug_impl(A, X, &V1, Z, o, true, s))) return rc;  // v_1 = A~ v_0
     o.flags |= SELL_SPMV_AXPBY;
     o.alpha = 2.0 / scale;
     o.beta = -1.0;
     for (int64_t m = 1; m < N; ++m) {
-        // v_m+1 = 2 A~ v_m - v_m-1, written over v_m-1
+        // v_m+1 = 2 A~ v_m - v_m-1, written over v_m-1 (v_0 is X, which stays)
         o.eta = coef[m + 1];
-        if ((rc = aug_impl(A, &V1, &V0, Z, o, true, s))) return rc;
+        if ((rc = aug_impl(A, &V1, &V0, Z, o, true, s, nullptr, nullptr, nullptr, m == 1 ? X : nullptr))) return rc;
         std::swap(V0, V1);  // (V0, V1) = (v_m, v_m+1)
     }
     return SELL_OK;
@@ -215,50 +236,53 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
     const size_t vb = size_t(n) * b * (dt == SELL_F64 ? 8 : 4);
     const int64_t nseg = (N + K - 1) / K;
     const int64_t seglen = std::min<int64_t>(K, N);
+    // outer products per launch: the steps that make up 16 columns. Past that the gradient's own
+    // traffic is small beside the gathers, and the adjoint vectors kept for a launch would cost
+    // memory (they are at most 16 columns in all).
+    const int64_t group = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(seglen, N), kGradPairs / b));
+    const int64_t nw = group + 2;  // adjoint vectors: the group's, and the two that the next step reads
     Temps T(s);
-    void *pw0, *pw1, *pwn, *pseg;
-    double *dsell = nullptr;
-    if ((rc = T.alloc(&pw0, vb)) || (rc = T.alloc(&pw1, vb)) || (rc = T.alloc(&pwn, vb)) ||
-        (rc = T.alloc(&pseg, vb * size_t(seglen))) ||
-        (rc = T.alloc(reinterpret_cast<void **>(&dsell), size_t(A->h.stored > 0 ? A->h.stored : 1) * 8)))
-        return rc;
-    sell_bv W1 = block(pw1, n, b, dt), W0 = block(pw0, n, b, dt), Wn = block(pwn, n, b, dt);
-    auto seg = [&](int64_t i) { return block(static_cast<char *>(pseg) + size_t(i) * vb, n, b, dt); };
+    void *pw, *pseg = nullptr;
+    if ((rc = T.alloc(&pw, vb * size_t(nw))) || (seglen > 2 && (rc = T.alloc(&pseg, vb * size_t(seglen - 2))))) return rc;
+    auto w = [&](int64_t m) { return block(static_cast<char *>(pw) + size_t(m % nw) * vb, n, b, dt); };
     const char *ck = static_cast<const char *>(ckpt);
-    if ((rc = launch_copy(&W1, G, s))) return rc;  // w_N = G
-    if ((rc = launch_fill(W0.ptr, dt, n, b, b, 1, 0.0, s))) return rc;  // w_N-1 (partial) = 0
-    if ((rc = launch_fill(dsell, SELL_F64, A->h.stored, 1, 1, 1, 0.0, s))) return rc;
+    GradPairs pairs;
+    pairs.n = 0;
+    int written = 0;
+    auto flush = [&]() -> int {
+        if (pairs.n == 0) return SELL_OK;
+        const int r = launch_grad(A, pairs, b, b, dt, b, written, dval, s);
+        pairs.n = 0;
+        written = 1;
+        return r;
+    };
     for (int64_t k = nseg - 1; k >= 0; --k) {
         const int64_t lo = k * K, hi = std::min(lo + K - 1, N - 1);
-        // recompute v_lo .. v_hi of this segment from its checkpoint (v_lo, v_lo+1)
-        HIPCHK(hipMemcpyAsync(seg(0).ptr, ck + size_t(2 * k) * vb, vb, hipMemcpyDeviceToDevice, s));
-        if (hi > lo) HIPCHK(hipMemcpyAsync(seg(1).ptr, ck + size_t(2 * k + 1) * vb, vb, hipMemcpyDeviceToDevice, s));
+        // v_lo and v_lo+1 are the segment's checkpoint, v_lo+2 .. v_hi are recomputed from it
+        auto v = [&](int64_t m) {
+            const int64_t i = m - lo;
+            return i < 2 ? block(const_cast<char *>(ck) + size_t(2 * k + i) * vb, n, b, dt)
+                         : block(static_cast<char *>(pseg) + size_t(i - 2) * vb, n, b, dt);
+        };
         for (int64_t m = lo + 2; m <= hi; ++m) {
-            sell_bv prev = seg(m - lo - 1), out = seg(m - lo), prev2 = seg(m - lo - 2);
-            if ((rc = launch_copy(&out, &prev2, s))) return rc;
-            if ((rc = shifted_product(A, prev, out, 2.0 / scale, c, -1.0, s))) return rc;
+            sell_bv out = v(m), prev = v(m - 2);
+            if ((rc = shifted_product(A, v(m - 1), out, 2.0 / scale, c, &prev, s))) return rc;
         }
-        for (int64_t m = hi; m >= std::max<int64_t>(lo, 1); --m) {
-            // W1 = w_m+1 (complete), W0 = w_m (partial)
-            sell_bv vm = seg(m - lo);
-            if ((rc = launch_grad_accum(A, W1.ptr, b, vm.ptr, b, dt, b, 2.0 / scale, dsell, s))) return rc;
-            if ((rc = launch_axpby(dt, n, b, b, -1.0, W1.ptr, 0.0, Wn.ptr, s))) return rc;  // w_m-1 = -w_m+1
-            if ((rc = shifted_product(AT, W1, W0, 2.0 / scale, c, 1.0, s))) return rc;      // w_m += 2 A~^T w_m+1
-            sell_bv t = W1;
-            W1 = W0;
-            W0 = Wn;
-            Wn = t;
-        }
-        if (lo == 0) {
-            // first step v_1 = A~ v_0: W1 = w_1, W0 = w_0 (partial)
-            sell_bv v0 = seg(0);
-            if ((rc = launch_grad_accum(A, W1.ptr, b, v0.ptr, b, dt, b, 1.0 / scale, dsell, s))) return rc;
-            if ((rc = shifted_product(AT, W1, W0, 1.0 / scale, c, 1.0, s))) return rc;
+        for (int64_t m = hi; m >= lo; --m) {
+            // w_m from w_m+1 (w_N = G) and w_m+2 (w_N+1 = 0)
+            const sell_bv w1 = m + 1 == N ? *G : w(m + 1), w2 = m + 2 == N ? *G : w(m + 2);
+            pairs.g[pairs.n] = w1.ptr;
+            pairs.x[pairs.n] = v(m).ptr;
+            pairs.c[pairs.n++] = (m > 0 ? 2.0 : 1.0) / scale;
+            if ((pairs.n == group || m == lo) && (rc = flush())) return rc;
+            sell_bv out = m == 0 && !overlap(G->ptr, dX->ptr, vb) ? *dX : w(m);
+            if ((rc = shifted_product(AT, w1, out, (m > 0 ? 2.0 : 1.0) / scale, c, m + 2 <= N ? &w2 : nullptr, s)))
+                return rc;
         }
     }
-    if ((rc = launch_copy(dX, &W0, s))) return rc;
-    if (A->h.nnz == 0) return SELL_OK;
-    return launch_sell_to_csr(A, dsell, 0, dval, s);
+    if (!overlap(G->ptr, dX->ptr, vb)) return SELL_OK;
+    const sell_bv w0 = w(0);
+    return launch_copy(dX, &w0, s);
 }
 
 }  // extern "C"

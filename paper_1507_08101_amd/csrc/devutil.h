@@ -5,6 +5,14 @@
 
 namespace sellcs {
 
+// Workgroup id -> position, so that XCD x (the hardware deals workgroups x, x+8, x+16, ... to it)
+// works on one contiguous eighth of the positions: neighbouring rows share its L2.
+__device__ __forceinline__ int xcd_block(int bid, int nblocks) {
+    const int q = nblocks >> 3, r = nblocks & 7;
+    const int x = bid & 7, k = bid >> 3;
+    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
+}
+
 // Sum of one value per thread of a 256-thread workgroup in a fixed order: butterfly inside
 // each wave, then the four wave sums in order. The result is valid in thread 0.
 __device__ __forceinline__ double block_sum_256(double v) {

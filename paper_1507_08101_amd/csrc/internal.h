@@ -185,6 +185,7 @@ struct ProdArgs {
     int32_t nb;            // columns in this slice
     const void *X; int64_t xrs, xcs;   // element (i, j) at X[i * xrs + j * xcs]
     void *Y; int64_t yrs, ycs;
+    int64_t yi_off;        // beta y reads the block this many bytes from Y, with Y's strides (0: Y)
     void *Z; int64_t zrs, zcs;
     uint32_t flags;
     double alpha, beta, delta, eta;
@@ -285,10 +286,11 @@ int launch_batch_dot_finish_packed(const double *partials, const int32_t *blk, c
 // *nblocks_out (may be null) receives the number of partials per quantity (workgroups).
 // ws_in: the reduction partials and lane scratch to use; nullptr takes the stream's workspace
 // (allocated on the first call on a stream).
+// Yin: the block that beta y reads (Y's shape, layout and leading dimension); nullptr: Y itself.
 struct Workspace;
 int aug_impl(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const sell_spmv_opts &o, bool aug,
              hipStream_t s, double *partials_out = nullptr, int32_t *nblocks_out = nullptr,
-             const Workspace *ws_in = nullptr);
+             const Workspace *ws_in = nullptr, const sell_bv *Yin = nullptr);
 // Checks the operands of sell_spmmv_aug and fills *o from opts (the defaults when null).
 int check_aug_call(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const sell_spmv_opts *opts,
                    sell_spmv_opts *o);
@@ -310,10 +312,16 @@ int ensure_stage(const sell_mat *A, int32_t chunks, hipStream_t s);
 // cache slots (stage.hip); rebuilt when any of them changes.
 int ensure_stage_plan(const sell_mat *A, int32_t nblk, int32_t stride, int32_t ns, hipStream_t s);
 
-// Value-gradient kernels (grad.hip).
-int launch_grad_accum(const sell_mat *A, const void *G, int64_t ldg, const void *X, int64_t ldx, int vec_dt,
-                      int32_t b, double alpha, double *dsell, hipStream_t s);
-int launch_sell_to_csr(const sell_mat *A, const double *dsell, int accumulate, double *dval, hipStream_t s);
+// Value gradients (grad.hip): dval (+)= sum over the pairs of c_p times the pattern-restricted
+// outer product of G_p and X_p, in CSR order (needs the update maps).
+constexpr int kGradPairs = 16;
+struct GradPairs {
+    const void *g[kGradPairs], *x[kGradPairs];
+    double c[kGradPairs];
+    int32_t n;
+};
+int launch_grad(const sell_mat *A, const GradPairs &pairs, int64_t ldg, int64_t ldx, int vec_dt, int32_t b,
+                int accumulate, double *dval, hipStream_t s);
 int launch_axpby(int vec_dt, int64_t n, int32_t b, int64_t ld, double alpha, const void *x, double beta, void *y,
                  hipStream_t s);
 // dst[pos[p]] = convert(src[p]) for p < n, dst of storage type vdt

@@ -39,6 +39,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "devutil.h"
 #include "internal.h"
 
 namespace sellcs {
@@ -70,14 +71,6 @@ __device__ __forceinline__ float to_acc(uint16_t v, float) { return __uint_as_fl
 
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __fma_rn(a, b, c); }
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __fmaf_rn(a, b, c); }
-
-// Workgroup id -> tile, so that XCD x (which receives workgroups x, x+8, x+16, ...)
-// processes one contiguous range of tiles.
-__device__ __forceinline__ int xcd_tile(int bid, int nblocks) {
-    const int q = nblocks >> 3, r = nblocks & 7;
-    const int x = bid & 7, k = bid >> 3;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
-}
 
 __device__ __forceinline__ double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
 
@@ -212,6 +205,8 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     const SELL_GLOBAL int32_t *__restrict__ col = to_global(a.col);
     const SELL_GLOBAL X *__restrict__ Xp = to_global(static_cast<const X *>(a.X));
     SELL_GLOBAL X *__restrict__ Yp = to_global(static_cast<X *>(a.Y));
+    // the y that beta y reads: Y itself (offset 0) or another block with Y's strides
+    const SELL_GLOBAL X *Yi = reinterpret_cast<const SELL_GLOBAL X *>(reinterpret_cast<SELL_GLOBAL char *>(Yp) + a.yi_off);
     SELL_GLOBAL X *__restrict__ Zp = to_global(static_cast<X *>(a.Z));
     const int64_t xrs = a.xrs, xcs = VEC ? 1 : a.xcs;
     const int64_t yrs = a.yrs, ycs = VEC ? 1 : a.ycs;
@@ -315,7 +310,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
 #pragma unroll
                 for (int t = 0; t < VPT; ++t) xin[t] = src[t];
             } else if (need_x) load_row<X, VPT, VEC>(Xp + rowc * xrs + int64_t(jl) * xcs, xcs, xin);
-            if (read_y) load_row<X, VPT, VEC>(Yp + rowc * yrs + int64_t(jl) * ycs, ycs, yin);
+            if (read_y) load_row<X, VPT, VEC>(Yi + rowc * yrs + int64_t(jl) * ycs, ycs, yin);
             if (read_z) load_row<X, VPT, VEC>(Zp + rowc * zrs + int64_t(jl) * zcs, zcs, zin);
         }
 
@@ -581,7 +576,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
 
 template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0>
 __global__ void __launch_bounds__(kBlock) prod_kernel(ProdArgs a, int vl_log2) {
-    const int tile = a.xcd_map ? xcd_tile(blockIdx.x, gridDim.x) : int(blockIdx.x);  // index in the partials
+    const int tile = a.xcd_map ? xcd_block(blockIdx.x, gridDim.x) : int(blockIdx.x);  // index in the partials
     int vls = vl_log2;
     if (B == 0 && vls < 0) {
         vls = 0;
@@ -614,7 +609,7 @@ template <int VK, int B, int VPT, bool AUG, int UB = 0, uint32_t FL = 0>
 __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__restrict__ table,
                                                             const int32_t *__restrict__ blk_start, int K,
                                                             const int32_t *__restrict__ active, int vl_log2) {
-    const int g = xcd_tile(blockIdx.x, gridDim.x);
+    const int g = xcd_block(blockIdx.x, gridDim.x);
     int lo = 0, hi = K;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -647,7 +642,7 @@ template <int VK, bool AUG>
 __global__ void __launch_bounds__(kBlock) prod_batch_mixed_kernel(const ProdArgs *__restrict__ table,
                                                                   const int32_t *__restrict__ blk_start, int K,
                                                                   const int32_t *__restrict__ active, int) {
-    const int g = xcd_tile(blockIdx.x, gridDim.x);
+    const int g = xcd_block(blockIdx.x, gridDim.x);
     int lo = 0, hi = K;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -688,7 +683,7 @@ __global__ void __launch_bounds__(kBlock) transpose_kernel(ProdArgs a, int vl_lo
     const int nb = DYN ? a.nb : B;
     const int VL = DYN ? (1 << vl_log2) : (B / VPT);
     const int vls = DYN ? vl_log2 : __builtin_ctz(B / VPT);
-    const int tile = a.xcd_map ? xcd_tile(blockIdx.x, gridDim.x) : int(blockIdx.x);
+    const int tile = a.xcd_map ? xcd_block(blockIdx.x, gridDim.x) : int(blockIdx.x);
     const int C = a.C;
     const int64_t t0 = int64_t(tile) * a.ntiles / a.nblocks, t1 = int64_t(tile + 1) * a.ntiles / a.nblocks;
     const int64_t s_begin = int64_t(a.tiles[t0]) * C;

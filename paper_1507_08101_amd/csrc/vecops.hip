@@ -74,6 +74,7 @@ int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s) {
     bool fixed_ok = fixed_width(a.nb) && vec_ok(a.X, a.xrs, a.xcs, esize, align) &&
                     vec_ok(a.Y, a.yrs, a.ycs, esize, align);
     if (aug && (a.flags & SELL_SPMV_CHAIN)) fixed_ok = fixed_ok && vec_ok(a.Z, a.zrs, a.zcs, esize, align);
+    if (aug && (a.flags & SELL_SPMV_AXPBY)) fixed_ok = fixed_ok && a.yi_off % align == 0;
     if (!fixed_ok) {
         if (!fixed_width(a.nb))
             log_warn_once(kWarnProductWidth,

@@ -45,6 +45,29 @@ def test_grad_values_matches_oracle(sc, b):
     M.close()
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("b", [1, 2, 4, 5, 7, 8, 9, 12, 16, 17, 31, 32, 33, 63, 64, 65, 70])
+def test_grad_values_every_lane_group(sc, b, dt):
+    """Every width class of the gradient kernel (lanes per row, shifted last pieces, slices past 64),
+    rows longer than an entry batch and empty rows, sorted windows: per entry within the bound of a
+    b-term FP64 sum, (b + 4) u sum |g x|."""
+    import torch
+
+    A = synth.random_sparse(301, 170, 0.04, 135, duplicates=True, empty_rows=9, long_row=150)
+    M = sc.SellMatrix.from_csr(A, C=12 if b % 2 else 32, sigma=40, dtype=dt)
+    vt = np.float64 if dt == "f64" else np.float32
+    G = synth.block_vector(A.nrows, b, 136).astype(vt)
+    X = synth.block_vector(A.ncols, b, 137).astype(vt)
+    ref, mag = oracle.pattern_outer(A, G, X), oracle.pattern_outer(A, np.abs(G), np.abs(X))
+    dval = torch.full((A.nnz,), 5.0, dtype=torch.float64, device="cuda:0")
+    sc.sell_grad_values(M, dev(G), dev(X), dval, alpha=-0.7)
+    bound = 0.7 * (b + 4) * 2.0 ** -53 * mag
+    assert (np.abs(host(dval) + 0.7 * ref) <= bound).all()
+    sc.sell_grad_values(M, dev(G), dev(X), dval, alpha=1.7, accumulate=True)
+    assert (np.abs(host(dval) - ref) <= 4 * bound + 2.0 ** -52 * np.abs(ref)).all()
+    M.close()
+
+
 def test_spmm_autograd_gradcheck(sc):
     import torch
 
@@ -164,6 +187,41 @@ def test_chebyshev_forward_backward_vs_oracle(sc, N, K, b):
     dX_ref, dval_ref = oracle.cheb_grad(A, X, N, s, c, 2.0 * Yref)
     assert _relnorm(host(Xd.grad), dX_ref) <= 1e-11
     assert _relnorm(host(theta.grad), dval_ref) <= 1e-11
+    M.close()
+
+
+@pytest.mark.parametrize("N,K,b", [(1, 1, 1), (2, 1, 2), (5, 1, 1), (6, 2, 9), (9, 4, 16), (9, 4, 20), (12, 4, 1), (40, 25, 1)])
+def test_chebyshev_checkpoint_layouts(sc, N, K, b):
+    """Checkpoints of every step, segments that end at N, outer products grouped over 16, 1 and fewer
+    steps; the results written over the inputs (X over Y, G over dX), as separate buffers give."""
+    import torch
+
+    A, s, X = _anderson_case(8, b, 134)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1)
+    G = synth.block_vector(A.nrows, b, 135)
+    Yref = oracle.cheb_apply(A, X, N, s, 0.2)
+    dX_ref, dval_ref = oracle.cheb_grad(A, X, N, s, 0.2, G)
+    outs = []
+    for inplace in (False, True):
+        Xd, Gd = dev(X), dev(G)
+        Y, dX = (Xd, Gd) if inplace else (torch.empty_like(Xd), torch.empty_like(Gd))
+        ck = torch.full((sc.cheb_ckpt_elems(A.nrows, b, N, K),), float("nan"), dtype=torch.float64, device="cuda:0")
+        dval = torch.full((A.nnz,), float("nan"), dtype=torch.float64, device="cuda:0")
+        sc.sell_cheb_forward(M, Xd, Y, N, s, 0.2, K, ck)
+        sc.sell_cheb_backward(M, Gd, N, s, 0.2, K, ck, dX, dval)
+        outs.append([host(t) for t in (Y, dX, dval, ck)])
+        assert _relnorm(outs[-1][0], Yref) <= 1e-12
+        assert _relnorm(outs[-1][1], dX_ref) <= 1e-11
+        assert _relnorm(outs[-1][2], dval_ref) <= 1e-11
+    for u, v in zip(*outs):
+        assert np.array_equal(u, v)
+    # the checkpoints are the pairs (v_kK, v_kK+1)
+    pairs = outs[0][3].reshape(-1, 2, A.nrows, b)
+    for k in range(pairs.shape[0]):
+        for i in (0, 1):
+            m = k * K + i
+            want = X if m == 0 else oracle.cheb_apply(A, X, m, s, 0.2)
+            assert _relnorm(pairs[k, i], want) <= 1e-12
     M.close()
 
 
