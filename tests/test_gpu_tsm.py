@@ -114,3 +114,61 @@ def test_tsmm_inplace(sc, n, m):
     ref = oracle.tsmm_inplace(V, X, 1.5, -0.5)
     scale = 1.5 * np.abs(V) @ np.abs(X) + 0.5 * np.abs(V)
     assert np.all(np.abs(host(Vd) - ref) <= 1e-13 * scale + 1e-300)
+
+
+@pytest.mark.parametrize("m,k", [(16, 17), (17, 16), (32, 32), (33, 31), (48, 49), (64, 64), (63, 12), (12, 64), (64, 1), (1, 64),
+                                 (2, 8), (24, 24), (7, 7), (9, 9)])
+@pytest.mark.parametrize("n", [1, 15, 17, 129, 5000])
+def test_matrix_core_blocks_every_edge(sc, n, m, k):
+    """The matrix-core kernels where rows, columns and terms end inside a 16 x 16 x 4 block, one
+    wave's rows and several workgroups', on contiguous blocks and on slices of wider ones at an odd
+    offset: element by element within the bound of a sum of FP64 products, (terms + 6) u sum |v w|,
+    and rows past the block and columns beside it untouched."""
+    V, W = synth.block_vector(n, m, 170), synth.block_vector(n, k, 171)
+    X, Q = synth.block_vector(m, k, 172), synth.block_vector(m, m, 173)
+    u = 2.0 ** -53
+    g = oracle.tsmttsm(V, W, 1.5, 0.0, np.zeros((m, k)))
+    gb = 1.5 * (n + 6) * u * (np.abs(V).T @ np.abs(W)) * 2
+    w = oracle.tsmm(V, X, -0.5, 0.25, W)
+    wb = 2 * (m + 6) * u * (0.5 * np.abs(V) @ np.abs(X) + 0.25 * np.abs(W))
+    v = oracle.tsmm_inplace(V, Q, 2.0, -0.5)
+    vb = 2 * (m + 6) * u * (2.0 * np.abs(V) @ np.abs(Q) + 0.5 * np.abs(V))
+    for off in (0, 3):
+        import torch
+
+        def block(a):
+            t = torch.full((n + 1, a.shape[1] + off), 7.0, dtype=torch.float64, device="cuda:0")
+            s = t[:n, off:]
+            s.copy_(torch.from_numpy(a))
+            return t, s
+
+        Vt, Vs = block(V)
+        Wt, Ws = block(W)
+        Gd = dev(np.full((m, k), np.nan))
+        sc.sell_tsmttsm(Vs, Ws, Gd, alpha=1.5)
+        assert (np.abs(host(Gd) - g) <= gb).all()
+        sc.sell_tsmm(Vs, dev(X), Ws, alpha=-0.5, beta=0.25)
+        assert (np.abs(host(Ws) - w) <= wb).all()
+        sc.sell_tsmm_inplace(Vs, dev(Q), alpha=2.0, beta=-0.5)
+        assert (np.abs(host(Vs) - v) <= vb).all()
+        for t in (Vt, Wt):
+            assert (host(t)[n] == 7.0).all() and (host(t)[:, :off] == 7.0).all()
+
+
+def test_matrix_core_blocks_keep_nonfinite_entries_in_their_places(sc):
+    """A NaN or an infinity touches the row (V X) or the row and column (V^T W) it belongs to and
+    nothing else, padding of the 16 x 16 x 4 blocks included."""
+    n, m, k = 100, 35, 21
+    V, W, X = synth.block_vector(n, m, 174), synth.block_vector(n, k, 175), synth.block_vector(m, k, 176)
+    V[41, 34], W[99, 20] = np.nan, np.inf
+    Gd, Wd = dev(np.zeros((m, k))), dev(W)
+    sc.sell_tsmttsm(dev(V), Wd, Gd)
+    bad = ~np.isfinite(host(Gd))
+    want = np.zeros((m, k), bool)
+    want[34, :] = want[:, 20] = True
+    assert np.array_equal(bad, want)
+    sc.sell_tsmm(dev(V), dev(X), Wd)
+    bad = ~np.isfinite(host(Wd))
+    want = np.zeros((n, k), bool)
+    want[41, :] = True
+    assert np.array_equal(bad, want)
