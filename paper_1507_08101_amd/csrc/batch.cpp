@@ -24,9 +24,9 @@
 using namespace sellcs;
 
 namespace sellcs {
-const void *batch_kernel_f64(int b, int vpt, bool aug, bool fixed_ok, int ub, int ubw, uint32_t flags);
-const void *batch_kernel_f32(int b, int vpt, bool aug, bool fixed_ok, int ub, int ubw, uint32_t flags);
-const void *batch_kernel_bf16(int b, int vpt, bool aug, bool fixed_ok, int ub, int ubw, uint32_t flags);
+const void *batch_kernel_f64(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
+const void *batch_kernel_f32(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
+const void *batch_kernel_bf16(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
 const void *batch_mixed_kernel_f64(bool aug);
 const void *batch_mixed_kernel_f32(bool aug);
 const void *batch_mixed_kernel_bf16(bool aug);
@@ -280,11 +280,13 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
                       "4, 8, 16, 32, or rows that are not row-major and %d-byte aligned): the run-time-width "
                       "kernel runs",
                       b, align);
+    const bool contig = b > 1 && xcs == 1 && ycs == 1 && (!chain || zcs == 1);
+    const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     const int ub = B->batch_len, ubw = B->batch_len_wide;
     const uint32_t kflags = aug ? o.flags : 0u;  // every matrix of the launch has these flags
-    const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, fixed_ok, ub, ubw, kflags)
-                       : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, fixed_ok, ub, ubw, kflags)
-                                         : batch_kernel_bf16(b, vpt, aug, fixed_ok, ub, ubw, kflags);
+    const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, path, ub, ubw, kflags)
+                       : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, path, ub, ubw, kflags)
+                                         : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags);
     // workgroups per matrix: waves of the resident grid split so that the busiest workgroup
     // has as little work as possible
     const int32_t G0 = product_grid(B, kern);
@@ -341,11 +343,9 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
     if (out_blk) *out_blk = d_blk;
     if (out_partials) *out_partials = B->partials;
     if (G > 0) {
-        int vl_log2 = 0;
-        if (!fixed_ok)
-            while ((1 << vl_log2) < b) ++vl_log2;
+        int vl = path == kPathFixed ? 0 : run_time_lanes(b, path == kPathContig);
         int Karg = K;
-        void *args[] = {&d_tab, &d_blk, &Karg, &active, &vl_log2};
+        void *args[] = {&d_tab, &d_blk, &Karg, &active, &vl};
         HIPCHK(hipLaunchKernel(kern, dim3(unsigned(G)), dim3(kBlock), args, 0, s));
     }
     if (dots && finish) {

@@ -199,6 +199,23 @@ struct ProdArgs {
 
 enum VecKind { VK_F64F64 = 0, VK_F32F32 = 1, VK_BF16F32 = 2 };
 
+// The product kernels that can serve a launch: compiled width with aligned rows; run-time width
+// with contiguous rows; run-time width with any strides.
+enum ProdPath { kPathAny = 0, kPathContig = 1, kPathFixed = 2 };
+// Columns and lanes per row of the run-time-width kernel for contiguous rows of b >= 2 columns: the
+// fewest lanes of at most 4 columns, and the fewest columns those lanes can have.
+inline int run_time_vpt(int b) {
+    const int lanes = (b + 3) / 4;
+    return (b + lanes - 1) / lanes;
+}
+// Its lane argument: the lanes per row, or with any strides (one column per lane) the binary
+// logarithm of the power of two that holds b.
+inline int run_time_lanes(int b, bool contig) {
+    if (contig) return (b + 3) / 4;
+    int l = 0;
+    while ((1 << l) < b) ++l;
+    return l;
+}
 int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s);
 int launch_transpose_atomic(ProdArgs &a, int vk, hipStream_t s);
 int launch_fill(void *p, int dt, int64_t nrows, int32_t ncols, int64_t rs, int64_t cs,

@@ -88,41 +88,80 @@ __device__ __forceinline__ SELL_GLOBAL T *to_global(T *p) {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-// VPT consecutive elements at p (element stride cs). VEC: cs == 1 and p aligned to
-// min(16, VPT * sizeof(X)) bytes, so the row piece moves as 8- or 16-byte vector accesses.
-template <class X, int VPT, bool VEC>
+// 16-byte pieces of rows aligned to their element only (4 bytes): one load or store all the same,
+// since global memory takes any 4-byte aligned address.
+typedef unsigned int u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// How the rows of the block vectors lie: element stride as given (kStrided), contiguous and
+// aligned to the element (kContig), or contiguous with row pieces aligned to min(16, VPT *
+// sizeof(X)) bytes (kAligned).
+enum RowMode { kStrided, kContig, kAligned };
+
+// VPT consecutive elements at p (element stride cs), as 16-, 8- and 4-byte vector accesses where
+// the rows are contiguous.
+template <class X, int VPT, RowMode MODE>
 __device__ __forceinline__ void load_row(const SELL_GLOBAL X *p, int64_t cs, X (&o)[VPT]) {
     constexpr int bytes = VPT * int(sizeof(X));
-    if constexpr (VEC && bytes % 16 == 0) {
+    if constexpr (MODE == kAligned && bytes % 16 == 0) {
 #pragma unroll
         for (int q = 0; q < bytes / 16; ++q) {
             const u32x4 v = reinterpret_cast<const SELL_GLOBAL u32x4 *>(p)[q];
             __builtin_memcpy(reinterpret_cast<char *>(o) + 16 * q, &v, 16);
         }
-    } else if constexpr (VEC && bytes == 8) {
+    } else if constexpr (MODE == kAligned && bytes == 8) {
         const u32x2 v = *reinterpret_cast<const SELL_GLOBAL u32x2 *>(p);
         __builtin_memcpy(o, &v, 8);
+    } else if constexpr (MODE == kContig) {
+        const SELL_GLOBAL char *b = reinterpret_cast<const SELL_GLOBAL char *>(p);
+#pragma unroll
+        for (int q = 0; q < bytes / 16; ++q) {
+            const u32x4u v = *reinterpret_cast<const SELL_GLOBAL u32x4u *>(b + 16 * q);
+            __builtin_memcpy(reinterpret_cast<char *>(o) + 16 * q, &v, 16);
+        }
+        if constexpr (bytes % 16 >= 8) {
+            const u32x2u v = *reinterpret_cast<const SELL_GLOBAL u32x2u *>(b + bytes / 16 * 16);
+            __builtin_memcpy(reinterpret_cast<char *>(o) + bytes / 16 * 16, &v, 8);
+        }
+        if constexpr (bytes % 8 == 4) o[VPT - 1] = p[VPT - 1];
     } else {
 #pragma unroll
         for (int t = 0; t < VPT; ++t) o[t] = p[t * cs];
     }
 }
 
-// Row stores are nontemporal: the product never reads its outputs again in the same launch.
-template <class X, int VPT, bool VEC>
+// Row stores are nontemporal: the product never reads its outputs again in the same launch. Not so
+// for kContig, whose pieces fill lines less well (96^3 Anderson matrix, FP64: b = 7 45.7 us
+// nontemporal, 43.3 ordinary; b = 12 with chain 131 and 127; from b = 33 on nontemporal would win,
+// 201 against 228).
+template <class X, int VPT, RowMode MODE>
 __device__ __forceinline__ void store_row(SELL_GLOBAL X *p, int64_t cs, const X (&o)[VPT]) {
     constexpr int bytes = VPT * int(sizeof(X));
-    if constexpr (VEC && bytes % 16 == 0) {
+    if constexpr (MODE == kAligned && bytes % 16 == 0) {
 #pragma unroll
         for (int q = 0; q < bytes / 16; ++q) {
             u32x4 v;
             __builtin_memcpy(&v, reinterpret_cast<const char *>(o) + 16 * q, 16);
             __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x4 *>(p) + q);
         }
-    } else if constexpr (VEC && bytes == 8) {
+    } else if constexpr (MODE == kAligned && bytes == 8) {
         u32x2 v;
         __builtin_memcpy(&v, o, 8);
         __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x2 *>(p));
+    } else if constexpr (MODE == kContig) {
+        SELL_GLOBAL char *b = reinterpret_cast<SELL_GLOBAL char *>(p);
+#pragma unroll
+        for (int q = 0; q < bytes / 16; ++q) {
+            u32x4u v;
+            __builtin_memcpy(&v, reinterpret_cast<const char *>(o) + 16 * q, 16);
+            *reinterpret_cast<SELL_GLOBAL u32x4u *>(b + 16 * q) = v;
+        }
+        if constexpr (bytes % 16 >= 8) {
+            u32x2u v;
+            __builtin_memcpy(&v, reinterpret_cast<const char *>(o) + bytes / 16 * 16, 8);
+            *reinterpret_cast<SELL_GLOBAL u32x2u *>(b + bytes / 16 * 16) = v;
+        }
+        if constexpr (bytes % 8 == 4) p[VPT - 1] = o[VPT - 1];
     } else {
 #pragma unroll
         for (int t = 0; t < VPT; ++t) p[t * cs] = o[t];
@@ -140,20 +179,28 @@ constexpr int kBatchDefault = 8;
 //        the block vectors are row-major with rows aligned for vector accesses (VEC).
 // B == 0: run-time width nb <= 64, one column per lane, VL = next power of two >= nb,
 //         any strides.
+// B < 0:  run-time width nb, VPT <= nb <= 64, contiguous rows of any alignment: VL = vl lanes per
+//         row with VPT columns each, 64 / VL rows per wave (VL need not be a power of two; the
+//         lanes left over idle). The last lane's piece is shifted back to end at column nb - 1:
+//         it computes columns that its neighbour has too, the same values, and leaves their dots
+//         to the neighbour. With one 4- or 8-byte element per lane (B == 0) such widths moved half
+//         the bytes per gather and left up to half of the lanes idle: 96^3 Anderson matrix, FP64,
+//         b = 3 50.6 -> 25.2 us, b = 12 177 -> 75, b = 33 712 -> 228, b = 64 801 -> 456; FP32 b = 3
+//         with <y,y> and <x,y> 38.1 -> 21.2.
 // The product over the tiles of workgroup `tile` (one of a.nblocks) of one matrix.
 // FL != 0: the augmentation flags are known at compile time (a.flags == FL), so the unused
 // parts of the epilogue take no registers.
 template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0>
-__device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, const int vl_log2) {
+__device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, const int vl) {
     using V = typename KTypes<VK>::V;
     using X = typename KTypes<VK>::X;
     using Acc = typename KTypes<VK>::Acc;
-    constexpr bool DYN = (B == 0);
-    constexpr bool VEC = !DYN;
+    constexpr bool DYN = (B == 0), GEN = (B < 0);
+    constexpr RowMode VEC = DYN ? kStrided : GEN ? kContig : kAligned;
     constexpr int U = UB > 0 ? UB : kBatchDefault;
-    const int nb = DYN ? a.nb : B;
-    const int VL = DYN ? (1 << vl_log2) : (B / VPT);
-    const int vls = DYN ? vl_log2 : __builtin_ctz(B / VPT);
+    const int nb = DYN || GEN ? a.nb : B;
+    const int VL = DYN ? (1 << vl) : GEN ? vl : (B / VPT);
+    const int vls = DYN ? vl : GEN ? 0 : __builtin_ctz(B / VPT);
 
     // the diagonal entry from the row's own x (see the gathers below): kernels with compile-time
     // flags whose lanes gather 32 bytes
@@ -196,10 +243,13 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     };
     int64_t s_begin = 0, s_end = 0;
     const int tid = threadIdx.x;
-    const int vg = tid & (VL - 1);
-    const int rows_per_pass = kBlock >> vls;
-    const int jb = vg * VPT;
-    const bool col_ok = DYN ? (vg < nb) : true;
+    const int wrows = GEN ? 64 / VL : 0, wslot = GEN ? (tid & 63) / VL : 0;  // GEN: rows per wave, the lane's
+    const int vg = GEN ? (tid & 63) - wslot * VL : tid & (VL - 1);
+    const int rows_per_pass = GEN ? (kBlock / 64) * wrows : kBlock >> vls;
+    // row slot of this lane within a pass (GEN: the lanes left over take a row of their wave, unused)
+    const int rslot = GEN ? (tid >> 6) * wrows + (wslot < wrows ? wslot : 0) : tid >> vls;
+    const int jb = GEN && vg * VPT > nb - VPT ? nb - VPT : vg * VPT;
+    const bool col_ok = DYN ? (vg < nb) : GEN ? wslot < wrows : true;
 
     const SELL_GLOBAL V *__restrict__ val = to_global(static_cast<const V *>(a.val));
     const SELL_GLOBAL int32_t *__restrict__ col = to_global(a.col);
@@ -208,9 +258,9 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     // the y that beta y reads: Y itself (offset 0) or another block with Y's strides
     const SELL_GLOBAL X *Yi = reinterpret_cast<const SELL_GLOBAL X *>(reinterpret_cast<SELL_GLOBAL char *>(Yp) + a.yi_off);
     SELL_GLOBAL X *__restrict__ Zp = to_global(static_cast<X *>(a.Z));
-    const int64_t xrs = a.xrs, xcs = VEC ? 1 : a.xcs;
-    const int64_t yrs = a.yrs, ycs = VEC ? 1 : a.ycs;
-    const int64_t zrs = a.zrs, zcs = VEC ? 1 : a.zcs;
+    const int64_t xrs = a.xrs, xcs = VEC != kStrided ? 1 : a.xcs;
+    const int64_t yrs = a.yrs, ycs = VEC != kStrided ? 1 : a.ycs;
+    const int64_t zrs = a.zrs, zcs = VEC != kStrided ? 1 : a.zcs;
 
     const uint32_t fl = FL ? FL : a.flags;
     const bool want_dots = AUG && (fl & SELL_SPMV_DOTS);
@@ -393,7 +443,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
         if (!AUG) {
 #pragma unroll
             for (int t = 0; t < VPT; ++t) out[t] = X(acc[t]);
-            store_row<X, VPT, VEC>(ydst, ysd, out);
+            if (!GEN || col_ok) store_row<X, VPT, VEC>(ydst, ysd, out);
         } else {
             X zout[VPT];
 #pragma unroll
@@ -414,8 +464,8 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
                 if (read_z) z = delta * double(zin[t]) + z;
                 zout[t] = X(z);
             }
-            store_row<X, VPT, VEC>(ydst, ysd, out);
-            if (chain) {
+            if (!GEN || col_ok) store_row<X, VPT, VEC>(ydst, ysd, out);
+            if (chain && (!GEN || col_ok)) {
                 SELL_GLOBAL X *zdst = live ? Zp + row * zrs + int64_t(jb) * zcs : scratch;
                 store_row<X, VPT, VEC>(zdst, live ? zcs : 1, zout);
             }
@@ -426,7 +476,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
         const int64_t t0 = int64_t(tile) * a.ntiles / a.nblocks, t1 = int64_t(tile + 1) * a.ntiles / a.nblocks;
         s_begin = int64_t(tiles[t0]) * C;
         s_end = int64_t(tiles[t1]) * C;
-        int64_t s = s_begin + (tid >> vls);
+        int64_t s = s_begin + rslot;
         int cl_n = 0, pv_n = 0;
         int64_t cs_n = 0;
         if (s_begin < s_end) load_meta(s, s_end, cl_n, cs_n, pv_n);
@@ -469,7 +519,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
         int64_t pb = s_begin;  // first slot of the current pass
         int cl_n = 0, pv_n = 0;
         int64_t cs_n = 0;
-        if (r_count > 0 && s_begin < s_end) load_meta(pb + (tid >> vls), s_end, cl_n, cs_n, pv_n);
+        if (r_count > 0 && s_begin < s_end) load_meta(pb + rslot, s_end, cl_n, cs_n, pv_n);
         // Settle the first pass's metadata here, so that at the loop head only the previous
         // pass's stores are outstanding and the metadata loads of the following pass are not
         // held up behind them.
@@ -507,12 +557,12 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
                     npb = nsb;
                 }
             }
-            const int64_t s = pb + (tid >> vls);
+            const int64_t s = pb + rslot;
             const int64_t c = cshift >= 0 ? (s >> cshift) : int64_t(uint32_t(s) / uint32_t(C));
             const int len = s < s_end ? cl_n : 0;
             const int64_t base = cs_n + (s - c * C);
             const int64_t row = s < s_end && s < nrows ? (perm ? int64_t(pv_n) : s) : -1;
-            if (nrr < r_count && nsb < nse) load_meta(npb + (tid >> vls), nse, cl_n, cs_n, pv_n);  // one pass ahead
+            if (nrr < r_count && nsb < nse) load_meta(npb + rslot, nse, cl_n, cs_n, pv_n);  // one pass ahead
             pass_body(s, len, base, row, staged, own_pos, own_p0, half);
             if (nrr != rr) {
                 // last pass of unit ta
@@ -548,15 +598,30 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     const int w = tid >> 6;
 #pragma unroll
     for (int t = 0; t < VPT; ++t) {
-        for (int m = 32; m >= VL; m >>= 1) {
-            dyy[t] += shfl_xor_d(dyy[t], m);
-            dxy[t] += shfl_xor_d(dxy[t], m);
-            dxx[t] += shfl_xor_d(dxx[t], m);
+        if constexpr (GEN) {
+            // rows of the wave folded onto its first: the upper half of the rows left onto the lower
+            for (int left = wrows; left > 1;) {
+                const int half = (left + 1) / 2;
+                const bool add = wslot + half < left;
+                const int from = (lane + half * VL) & 63;
+                const double yy = __shfl(dyy[t], from, 64), xy = __shfl(dxy[t], from, 64), xx = __shfl(dxx[t], from, 64);
+                dyy[t] += add ? yy : 0.0;
+                dxy[t] += add ? xy : 0.0;
+                dxx[t] += add ? xx : 0.0;
+                left = half;
+            }
+        } else {
+            for (int m = 32; m >= VL; m >>= 1) {
+                dyy[t] += shfl_xor_d(dyy[t], m);
+                dxy[t] += shfl_xor_d(dxy[t], m);
+                dxx[t] += shfl_xor_d(dxx[t], m);
+            }
         }
     }
     if (lane < VL && col_ok) {
 #pragma unroll
         for (int t = 0; t < VPT; ++t) {
+            if (GEN && jb + t < vg * VPT) continue;  // the neighbour's column
             red[w][jb + t] = dyy[t];
             red[w][nb + jb + t] = dxy[t];
             red[w][2 * nb + jb + t] = dxx[t];
@@ -575,14 +640,9 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
 }
 
 template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0>
-__global__ void __launch_bounds__(kBlock) prod_kernel(ProdArgs a, int vl_log2) {
+__global__ void __launch_bounds__(kBlock) prod_kernel(ProdArgs a, int vl) {
     const int tile = a.xcd_map ? xcd_block(blockIdx.x, gridDim.x) : int(blockIdx.x);  // index in the partials
-    int vls = vl_log2;
-    if (B == 0 && vls < 0) {
-        vls = 0;
-        while ((1 << vls) < a.nb) ++vls;
-    }
-    prod_body<VK, B, VPT, AUG, UB, STG, FL>(a, tile, vls);
+    prod_body<VK, B, VPT, AUG, UB, STG, FL>(a, tile, vl);
 }
 
 // The flags of a step of the Chebyshev / KPM recurrence (y = alpha (A x - c x) - y with
@@ -602,13 +662,11 @@ constexpr uint32_t kCgFlags = SELL_SPMV_DOT_YY | SELL_SPMV_DOT_XY;
 
 // One launch over a batch of matrices: workgroups [blk_start[m], blk_start[m+1]) of the
 // (XCD-remapped) grid work on matrix m, whose launch arguments are table[m]. A matrix m with
-// active != null and active[m] == 0 is skipped (its dot partials are zeroed). With the
-// run-time-width kernel (B == 0) and vl_log2 < 0 every matrix gets the lanes per row of its
-// own width (table[m].nb), so matrices of different block widths share the launch.
+// active != null and active[m] == 0 is skipped (its dot partials are zeroed).
 template <int VK, int B, int VPT, bool AUG, int UB = 0, uint32_t FL = 0>
 __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__restrict__ table,
                                                             const int32_t *__restrict__ blk_start, int K,
-                                                            const int32_t *__restrict__ active, int vl_log2) {
+                                                            const int32_t *__restrict__ active, int vl) {
     const int g = xcd_block(blockIdx.x, gridDim.x);
     int lo = 0, hi = K;
     while (hi - lo > 1) {
@@ -625,12 +683,7 @@ __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__re
             for (int q = threadIdx.x; q < 3 * a.nb; q += kBlock) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
         return;
     }
-    int vls = vl_log2;
-    if (B == 0 && vls < 0) {
-        vls = 0;
-        while ((1 << vls) < a.nb) ++vls;
-    }
-    prod_body<VK, B, VPT, AUG, UB, false, FL>(a, tile, vls);
+    prod_body<VK, B, VPT, AUG, UB, false, FL>(a, tile, vl);
 }
 
 // A batch whose matrices have block widths of their own, in one launch: every workgroup runs
@@ -718,27 +771,24 @@ __global__ void __launch_bounds__(kBlock) transpose_kernel(ProdArgs a, int vl_lo
 
 template <int VK, int B, int VPT, bool AUG, int UB = 0>
 inline int go_prod_u(ProdArgs &a, hipStream_t s) {
-    int vl_log2 = 0;
-    if (B == 0) {
-        while ((1 << vl_log2) < a.nb) ++vl_log2;
-    }
+    const int vl = B > 0 ? 0 : run_time_lanes(a.nb, B < 0);
     using X = typename KTypes<VK>::X;
     // x through the LDS page cache: fixed widths over contiguous, 16-byte aligned rows
     if (a.stage && !(B > 0 && B * sizeof(X) >= 16 && a.xrs == B && a.xcs == 1 && a.lcol && a.st_slot &&
                      (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0))
         a.stage = 0;
     auto k = a.stage ? prod_kernel<VK, B, VPT, AUG, UB, (B > 0)> : prod_kernel<VK, B, VPT, AUG, UB>;
-    if constexpr (AUG && VK == VK_F64F64 && B > 0) {
+    if constexpr (AUG && VK == VK_F64F64 && B != 0) {
         if (!a.stage && a.flags == kKpmFlags)
             k = prod_kernel<VK, B, VPT, AUG, UB, false, kKpmFlags>;
     }
-    if constexpr (AUG && VK != VK_F64F64 && B > 0) {
+    if constexpr (AUG && VK != VK_F64F64 && B != 0) {
         if (!a.stage && a.flags == kCgFlags)
             k = prod_kernel<VK, B, VPT, AUG, UB, false, kCgFlags>;
     }
     if (a.stage) {
         a.nblocks = a.st_nblocks;  // the launch the plan was made for (stride checked there)
-        hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(kBlock), 0, s, a, vl_log2);
+        hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(kBlock), 0, s, a, vl);
         return hipGetLastError() == hipSuccess ? SELL_OK : SELL_ERR_HIP;
     }
     // Lanes that gather 32 bytes per entry (FP64 rows, 4 columns per lane) run one workgroup per
@@ -753,7 +803,7 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
     if (a.waves_hint > 1) a.nblocks = int32_t(std::min<int64_t>(int64_t(a.nblocks) * a.waves_hint, a.ntiles));
     // a tile stride needs whole columns of tiles and of workgroups
     a.tile_stride = 0;  // a unit stride applies to staged launches only
-    hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(kBlock), 0, s, a, vl_log2);
+    hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(kBlock), 0, s, a, vl);
     return hipGetLastError() == hipSuccess ? SELL_OK : SELL_ERR_HIP;
 }
 
@@ -764,7 +814,7 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
 template <int VK, int B, int VPT, bool AUG>
 inline int go_prod(ProdArgs &a, hipStream_t s) {
     using X = typename KTypes<VK>::X;
-    if constexpr (B > 0) {
+    if constexpr (B != 0) {
         const int hint = VPT * sizeof(X) >= 32 ? a.batch_hint_wide : a.batch_hint;
         if (hint == 7) return go_prod_u<VK, B, VPT, AUG, 7>(a, s);
         if (hint == 5) return go_prod_u<VK, B, VPT, AUG, 5>(a, s);
@@ -786,10 +836,10 @@ inline int go_transpose(ProdArgs &a, hipStream_t s) {
 
 
 template <int VK, bool AUG>
-int dispatch_prod(ProdArgs &a, hipStream_t s, bool fixed_ok) {
+int dispatch_prod(ProdArgs &a, hipStream_t s, int path) {
     const int b = a.nb;
     const int vpt = choose_vpt(VK, b, a.vpt_hint);
-    if (fixed_ok) {
+    if (path == kPathFixed) {
         switch (b) {
             case 1: return go_prod<VK, 1, 1, AUG>(a, s);
             case 2: return vpt >= 2 ? go_prod<VK, 2, 2, AUG>(a, s) : go_prod<VK, 2, 1, AUG>(a, s);
@@ -808,12 +858,19 @@ int dispatch_prod(ProdArgs &a, hipStream_t s, bool fixed_ok) {
             default: break;
         }
     }
+    if (path == kPathContig) {
+        switch (run_time_vpt(b)) {
+            case 2: return go_prod<VK, -1, 2, AUG>(a, s);
+            case 3: return go_prod<VK, -1, 3, AUG>(a, s);
+            default: return go_prod<VK, -1, 4, AUG>(a, s);
+        }
+    }
     return go_prod<VK, 0, 1, AUG>(a, s);
 }
 
 template <int VK, int B, int VPT, bool AUG, int UB = 0>
 inline const void *bk_u(bool cg) {
-    if constexpr (AUG && VK != VK_F64F64 && B > 0) {
+    if constexpr (AUG && VK != VK_F64F64 && B != 0) {
         if (cg) return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB, kCgFlags>);
     }
     return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB>);
@@ -825,7 +882,7 @@ inline const void *bk_u(bool cg) {
 template <int VK, int B, int VPT, bool AUG>
 inline const void *bk(int ub0, int ubw, bool cg) {
     using X = typename KTypes<VK>::X;
-    if constexpr (B > 0) {
+    if constexpr (B != 0) {
         const int ub = VPT * sizeof(X) >= 32 ? ubw : ub0;
         if (ub == 7) return bk_u<VK, B, VPT, AUG, 7>(cg);
         if (ub == 5) return bk_u<VK, B, VPT, AUG, 5>(cg);
@@ -833,12 +890,12 @@ inline const void *bk(int ub0, int ubw, bool cg) {
     return bk_u<VK, B, VPT, AUG>(cg);
 }
 
-// The batched kernel for (width, columns per lane, index batch length); fixed_ok as in
+// The batched kernel for (width, columns per lane, index batch length); path as in
 // dispatch_prod.
 template <int VK, bool AUG>
-const void *batch_kernel_for(int b, int vpt, bool fixed_ok, int ub, int ubw, uint32_t flags) {
+const void *batch_kernel_for(int b, int vpt, int path, int ub, int ubw, uint32_t flags) {
     const bool cg = flags == kCgFlags;
-    if (fixed_ok) {
+    if (path == kPathFixed) {
         switch (b) {
             case 1: return bk<VK, 1, 1, AUG>(ub, ubw, cg);
             case 2: return vpt >= 2 ? bk<VK, 2, 2, AUG>(ub, ubw, cg) : bk<VK, 2, 1, AUG>(ub, ubw, cg);
@@ -849,6 +906,13 @@ const void *batch_kernel_for(int b, int vpt, bool fixed_ok, int ub, int ubw, uin
             case 32:
                 return vpt >= 4 ? bk<VK, 32, 4, AUG>(ub, ubw, cg) : vpt == 2 ? bk<VK, 32, 2, AUG>(ub, ubw, cg) : bk<VK, 32, 1, AUG>(ub, ubw, cg);
             default: break;
+        }
+    }
+    if (path == kPathContig) {
+        switch (run_time_vpt(b)) {
+            case 2: return bk<VK, -1, 2, AUG>(ub, ubw, cg);
+            case 3: return bk<VK, -1, 3, AUG>(ub, ubw, cg);
+            default: return bk<VK, -1, 4, AUG>(ub, ubw, cg);
         }
     }
     return bk<VK, 0, 1, AUG>(ub, ubw, cg);

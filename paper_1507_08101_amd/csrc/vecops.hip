@@ -11,9 +11,9 @@
 
 namespace sellcs {
 
-int prod_f64(ProdArgs &a, bool aug, bool fixed_ok, hipStream_t s);
-int prod_f32(ProdArgs &a, bool aug, bool fixed_ok, hipStream_t s);
-int prod_bf16(ProdArgs &a, bool aug, bool fixed_ok, hipStream_t s);
+int prod_f64(ProdArgs &a, bool aug, int path, hipStream_t s);
+int prod_f32(ProdArgs &a, bool aug, int path, hipStream_t s);
+int prod_bf16(ProdArgs &a, bool aug, int path, hipStream_t s);
 int transpose_f64(ProdArgs &a, hipStream_t s);
 int transpose_f32(ProdArgs &a, hipStream_t s);
 int transpose_bf16(ProdArgs &a, hipStream_t s);
@@ -87,10 +87,12 @@ int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s) {
                           "strided or offset views): the run-time-width kernel runs",
                           align);
     }
+    const bool contig = a.nb > 1 && a.xcs == 1 && a.ycs == 1 && (!(aug && (a.flags & SELL_SPMV_CHAIN)) || a.zcs == 1);
+    const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     switch (vk) {
-        case VK_F64F64: return prod_f64(a, aug, fixed_ok, s);
-        case VK_F32F32: return prod_f32(a, aug, fixed_ok, s);
-        case VK_BF16F32: return prod_bf16(a, aug, fixed_ok, s);
+        case VK_F64F64: return prod_f64(a, aug, path, s);
+        case VK_F32F32: return prod_f32(a, aug, path, s);
+        case VK_BF16F32: return prod_bf16(a, aug, path, s);
         default: return SELL_ERR_DTYPE;
     }
 }

@@ -485,3 +485,76 @@ def test_device_export_round_trip(sc):
     ocol, oval = oracle.sell_fill(A, 16, operm, ocl, ocs)
     assert np.array_equal(perm, operm) and np.array_equal(scol, ocol) and np.array_equal(sval, oval)
     M.close()
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("b,ld,off", [(2, 3, 1), (3, 3, 0), (4, 5, 1), (5, 5, 0), (6, 6, 0), (7, 11, 3), (8, 9, 0), (9, 9, 0),
+                                      (10, 10, 0), (12, 12, 0), (16, 17, 1), (21, 21, 0), (32, 33, 1), (33, 33, 0), (45, 45, 0),
+                                      (61, 61, 0), (64, 64, 0), (64, 67, 2)])
+def test_contiguous_rows_of_any_width_equal_the_strided_kernel(sc, b, ld, off, dt):
+    """The run-time-width kernel for contiguous rows (pieces of 2 to 4 columns, rows per wave that do
+    not fill it, unaligned rows, slices of wider blocks) against the any-strides kernel on the same
+    values held column-major: y and z bit for bit, the dots of the final y within a fixed-order FP64
+    sum's error, nothing written beside the block, for every index batch length."""
+    import torch
+
+    A = synth.random_sparse(1003, 1003, 0.008, 190, duplicates=True, empty_rows=11, long_row=90)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=128, dtype=dt)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    n = A.nrows
+    flags = sc.VSHIFT | sc.SCALE | sc.AXPBY | sc.DOTS | sc.CHAIN
+    kw = dict(flags=flags, alpha=0.7, beta=-0.3, gamma_v=np.linspace(-1, 1, b), delta=0.5, eta=-2.0)
+
+    def rows(seed):
+        t = torch.full((n + 1, ld), 9.0, dtype=vt, device="cuda:0")
+        s = t[:n, off:off + b]
+        s.copy_(torch.from_numpy(synth.block_vector(n, b, seed)))
+        return t, s
+
+    for batch in (5, 7, 8):
+        M.set_batch(batch)
+        (xt, x), (yt, y), (zt, z) = rows(191), rows(192), rows(193)
+        xc, yc, zc = (v.t().contiguous().t() for v in (x, y, z))
+        dot, dotc = (torch.zeros(3 * b, dtype=torch.float64, device="cuda:0") for _ in range(2))
+        sc.sell_spmmv_aug(M, x, y, z, dot=dot, **kw)
+        sc.sell_spmmv_aug(M, xc, yc, zc, dot=dotc, **kw)
+        assert torch.equal(y, yc) and torch.equal(z, zc)
+        xd, yd = xc.double(), yc.double()
+        mag = torch.cat([(yd * yd).sum(0), (xd * yd).abs().sum(0), (xd * xd).sum(0)])
+        assert bool(((dot - dotc).abs() <= 2 * (n + 8) * 2.0 ** -53 * mag).all())
+        for t in (xt, yt, zt):
+            assert bool((t[n] == 9.0).all()) and bool((t[:, :off] == 9.0).all()) and bool((t[:, off + b:] == 9.0).all())
+        sc.sell_spmmv(M, x, y)
+        sc.sell_spmmv(M, xc, yc)
+        assert torch.equal(y, yc)
+    M.close()
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("b", [3, 6, 12, 33, 64])
+def test_batch_of_any_width_equals_single_products(sc, b, dt):
+    """A uniform batch at a width without a compiled kernel: y bit for bit the single products'."""
+    import torch
+
+    mats = [synth.anderson3d(6), synth.random_sparse(700, 700, 0.01, 194, empty_rows=5), synth.laplacian2d(23)]
+    Ms = [sc.SellMatrix.from_csr(A, C=32, sigma=32, dtype=dt) for A in mats]
+    B = sc.SellBatch(Ms)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    X = torch.from_numpy(synth.block_vector(B.cols, b, 195)).to("cuda:0", vt)
+    Y = torch.zeros((B.rows, b), dtype=vt, device="cuda:0")
+    dot = torch.zeros(3 * b * len(mats), dtype=torch.float64, device="cuda:0")
+    sc.sell_batch_spmmv_aug(B, X, Y, flags=sc.DOT_YY | sc.DOT_XY, dot=dot)
+    at = 0
+    for k, (A, M) in enumerate(zip(mats, Ms)):
+        y = torch.zeros((A.nrows, b), dtype=vt, device="cuda:0")
+        d = torch.zeros(3 * b, dtype=torch.float64, device="cuda:0")
+        x = X[at:at + A.nrows]
+        sc.sell_spmmv_aug(M, x, y, flags=sc.DOT_YY | sc.DOT_XY, dot=d)
+        assert torch.equal(y, Y[at:at + A.nrows])
+        xd, yd = x.double(), y.double()
+        mag = torch.cat([(yd * yd).sum(0), (xd * yd).abs().sum(0), torch.zeros(b, dtype=torch.float64, device="cuda:0")])
+        assert bool(((dot[3 * b * k:3 * b * (k + 1)] - d).abs() <= 2 * (A.nrows + 8) * 2.0 ** -53 * mag).all())
+        at += A.nrows
+    B.close()
+    for M in Ms:
+        M.close()
