@@ -2,8 +2,8 @@
 //
 // The batch's block vectors hold the matrices' operands one after another: matrix m reads
 // rows [col_off[m], col_off[m+1]) of X and writes rows [row_off[m], row_off[m+1]) of Y. One
-// launch of the batched product kernel covers every matrix: sixteen waves of the device's resident
-// workgroups are split over the matrices by their cost (stored entries plus rows) so that the
+// launch of the batched product kernel covers every matrix: up to sixteen waves of the device's
+// resident workgroups are split over the matrices by their cost (stored entries plus rows) so that the
 // busiest workgroup has as little work as possible, and each workgroup finds its matrix's launch arguments in a table in device memory by a binary
 // search over the workgroup offsets. The tables are staged through pinned host memory into a
 // few device slots; a call whose table equals one already on the device (the same operands
@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <new>
 #include <queue>
@@ -77,6 +78,8 @@ struct sell_batch {
     int32_t batch_len = 8;               // index batch length shared by all matrices (else 8)
     int32_t batch_len_wide = 8;          // the same for the kernels gathering 32 bytes per lane
     std::map<int32_t, std::vector<int32_t>> blk_cache;  // workgroup offsets per resident grid size
+    std::vector<int32_t> sub_active, sub_blk;            // the last split over a subset of the matrices
+    int32_t sub_G0 = -1;
     // block widths of the matrices for packed operands (empty: not set)
     std::vector<int32_t> widths;
     std::vector<int64_t> xoff, yoff;                       // element offsets of the packed blocks
@@ -169,17 +172,31 @@ void apportion_products(const sell_batch *B, int32_t G0, const int32_t *host_act
 
 namespace {
 
-// Workgroups of a product launch with kernel kern: 16 waves of the resident grid by default. A
-// finer split than one wave balances uneven matrices better, since workgroups that finish early
-// take the next ones (64 Laplacians of edges 20..100 at b = 8: 1.42 ms with 16 waves, 1.68 ms
-// with 2, 1.83 ms with 1; mixed widths 1..32: 2.85 ms against 4.06 ms with 2).
-int32_t product_grid(const sell_batch *B, const void *kern) {
+// The launch shape of a product with kernel kern over matrices of `passes` passes of kBlock
+// threads in all: 16 waves of the resident grid by default, but no workgroup with fewer than three
+// passes on average. A finer split than one wave balances uneven matrices better, since workgroups
+// that finish early take the next ones (64 Laplacians of edges 20..100 at b = 8: 1.42 ms with 16
+// waves, 1.68 ms with 2, 1.83 ms with 1; mixed widths 1..32: 2.85 ms against 4.06 ms with 2), until
+// a workgroup's start and end outweigh its rows: 16 Laplacians of edges 20..48, FP64 with two dots,
+// b = 1 58 us in 16 waves, 20 with three passes each (1: 22, 6: 22); b = 4 41 and 31.
+// Few passes each also make workgroups of half the size the better ones where only one of kBlock
+// threads fits a compute unit (64 Laplacians of edges 20..40, b = 8 with dots, 1.8 passes: 152 us
+// with 512 threads, 110 with 256; edges 20..100, 21 passes: 1,183 with 512, 1,199 with 256).
+struct BatchShape {
+    int32_t G0;
+    int threads;
+};
+BatchShape product_shape(const sell_batch *B, const void *kern, const std::function<int64_t(int)> &passes) {
     static const int32_t waves = [] {
         const char *e = std::getenv("SELLCS_BATCH_WAVES");
         const int v = e ? std::atoi(e) : 16;
         return int32_t(v >= 1 && v <= 32 ? v : 16);
     }();
-    return waves * resident_grid(kern, kBlock, int32_t(std::min<int64_t>(B->total_tiles, 1 << 30)), B->bpc_hint);
+    const int64_t one = resident_grid(kern, kBlock, int32_t(std::min<int64_t>(B->total_tiles, 1 << 30)), B->bpc_hint);
+    BatchShape sh;
+    sh.threads = passes(kBlock) < 8 * waves * one ? block_threads(kern, B->bpc_hint) : kBlock;
+    sh.G0 = int32_t(std::min<int64_t>(waves * one, std::max<int64_t>(1, passes(sh.threads) / 3)));
+    return sh;
 }
 
 // Room for 3 * kMaxSliceCols partials per workgroup of any split of this grid, so that later
@@ -289,12 +306,25 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
                                          : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags);
     // workgroups per matrix: waves of the resident grid split so that the busiest workgroup
     // has as little work as possible
-    const int32_t G0 = product_grid(B, kern);
-    std::vector<int32_t> sub_blk;
+    const BatchShape shape = product_shape(B, kern, [&](int threads) {
+        const int32_t rows = pass_rows(b, vpt, path, threads);
+        int64_t n = 0;
+        for (int m = 0; m < K; ++m)
+            if (!host_active || host_active[m]) n += (B->mats[size_t(m)]->h.nrows + rows - 1) / rows;
+        return n;
+    });
+    const int32_t G0 = shape.G0;
     const std::vector<int32_t> *pblk_h = nullptr;
     if (host_active) {
-        apportion_products(B, G0, host_active, sub_blk);
-        pblk_h = &sub_blk;
+        // the split over a subset is kept for the calls that follow with the same one (a solver's
+        // iterations): at thousands of workgroups it costs the host more than the launch
+        if (B->sub_G0 != G0 || B->sub_active.size() != size_t(K) ||
+            !std::equal(B->sub_active.begin(), B->sub_active.end(), host_active)) {
+            apportion_products(B, G0, host_active, B->sub_blk);
+            B->sub_active.assign(host_active, host_active + K);
+            B->sub_G0 = G0;
+        }
+        pblk_h = &B->sub_blk;
     } else {
         auto hit = B->blk_cache.find(G0);
         if (hit == B->blk_cache.end()) {
@@ -317,6 +347,7 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
         base_args(a, A);
         a.nb = b;
         a.nblocks = blk[size_t(m) + 1] - blk[size_t(m)];
+        a.threads = shape.threads;
         a.tile_stride = 0;
         a.stage = 0;
         a.xrs = xrs;
@@ -346,7 +377,7 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
         int vl = path == kPathFixed ? 0 : run_time_lanes(b, path == kPathContig);
         int Karg = K;
         void *args[] = {&d_tab, &d_blk, &Karg, &active, &vl};
-        HIPCHK(hipLaunchKernel(kern, dim3(unsigned(G)), dim3(kBlock), args, 0, s));
+        HIPCHK(hipLaunchKernel(kern, dim3(unsigned(G)), dim3(unsigned(shape.threads)), args, 0, s));
     }
     if (dots && finish) {
         if (G == 0) {
@@ -389,7 +420,16 @@ int batch_aug_packed_impl(sell_batch *B, const void *X, void *Y, void *Z, const 
     const void *kern = vk == VK_F64F64   ? batch_mixed_kernel_f64(aug)
                        : vk == VK_F32F32 ? batch_mixed_kernel_f32(aug)
                                          : batch_mixed_kernel_bf16(aug);
-    const int32_t G0 = product_grid(B, kern);
+    const BatchShape shape = product_shape(B, kern, [&](int threads) {
+        int64_t n = 0;
+        for (int m = 0; m < K; ++m) {
+            const int w = B->widths[size_t(m)];
+            const int32_t rows = pass_rows(w, w >= 4 ? 4 : w, fixed_width(w) ? kPathFixed : kPathAny, threads);
+            n += (B->mats[size_t(m)]->h.nrows + rows - 1) / rows;
+        }
+        return n;
+    });
+    const int32_t G0 = shape.G0;
     auto hit = B->blk_cache_w.find(G0);
     if (hit == B->blk_cache_w.end()) {
         // workgroups per table position (matrices in width order)
@@ -420,6 +460,7 @@ int batch_aug_packed_impl(sell_batch *B, const void *X, void *Y, void *Z, const 
         base_args(a, A);
         a.nb = w;
         a.nblocks = blk[size_t(p) + 1] - blk[size_t(p)];
+        a.threads = shape.threads;
         a.tile_stride = 0;
         a.stage = 0;
         a.X = xb + B->xoff[size_t(m)] * esize;
@@ -452,7 +493,7 @@ int batch_aug_packed_impl(sell_batch *B, const void *X, void *Y, void *Z, const 
         int Karg = K;
         const int32_t *active = nullptr;
         void *args[] = {&d_tab, &d_blk, &Karg, &active, &vl_log2};
-        HIPCHK(hipLaunchKernel(kern, dim3(unsigned(G)), dim3(kBlock), args, 0, s));
+        HIPCHK(hipLaunchKernel(kern, dim3(unsigned(G)), dim3(unsigned(shape.threads)), args, 0, s));
     }
     if (dots) {
         if (G == 0) return launch_fill(o.dot, SELL_F64, 1, int32_t(3 * B->sum_w), 3 * B->sum_w, 1, 0.0, s);

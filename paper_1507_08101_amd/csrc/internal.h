@@ -160,6 +160,7 @@ struct ProdArgs {
     int32_t ntiles, C;     // fine work partitions of the matrix; chunk height
     int32_t nblocks;       // workgroups of the launch (set by the launcher); workgroup g
                            // owns fine tiles [g * ntiles / nblocks, (g + 1) * ntiles / nblocks)
+    int32_t threads;       // threads per workgroup (kBlock, or half of it: block_threads)
     int32_t cshift;        // log2(C) when C is a power of two, else -1
     int32_t xcd_map;       // 1: give each XCD one contiguous range of tiles
     int32_t vpt_hint;      // columns per lane requested for the matrix (0: default)
@@ -215,6 +216,11 @@ inline int run_time_lanes(int b, bool contig) {
     int l = 0;
     while ((1 << l) < b) ++l;
     return l;
+}
+// Rows that a workgroup of a product works on at once (vpt: columns per lane of a fixed width).
+inline int32_t pass_rows(int b, int vpt, int path, int threads) {
+    if (path == kPathFixed) return threads / (b / vpt);
+    return path == kPathContig ? threads / 64 * (64 / run_time_lanes(b, true)) : threads >> run_time_lanes(b, false);
 }
 int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s);
 int launch_transpose_atomic(ProdArgs &a, int vk, hipStream_t s);
@@ -315,6 +321,14 @@ int check_aug_call(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, 
 // kernel times the compute units), at most the number of fine tiles.
 // blocks_per_cu > 0 lowers the workgroups per compute unit to at most that many.
 int32_t resident_grid(const void *kernel, int threads, int32_t ntiles, int32_t blocks_per_cu = 0);
+// Threads per workgroup of a product grid of several waves of workgroups: kBlock, or half of it for
+// a kernel whose registers let only one workgroup of kBlock threads onto a compute unit. Nothing
+// would then run there while a workgroup starts up and ends; of half the size three fit: the
+// irregular matrix of 2 M rows, FP64, b = 8 with two dots 860 -> 586 us, with the KPM step's options
+// 1,171 -> 722, b = 12 1,138 -> 912; 100 K rows, b = 8 144 -> 102. Kernels of which two fit are better
+// off whole (the plain product of 4 M rows, b = 8: 1,064 and 1,195 us): fewer tiles in work at a time
+// keep more of x in L2. (A call that chose its workgroups per compute unit, bpc_hint > 0, keeps kBlock.)
+int block_threads(const void *kernel, int32_t bpc_hint);
 // Columns per lane of the fixed-width product kernels: hint (1, 2 or 4, at most b) when
 // given, else 4 for b >= 4 and b otherwise.
 int choose_vpt(int vk, int b, int hint = 0);

@@ -6,7 +6,8 @@
 //     dots <y,y>_j, <x,y>_j, <x,x>_j of the final y;  z_ij = delta z_ij + eta y_ij.
 //
 // Mapping onto CDNA4 (wave64):
-//   * One workgroup of kBlock threads owns one "tile": a contiguous range of chunks whose
+//   * One workgroup of kBlock threads (half of that in grids of several waves where only one
+//     would fit a compute unit) owns one "tile": a contiguous range of chunks whose
 //     cost (stored entries + row slots) is balanced at build time. Workgroup ids are
 //     remapped so that each of the 8 XCDs (the hardware deals workgroups to XCDs in turn)
 //     works on one contiguous eighth of the tiles; neighbouring rows then share an L2.
@@ -245,7 +246,8 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     const int tid = threadIdx.x;
     const int wrows = GEN ? 64 / VL : 0, wslot = GEN ? (tid & 63) / VL : 0;  // GEN: rows per wave, the lane's
     const int vg = GEN ? (tid & 63) - wslot * VL : tid & (VL - 1);
-    const int rows_per_pass = GEN ? (kBlock / 64) * wrows : kBlock >> vls;
+    const int nthr = STG ? kBlock : a.threads;  // threads of the workgroup
+    const int rows_per_pass = GEN ? (nthr / 64) * wrows : nthr >> vls;
     // row slot of this lane within a pass (GEN: the lanes left over take a row of their wave, unused)
     const int rslot = GEN ? (tid >> 6) * wrows + (wslot < wrows ? wslot : 0) : tid >> vls;
     const int jb = GEN && vg * VPT > nb - VPT ? nb - VPT : vg * VPT;
@@ -594,7 +596,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     if (!want_dots) return;
 
     // ---- dot partials of this tile (deterministic: butterfly in the wave, waves in order)
-    __shared__ double red[kBlock / 64][3 * kMaxSliceCols];
+    __shared__ double red[kBlock / 64][3 * (B > 0 ? B : kMaxSliceCols)];
     const int w = tid >> 6;
 #pragma unroll
     for (int t = 0; t < VPT; ++t) {
@@ -631,10 +633,9 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     // one partial per tile and quantity, plain stores: the sums over tiles are taken by a
     // separate kernel (kernel boundaries order the memory without device-wide fences)
     const int nq = 3 * nb;
-    for (int q = tid; q < nq; q += kBlock) {
+    for (int q = tid; q < nq; q += nthr) {
         double sum = 0.0;
-#pragma unroll
-        for (int ww = 0; ww < kBlock / 64; ++ww) sum += red[ww][q];
+        for (int ww = 0; ww < nthr / 64; ++ww) sum += red[ww][q];
         to_global(a.partials)[size_t(q) * a.nblocks + tile] = sum;
     }
 }
@@ -680,7 +681,7 @@ __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__re
     const int tile = g - blk_start[lo];
     if (active && !active[lo]) {
         if (AUG && (a.flags & SELL_SPMV_DOTS))
-            for (int q = threadIdx.x; q < 3 * a.nb; q += kBlock) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
+            for (int q = threadIdx.x; q < 3 * a.nb; q += blockDim.x) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
         return;
     }
     prod_body<VK, B, VPT, AUG, UB, false, FL>(a, tile, vl);
@@ -708,7 +709,7 @@ __global__ void __launch_bounds__(kBlock) prod_batch_mixed_kernel(const ProdArgs
     const int tile = g - blk_start[lo];
     if (active && !active[lo]) {
         if (AUG && (a.flags & SELL_SPMV_DOTS))
-            for (int q = threadIdx.x; q < 3 * a.nb; q += kBlock) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
+            for (int q = threadIdx.x; q < 3 * a.nb; q += blockDim.x) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
         return;
     }
     switch (a.runtime_width ? 0 : a.nb) {
@@ -799,11 +800,21 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
     int32_t bpc = a.bpc_hint;
     if (bpc == 0 && VPT * int(sizeof(typename KTypes<VK>::X)) >= 32) bpc = 1;
     a.nblocks = resident_grid(reinterpret_cast<const void *>(k), kBlock, a.ntiles, bpc);
+    a.threads = kBlock;
     // several waves: workgroups that finish early take the next ones (uneven tiles)
-    if (a.waves_hint > 1) a.nblocks = int32_t(std::min<int64_t>(int64_t(a.nblocks) * a.waves_hint, a.ntiles));
+    if (a.waves_hint > 1) {
+        a.threads = block_threads(reinterpret_cast<const void *>(k), a.bpc_hint);
+        // but none without a pass of rows of its own, or two where it ends in a reduction: on 100 K
+        // rows of the irregular matrix at b = 12 (FP32 vectors) <x,y> and <y,y> took 99 us with a
+        // tenth of a pass each and 90 with two; the plain product 80 either way
+        const int path = B > 0 ? kPathFixed : B < 0 ? kPathContig : kPathAny;
+        const int64_t rows = pass_rows(a.nb, VPT, path, a.threads), passes = (a.nrows + rows - 1) / rows;
+        const int64_t most = std::max<int64_t>(a.nblocks, AUG && (a.flags & SELL_SPMV_DOTS) ? passes / 2 : passes);
+        a.nblocks = int32_t(std::min<int64_t>(std::min<int64_t>(int64_t(a.nblocks) * a.waves_hint, a.ntiles), most));
+    }
     // a tile stride needs whole columns of tiles and of workgroups
     a.tile_stride = 0;  // a unit stride applies to staged launches only
-    hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(kBlock), 0, s, a, vl);
+    hipLaunchKernelGGL(k, dim3(a.nblocks), dim3(unsigned(a.threads)), 0, s, a, vl);
     return hipGetLastError() == hipSuccess ? SELL_OK : SELL_ERR_HIP;
 }
 

@@ -31,33 +31,36 @@ int choose_vpt(int vk, int b, int hint) {
     return v;
 }
 
-int32_t resident_grid(const void *kernel, int threads, int32_t ntiles, int32_t blocks_per_cu) {
-    if (ntiles <= 0) return 0;
-    // (workgroups per CU, CUs) of each kernel on each device
-    static thread_local std::map<std::pair<int, const void *>, std::pair<int32_t, int32_t>> cache;
+// (workgroups per CU, CUs) of a kernel on the current device
+static std::pair<int32_t, int32_t> occupancy(const void *kernel, int threads) {
+    static thread_local std::map<std::pair<std::pair<int, int>, const void *>, std::pair<int32_t, int32_t>> cache;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    auto key = std::make_pair(dev, kernel);
-    auto it = cache.find(key);
-    std::pair<int32_t, int32_t> occ;
-    if (it != cache.end()) {
-        occ = it->second;
-    } else {
-        int per_cu = 0, ncu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
-            per_cu = 1;
-        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
-            ncu = 256;
-        if (const char *e = std::getenv("SELLCS_BLOCKS_PER_CU")) {
-            const int v = std::atoi(e);
-            if (v >= 1 && v <= 64) per_cu = v;
-        }
-        occ = std::make_pair(int32_t(per_cu), int32_t(ncu));
-        cache.emplace(key, occ);
+    const auto key = std::make_pair(std::make_pair(dev, threads), kernel);
+    const auto it = cache.find(key);
+    if (it != cache.end()) return it->second;
+    int per_cu = 0, ncu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 256;
+    if (const char *e = std::getenv("SELLCS_BLOCKS_PER_CU")) {
+        const int v = std::atoi(e);
+        if (v >= 1 && v <= 64) per_cu = v;
     }
+    const auto occ = std::make_pair(int32_t(per_cu), int32_t(ncu));
+    cache.emplace(key, occ);
+    return occ;
+}
+
+int32_t resident_grid(const void *kernel, int threads, int32_t ntiles, int32_t blocks_per_cu) {
+    if (ntiles <= 0) return 0;
+    const std::pair<int32_t, int32_t> occ = occupancy(kernel, threads);
     const int32_t per = (blocks_per_cu > 0 && blocks_per_cu < occ.first) ? blocks_per_cu : occ.first;
     const int64_t full = int64_t(per) * occ.second;
     return full < ntiles ? int32_t(full) : ntiles;
+}
+
+int block_threads(const void *kernel, int32_t bpc_hint) {
+    return bpc_hint == 0 && occupancy(kernel, kBlock).first == 1 ? kBlock / 2 : kBlock;
 }
 
 static bool fixed_width(int b) { return b == 1 || b == 2 || b == 4 || b == 8 || b == 16 || b == 32; }

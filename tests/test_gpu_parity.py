@@ -558,3 +558,31 @@ def test_batch_of_any_width_equals_single_products(sc, b, dt):
     B.close()
     for M in Ms:
         M.close()
+
+
+@pytest.mark.parametrize("dt,b", [("f64", 1), ("f64", 4), ("f64", 8), ("f64", 12), ("f64", 32), ("f64", 64), ("bf16", 8), ("f32", 12)])
+@pytest.mark.parametrize("n", [33, 700, 9000])
+def test_grids_of_several_waves_equal_one_wave(sc, dt, b, n):
+    """Products on grids of many workgroups (whole or half size, at least a pass of rows each) against
+    one wave: y and z bit for bit, dots within a fixed-order FP64 sum's error."""
+    import torch
+
+    A = synth.irregular(n, mean_len=8.0, max_len=min(n, 300), band=50, seed=196)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=256, dtype=dt)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    X, Y0, Z0 = (torch.from_numpy(synth.block_vector(n, b, s)).to("cuda:0", vt) for s in (197, 198, 199))
+    outs = []
+    for waves in (1, 0, 2, 16):
+        M.set_waves(waves)
+        Y, Z, P = Y0.clone(), Z0.clone(), torch.empty_like(Y0)
+        dot = torch.zeros(3 * b, dtype=torch.float64, device="cuda:0")
+        sc.sell_spmmv_aug(M, X, Y, Z, flags=sc.SHIFT | sc.SCALE | sc.AXPBY | sc.DOTS | sc.CHAIN, alpha=0.5, beta=-1.0,
+                          gamma=0.3, delta=1.0, eta=0.5, dot=dot)
+        sc.sell_spmmv(M, X, P)
+        outs.append((Y, Z, P, dot))
+    xd, yd = X.double(), outs[0][0].double()
+    mag = torch.cat([(yd * yd).sum(0), (xd * yd).abs().sum(0), (xd * xd).sum(0)])
+    for o in outs[1:]:
+        assert all(torch.equal(u, v) for u, v in zip(o[:3], outs[0][:3]))
+        assert bool(((o[3] - outs[0][3]).abs() <= 2 * (n + 8) * 2.0 ** -53 * mag).all())
+    M.close()
