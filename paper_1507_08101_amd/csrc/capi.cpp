@@ -924,8 +924,8 @@ int sell_kpm(const sell_mat *A, sell_bv *V, sell_bv *W, int64_t M, double scale,
     if (rc == SELL_OK && A->h.nrows > 0 && nblk > 0) {
         rc = launch_dot_finish_strided(parts, nblk, b, SELL_SPMV_DOTS, dots, b, 1, 3 * b, per_step, s);
         if (rc == SELL_OK && M > 1)
-            rc = launch_dot_finish_strided(parts + per_step, nblk1, b, SELL_SPMV_DOTS, dots + 3 * b, b, M - 1, 3 * b,
-                                           per_step, s);
+            rc = launch_dot_finish_strided(parts + per_step, nblk1, b, SELL_SPMV_DOT_YY | SELL_SPMV_DOT_XY, dots + 3 * b,
+                                           b, M - 1, 3 * b, per_step, s);
     } else if (rc == SELL_OK)
         rc = launch_fill(dots, SELL_F64, M, 3 * b, 3 * b, 1, 0.0, s);
     if (rc == SELL_OK) rc = launch_kpm_moments(dots, M, b, mu, s);

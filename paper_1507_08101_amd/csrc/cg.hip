@@ -1,7 +1,7 @@
 // cg.hip -- vector kernels of the conjugate-gradient drivers (block vectors, one CG per
 // column, all scalars kept in FP64 on the device so an iteration needs no host sync).
 //
-// Column sums are deterministic: butterfly shuffles inside a wave, LDS across waves, one
+// Column sums are deterministic: register moves inside a wave, LDS across waves, one
 // partial per workgroup (plain stores), then a one-workgroup-per-column kernel adds the
 // partials in workgroup order and performs the per-column scalar updates.
 #include <algorithm>
@@ -17,11 +17,11 @@ constexpr int kVT = 256;  // threads per workgroup of the vector kernels
 
 // Per-workgroup column sums of one FP64 value per thread (column j = tid & (bpad - 1);
 // lanes with j >= b give 0), written with plain stores to partials[j * gridDim.x + block].
-// Butterfly inside the wave, waves in order: a fixed order.
+// Inside the wave, then the waves in order: a fixed order.
 __device__ void colsum_store(double v, int bpad, int b, double *partials) {
     __shared__ double red[kVT / 64][64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    for (int m = 32; m >= bpad; m >>= 1) v += __shfl_xor(v, m, 64);
+    v = class_sum(v, bpad);
     if (lane < bpad) red[w][lane] = v;
     __syncthreads();
     if (tid < b) {
@@ -82,9 +82,7 @@ __device__ void colsum_store_vec(const double (&acc)[V], double *partials) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        double x = acc[v];
-#pragma unroll
-        for (int m = 32; m >= TPR; m >>= 1) x += __shfl_xor(x, m, 64);
+        const double x = class_sum(acc[v], TPR);
         if (lane < TPR) red[w][lane * V + v] = x;
     }
     __syncthreads();

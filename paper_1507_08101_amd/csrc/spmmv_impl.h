@@ -29,10 +29,9 @@
 //   * Optionally (STG) x is gathered from a cache of x pages in LDS, filled by asynchronous
 //     global-to-LDS copies of the next work unit's pages during the current one, with
 //     16-bit unit-local column indices (stage.hip builds them and the slot plan).
-//   * Dots are reduced without floating-point atomics: butterfly shuffles inside the
-//     wave, LDS across the waves of the workgroup, one partial per tile written with a
-//     plain store; a separate small kernel (or the caller's next kernel) sums the partials
-//     in tile order. The order is fixed, so results are bitwise reproducible. There is no
+//   * Dots are reduced without floating-point atomics: register moves inside the wave, LDS
+//     across the waves of the workgroup, one partial per tile written with a plain store; a
+//     separate small kernel (or the caller's next kernel) sums the partials in tile order. The order is fixed, so results are bitwise reproducible. There is no
 //     "last workgroup" ticket: on a multi-XCD part the device-scope release/acquire it
 //     needs writes back and invalidates the L2 once per workgroup.
 #pragma once
@@ -72,8 +71,6 @@ __device__ __forceinline__ float to_acc(uint16_t v, float) { return __uint_as_fl
 
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __fma_rn(a, b, c); }
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __fmaf_rn(a, b, c); }
-
-__device__ __forceinline__ double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
 
 // Pointers into global memory. Pointers read from memory (the argument tables of the batched
 // kernel) are generic to the compiler, which would access them with flat instructions (that
@@ -595,45 +592,38 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
 
     if (!want_dots) return;
 
-    // ---- dot partials of this tile (deterministic: butterfly in the wave, waves in order)
+    // ---- dot partials of this tile (deterministic: lanes of the wave, then waves in order); dots
+    // that were not asked for are not summed
     __shared__ double red[kBlock / 64][3 * (B > 0 ? B : kMaxSliceCols)];
     const int w = tid >> 6;
-#pragma unroll
-    for (int t = 0; t < VPT; ++t) {
-        if constexpr (GEN) {
-            // rows of the wave folded onto its first: the upper half of the rows left onto the lower
-            for (int left = wrows; left > 1;) {
-                const int half = (left + 1) / 2;
-                const bool add = wslot + half < left;
-                const int from = (lane + half * VL) & 63;
-                const double yy = __shfl(dyy[t], from, 64), xy = __shfl(dxy[t], from, 64), xx = __shfl(dxx[t], from, 64);
-                dyy[t] += add ? yy : 0.0;
-                dxy[t] += add ? xy : 0.0;
-                dxx[t] += add ? xx : 0.0;
-                left = half;
-            }
-        } else {
-            for (int m = 32; m >= VL; m >>= 1) {
-                dyy[t] += shfl_xor_d(dyy[t], m);
-                dxy[t] += shfl_xor_d(dxy[t], m);
-                dxx[t] += shfl_xor_d(dxx[t], m);
-            }
-        }
-    }
-    if (lane < VL && col_ok) {
+    auto wave_sums = [&](double (&d)[VPT], int group) {
+        if (!(fl & (SELL_SPMV_DOT_YY << group))) return;
 #pragma unroll
         for (int t = 0; t < VPT; ++t) {
-            if (GEN && jb + t < vg * VPT) continue;  // the neighbour's column
-            red[w][jb + t] = dyy[t];
-            red[w][nb + jb + t] = dxy[t];
-            red[w][2 * nb + jb + t] = dxx[t];
+            if (GEN && (VL & (VL - 1))) {
+                // rows of the wave folded onto its first: the upper half of the rows left onto the lower
+                for (int left = wrows; left > 1;) {
+                    const int half = (left + 1) / 2;
+                    const double v = __shfl(d[t], (lane + half * VL) & 63, 64);
+                    d[t] += wslot + half < left ? v : 0.0;
+                    left = half;
+                }
+            } else {
+                d[t] = class_sum(d[t], VL);
+            }
+            // (GEN: a column that is the neighbour's is left to it)
+            if (lane < VL && col_ok && !(GEN && jb + t < vg * VPT)) red[w][group * nb + jb + t] = d[t];
         }
-    }
+    };
+    wave_sums(dyy, 0);
+    wave_sums(dxy, 1);
+    wave_sums(dxx, 2);
     __syncthreads();
     // one partial per tile and quantity, plain stores: the sums over tiles are taken by a
     // separate kernel (kernel boundaries order the memory without device-wide fences)
     const int nq = 3 * nb;
     for (int q = tid; q < nq; q += nthr) {
+        if (!(fl & (SELL_SPMV_DOT_YY << (q / nb)))) continue;
         double sum = 0.0;
         for (int ww = 0; ww < nthr / 64; ++ww) sum += red[ww][q];
         to_global(a.partials)[size_t(q) * a.nblocks + tile] = sum;
