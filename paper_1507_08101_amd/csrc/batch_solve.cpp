@@ -2,12 +2,13 @@
 // advanced by the same kernel launches.
 //
 // Every system m (matrix A_m of the batch, right-hand sides B_m, one CG per column) keeps its
-// own FP64 scalars on the device. One iteration over the whole batch is four launches:
+// own FP64 scalars on the device. One iteration over the whole batch is three launches:
 //   Q = A P            batched product with the fused <p, q> and <q, q> per system and column
-//   alpha, beta        one workgroup per system (beta from <r', r'> = alpha^2 <q, q> - rho)
+//   scalars            one workgroup per system: rho and the flags of the iteration before (a
+//                      system whose columns have all converged drops out: the vector pass and the
+//                      next products skip it), alpha, beta (from <r', r'> = alpha^2 <q, q> - rho)
 //   R -= a Q, D += a P, P = R + b P   one segmented vector pass with the partials of <r, r>
-//   rho, flags         one workgroup per system (a system whose columns have all converged
-//                      drops out: the product and vector kernels skip it)
+// and a last launch of the scalars ends a run of iterations.
 // Runs of kCheckEvery iterations are captured in a HIP graph and replayed (or launched
 // directly); the host looks at the scalars between runs. The launches of an iteration are
 // spread over the systems that still iterate only: whenever that set changes, the resident
@@ -180,10 +181,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         (rc = DB.alloc(&pd, nv * isz)) || (rc = DB.alloc(&pp, nv * isz)) || (rc = DB.alloc(&pq, nv * isz)))
         return rc;
     // device scalars: rho alpha beta thresh2 bb rr(3Kb) | vec partials (b G) | int32 flags
-    // vector-kernel workgroups of an iteration (4,096 and 8,192 ran 1-2 % faster than 2,048 and
-    // 1,024 with 8 rows in flight per thread)
-    const int32_t Gv = 4 * kCgMaxGrid;
-    const size_t gmax = size_t(std::max(std::max(sg.G, Gv), K));
+    const size_t gmax = size_t(std::max(std::max(sg.G, 4 * kCgMaxGrid), K));
     const size_t nd = 5 * Kb + 3 * Kb + size_t(b) * gmax;
     // active, sys_active, mask | iters (int64) | column mask | iteration and update workgroup offsets
     const size_t ni = Kb + 2 * size_t(K) + 2 * size_t(K) + 2 + Kb + 2 * (size_t(K) + 1);
@@ -227,6 +225,17 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
 
     std::vector<double> wrows(static_cast<size_t>(K));
     for (int m = 0; m < K; ++m) wrows[size_t(m)] = double(batch_matrix(A64, m)->h.nrows);
+    // Vector-kernel workgroups of the flagged systems, split by their rows.
+    auto split_rows = [&](const std::vector<int32_t> &flag, std::vector<int32_t> &blk) {
+        std::vector<int64_t> cap(static_cast<size_t>(K));
+        int64_t rows = 0;
+        for (int m = 0; m < K; ++m) {
+            const int64_t nr = flag[size_t(m)] ? batch_matrix(A64, m)->h.nrows : 0;
+            cap[size_t(m)] = nr > 0 ? std::max<int64_t>(1, (nr + 3) / 4) : 0;
+            rows += nr;
+        }
+        apportion(wrows, cap, bcg_vector_grid(idt, rows, b), blk);
+    };
     // The workgroups of the update's vector kernels, split over the systems it updates (with the
     // batch's own split, an update of a few systems ran on their small share of the grid).
     std::vector<int32_t> vblkr;
@@ -239,12 +248,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         int r;
         HIPCHK(hipMemcpyAsync(mask_d, mask.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, s));
         {
-            std::vector<int64_t> cap(static_cast<size_t>(K));
-            for (int m = 0; m < K; ++m) {
-                const int64_t nr = batch_matrix(A64, m)->h.nrows;
-                cap[size_t(m)] = (mask[size_t(m)] && nr > 0) ? std::max<int64_t>(1, (nr + 3) / 4) : 0;
-            }
-            apportion(wrows, cap, Gv, vblkr);
+            split_rows(mask, vblkr);
             sgr.G = vblkr[size_t(K)];
             // vblkr is not touched again before the synchronisation below
             HIPCHK(hipMemcpyAsync(vblkr_d, vblkr.data(), (size_t(K) + 1) * sizeof(int32_t), hipMemcpyHostToDevice,
@@ -327,12 +331,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         *changed = appo_active != sysact;
         if (!*changed) return SELL_OK;
         appo_active = sysact;
-        std::vector<int64_t> cap(static_cast<size_t>(K));
-        for (int m = 0; m < K; ++m) {
-            const int64_t nr = batch_matrix(A64, m)->h.nrows;
-            cap[size_t(m)] = (sysact[size_t(m)] && nr > 0) ? std::max<int64_t>(1, (nr + 3) / 4) : 0;
-        }
-        apportion(wrows, cap, Gv, vblk);
+        split_rows(sysact, vblk);
         sgi.G = vblk[size_t(K)];
         HIPCHK(hipMemcpyAsync(vblk_d, vblk.data(), (size_t(K) + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
         HIPCHK(hipStreamSynchronize(s));  // vblk is reused by the next split
@@ -341,6 +340,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
 
     sell_spmv_opts po = SELL_SPMV_OPTS_INIT;
     po.flags = SELL_SPMV_DOT_XY | SELL_SPMV_DOT_YY;
+    bool pending = false;  // the last vector pass's <r, r> are still to be summed
     auto iteration = [&]() -> int {
         int r;
         const int32_t *pblk = nullptr;
@@ -348,9 +348,17 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         if ((r = batch_aug_impl(Ain, &P, &Q, nullptr, po, true, sc.sys_active, appo_active.data(), false, s, &pblk,
                                 &pparts, true)))
             return r;
-        if ((r = bcg_launch_step(pparts, pblk, K, b, sc, s))) return r;
-        if (sgi.G == 0) return SELL_OK;
-        return bcg_launch_rp(idt, pr, pq, pp, pd, b, sgi, sc, vparts, s);
+        if ((r = bcg_launch_step(pparts, pblk, pending ? vparts : nullptr, sgi, b, sc, s))) return r;
+        pending = sgi.G > 0;
+        return pending ? bcg_launch_rp(idt, pr, pq, pp, pd, b, sgi, sc, vparts, s) : SELL_OK;
+    };
+    // `count` iterations and the scalars of the last one
+    auto run_iterations = [&](int64_t count) -> int {
+        int r = SELL_OK;
+        pending = false;
+        for (int64_t k = 0; k < count && r == SELL_OK; ++k) r = iteration();
+        if (r == SELL_OK && pending) r = bcg_launch_step(nullptr, nullptr, vparts, sgi, b, sc, s);
+        return r;
     };
 
     Graph graph;
@@ -379,8 +387,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         if (use_graph && run == kCheckEvery && stable >= 2) {
             if (!graph.ge) {
                 HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-                int r = SELL_OK;
-                for (int k = 0; k < run && r == SELL_OK; ++k) r = iteration();
+                const int r = run_iterations(run);
                 hipGraph_t g = nullptr;
                 const hipError_t e = hipStreamEndCapture(s, &g);
                 graph.g = g;
@@ -390,8 +397,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
             }
             HIPCHK(hipGraphLaunch(graph.ge, s));
         } else {
-            for (int64_t k = 0; k < run; ++k)
-                if ((rc = iteration())) return rc;
+            if ((rc = run_iterations(run))) return rc;
         }
         ++stable;
         it += run;

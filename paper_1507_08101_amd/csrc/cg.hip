@@ -112,13 +112,23 @@ __device__ double sum_partials(const double *p, int n) {
 // numerator that cancels to zero or below restarts the column from p = r' (beta = 0). After a
 // reliable update keeps p but replaces r by the true residual, <r, q> = <p, q> holds only up to
 // the drift that the update removed, and that iteration's beta carries the same small error.
-__global__ void __launch_bounds__(kVT) cg_step_kernel(const double *prod_partials, int ntiles, int b, CgDev sc) {
+//
+// rp_parts: null, or the previous vector pass's G partials of <r, r> per column, which are summed
+// here first (rho and the column's flag, as cg_rho_kernel does): one launch less per iteration.
+__global__ void __launch_bounds__(kVT) cg_step_kernel(const double *prod_partials, int ntiles, int b,
+                                                      const double *rp_parts, int G, CgDev sc) {
     const int j = blockIdx.x;
+    const double rn = rp_parts ? sum_partials(rp_parts + size_t(j) * G, G) : 0.0;
     const double qq = sum_partials(prod_partials + size_t(j) * ntiles, ntiles);
     const double pq = sum_partials(prod_partials + size_t(b + j) * ntiles, ntiles);
     if (threadIdx.x == 0) {
-        const double rho = sc.rho[j];
-        const bool act = sc.active[j] != 0;
+        bool act = sc.active[j] != 0;
+        if (rp_parts) {
+            act = act && rn > sc.thresh2[j];
+            sc.rho[j] = rn;
+            sc.active[j] = act ? 1 : 0;
+        }
+        const double rho = rp_parts ? rn : sc.rho[j];
         const double al = (act && pq != 0.0) ? rho / pq : 0.0;
         const double num = al * al * qq - rho;
         sc.pq[j] = pq;
@@ -301,26 +311,63 @@ __device__ __forceinline__ void seg_rows(const BatchSeg &sg, int m, int bpad, F 
         f(i);
 }
 
-// alpha[m, j] and beta[m, j] of every system that iterates, as cg_step_kernel computes them, from
-// the batched product's partials of matrix m (quantity t at pparts + 3 b pblk[m] + t npm,
-// npm = pblk[m+1] - pblk[m]; <q, q> is quantity j, <p, q> quantity b + j). One workgroup per
-// system and column (grid K x b).
-__global__ void __launch_bounds__(kVT) bcg_step_kernel(const double *pparts, const int32_t *pblk, int b,
-                                                       BatchCg sc) {
-    const int m = blockIdx.x, j = blockIdx.y;
+// The scalars of every system that iterates, one workgroup per system and a wave per column:
+//   vparts: null, or the previous vector pass's partials of <r, r> (those of system m, column j at
+//   j G + vblk[m]): rho, the column flags (active &= rho > thresh2), the system's flag (set while
+//   one of its columns is active) and its iteration counter, as of that pass;
+//   pparts: null, or the batched product's partials of matrix m (quantity t at pparts + 3 b pblk[m] +
+//   t npm, npm = pblk[m+1] - pblk[m]; <q, q> is quantity j, <p, q> quantity b + j): alpha and beta, as
+//   cg_step_kernel computes them. Both in one launch inside a run of iterations (a system that
+//   retires in it has had one product more, and its vector pass is skipped).
+// 16 Laplacians, b = 4: 5.1 us per iteration against 13.7 for a launch each, with the columns one
+// after another in the first.
+constexpr int kST = 1024;
+
+__device__ double wave_sum(const double *p, int n) {
+    double s = 0.0;
+    for (int t = threadIdx.x & 63; t < n; t += 64) s += p[t];
+    return class_sum(s, 1);
+}
+
+__global__ void __launch_bounds__(kST) bcg_step_kernel(const double *pparts, const int32_t *pblk, const double *vparts,
+                                                       int G, const int32_t *vblk, int b, BatchCg sc) {
+    __shared__ int any;
+    const int m = blockIdx.x;
     if (!sc.sys_active[m]) return;
-    const int npm = pblk[m + 1] - pblk[m];
-    const double *base = pparts + size_t(3) * b * pblk[m];
-    const double qq = sum_partials(base + size_t(j) * npm, npm);
-    const double pq = sum_partials(base + size_t(b + j) * npm, npm);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0) any = 0;
+    __syncthreads();
+    const bool first = (threadIdx.x & 63) == 0;
+    for (int j = threadIdx.x >> 6; j < b; j += kST / 64) {
         const int q = m * b + j;
-        const double rho = sc.rho[q];
-        const bool act = sc.active[q] != 0;
-        const double al = (act && pq != 0.0) ? rho / pq : 0.0;
-        const double num = al * al * qq - rho;
-        sc.alpha[q] = al;
-        sc.beta[q] = (act && rho != 0.0 && num > 0.0) ? num / rho : 0.0;
+        double rn = 0.0, qq = 0.0, pq = 0.0;
+        if (vparts) rn = wave_sum(vparts + size_t(j) * G + vblk[m], vblk[m + 1] - vblk[m]);
+        if (pparts) {
+            const int npm = pblk[m + 1] - pblk[m];
+            const double *base = pparts + size_t(3) * b * pblk[m];
+            qq = wave_sum(base + size_t(j) * npm, npm);
+            pq = wave_sum(base + size_t(b + j) * npm, npm);
+        }
+        if (!first) continue;
+        bool act = sc.active[q] != 0;
+        if (vparts) {
+            act = act && rn > sc.thresh2[q];
+            sc.rho[q] = rn;
+            sc.active[q] = act ? 1 : 0;
+            if (act) any = 1;
+        }
+        if (pparts) {
+            const double rho = vparts ? rn : sc.rho[q];
+            const double al = (act && pq != 0.0) ? rho / pq : 0.0;
+            const double num = al * al * qq - rho;
+            sc.alpha[q] = al;
+            sc.beta[q] = (act && rho != 0.0 && num > 0.0) ? num / rho : 0.0;
+        }
+    }
+    if (!vparts) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sc.sys_active[m] = any;
+        sc.iters[m] += 1;
     }
 }
 
@@ -345,30 +392,6 @@ __global__ void __launch_bounds__(kVT) bcg_rp_kernel(T *R, const T *Q, T *P, T *
         });
     }
     colsum_store(acc, bpad, b, partials);
-}
-
-// rho = <r, r> from the vector pass's partials; active &= rho > thresh2; the system stays
-// active while one of its columns is; its iteration counter advances.
-__global__ void __launch_bounds__(kVT) bcg_rho_kernel(const double *partials, int G, BatchSeg sg, int b,
-                                                      BatchCg sc) {
-    const int m = blockIdx.x;
-    if (!sc.sys_active[m]) return;
-    const int v0 = sg.vblk[m], nv = sg.vblk[m + 1] - v0;
-    int any = 0;
-    for (int j = 0; j < b; ++j) {
-        const double rn = sum_partials(partials + size_t(j) * G + v0, nv);
-        if (threadIdx.x == 0) {
-            const int q = m * b + j;
-            const int still = (sc.active[q] && rn > sc.thresh2[q]) ? 1 : 0;
-            sc.rho[q] = rn;
-            sc.active[q] = still;
-            any |= still;
-        }
-    }
-    if (threadIdx.x == 0) {
-        sc.sys_active[m] = any;
-        sc.iters[m] += 1;
-    }
 }
 
 // bcg_rp_kernel on 16-byte column groups (b = TPR * V, rows contiguous)
@@ -634,8 +657,16 @@ static int ok() { return hipGetLastError() == hipSuccess ? SELL_OK : SELL_ERR_HI
 
 unsigned cg_reduce_grid(int64_t n, int b) { return vgrid(n * pow2_at_least(b), kCgMaxGrid); }
 
-int cg_launch_step(const double *prod_partials, int ntiles, int b, const CgDev &sc, hipStream_t s) {
-    hipLaunchKernelGGL(cg_step_kernel, dim3(b), dim3(kVT), 0, s, prod_partials, ntiles, b, sc);
+int cg_launch_step(const double *prod_partials, int ntiles, int b, const double *rp_parts, int G, const CgDev &sc,
+                   hipStream_t s) {
+    hipLaunchKernelGGL(cg_step_kernel, dim3(b), dim3(kVT), 0, s, prod_partials, ntiles, b, G > 0 ? rp_parts : nullptr, G,
+                       sc);
+    return ok();
+}
+
+int cg_launch_rho(const double *rp_parts, int G, int b, const CgDev &sc, hipStream_t s) {
+    if (G <= 0) return SELL_OK;
+    hipLaunchKernelGGL(cg_rho_kernel, dim3(b), dim3(kVT), 0, s, rp_parts, G, sc);
     return ok();
 }
 
@@ -715,14 +746,13 @@ static void launch_rp(void *R, const void *Q, void *P, void *X, int64_t n, int b
 }
 
 int cg_launch_rp(int dt, void *R, const void *Q, void *P, void *X, int64_t n, int b, int64_t ld, const CgDev &sc,
-                 double *partials, hipStream_t s) {
+                 double *partials, int *G, hipStream_t s) {
     unsigned g = 0;
     if (dt == SELL_F64)
         launch_rp<double>(R, Q, P, X, n, b, ld, sc, partials, &g, s);
     else
         launch_rp<float>(R, Q, P, X, n, b, ld, sc, partials, &g, s);
-    if (ok() != SELL_OK) return SELL_ERR_HIP;
-    hipLaunchKernelGGL(cg_rho_kernel, dim3(b), dim3(kVT), 0, s, partials, int(g), sc);
+    *G = int(g);
     return ok();
 }
 
@@ -768,9 +798,23 @@ template <class T>
 const T *ctp(const void *p) { return static_cast<const T *>(p); }
 }  // namespace
 
-int bcg_launch_step(const double *pparts, const int32_t *pblk, int K, int b, const BatchCg &sc, hipStream_t s) {
-    hipLaunchKernelGGL(bcg_step_kernel, dim3(K, b), dim3(kVT), 0, s, pparts, pblk, b, sc);
+int bcg_launch_step(const double *pparts, const int32_t *pblk, const double *vparts, const BatchSeg &sg, int b,
+                    const BatchCg &sc, hipStream_t s) {
+    hipLaunchKernelGGL(bcg_step_kernel, dim3(sg.K), dim3(kST), 0, s, pparts, pblk, vparts, sg.G, sg.vblk, b, sc);
     return ok();
+}
+
+// Workgroups of a batched vector pass over `rows` rows: about 16 rows per thread, at least one
+// workgroup per compute unit where there are rows for it, at most 4,096. 16 Laplacians of edges
+// 20..48, b = 4 (650 K rows): batched CG 16.6 ms with 512 workgroups, 21.1 with 4,096, whose
+// partials and idle threads cost more than they read; 48 of edges 30..90, BF16 values, b = 8 (12 M
+// rows): 308 ms with 512, 297 with 4,096.
+int32_t bcg_vector_grid(int dt, int64_t rows, int b) {
+    const int v = dt == SELL_F64 ? Vec16<double>::V : Vec16<float>::V;
+    const int tpr = b % v == 0 && ((b / v) & (b / v - 1)) == 0 ? b / v : pow2_at_least(b);
+    const int64_t full = (rows * tpr + kVT - 1) / kVT;
+    const int64_t g = std::max<int64_t>(std::min<int64_t>(full, 256), full / 16);
+    return int32_t(std::max<int64_t>(1, std::min<int64_t>(g, 4 * kCgMaxGrid)));
 }
 
 template <class T>
@@ -799,8 +843,6 @@ int bcg_launch_rp(int dt, void *R, const void *Q, void *P, void *D, int b, const
         blaunch_rp<double>(R, Q, P, D, b, sg, sc, partials, s);
     else
         blaunch_rp<float>(R, Q, P, D, b, sg, sc, partials, s);
-    if (ok() != SELL_OK) return SELL_ERR_HIP;
-    hipLaunchKernelGGL(bcg_rho_kernel, dim3(sg.K), dim3(kVT), 0, s, partials, sg.G, sg, b, sc);
     return ok();
 }
 

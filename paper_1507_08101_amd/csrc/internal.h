@@ -252,12 +252,16 @@ struct CgDev {
     int32_t *active;  // per column: 1 while not converged
 };
 unsigned cg_reduce_grid(int64_t n, int b);
-// alpha and beta per column from the product's partials of <q, q> and <p, q> (q = A p)
-int cg_launch_step(const double *prod_partials, int ntiles, int b, const CgDev &sc, hipStream_t s);
-// r -= alpha q, x += alpha p, p = r + beta p in one pass with the partials of <r, r>, then rho
-// and the column flags
+// alpha and beta per column from the product's partials of <q, q> and <p, q> (q = A p); G > 0: the
+// previous vector pass's rp_parts are summed into rho and the column flags first
+int cg_launch_step(const double *prod_partials, int ntiles, int b, const double *rp_parts, int G, const CgDev &sc,
+                   hipStream_t s);
+// r -= alpha q, x += alpha p, p = r + beta p in one pass with the partials of <r, r> (*G per column),
+// which the next step or cg_launch_rho sums
 int cg_launch_rp(int dt, void *R, const void *Q, void *P, void *X, int64_t n, int b, int64_t ld, const CgDev &sc,
-                 double *partials, hipStream_t s);
+                 double *partials, int *G, hipStream_t s);
+// rho and the column flags from a vector pass's partials (nothing when G <= 0)
+int cg_launch_rho(const double *rp_parts, int G, int b, const CgDev &sc, hipStream_t s);
 int cg_launch_coldot(int dt, const void *U, const void *V, int64_t n, int b, int64_t ld, double *result,
                      double *partials, double *thresh2, int32_t *active, const double *ref, double f2,
                      hipStream_t s);
@@ -279,10 +283,14 @@ struct BatchCg {
     int32_t *sys_active;                   // K system flags (some column active)
     int64_t *iters;                        // K iteration counters
 };
-// alpha and beta of the iterating systems from the batched product's partials
-int bcg_launch_step(const double *pparts, const int32_t *pblk, int K, int b, const BatchCg &sc, hipStream_t s);
+// the iterating systems' scalars: rho, flags and counters from the previous vector pass's partials
+// (vparts, may be null), alpha and beta from the batched product's (pparts, may be null)
+int bcg_launch_step(const double *pparts, const int32_t *pblk, const double *vparts, const BatchSeg &sg, int b,
+                    const BatchCg &sc, hipStream_t s);
+// workgroups of a batched vector pass over this many rows
+int32_t bcg_vector_grid(int dt, int64_t rows, int b);
 // r -= alpha q, d += alpha p, p = r + beta p on the iterating systems' rows in one pass with
-// the partials of <r, r>, then rho, the flags and the iteration counters
+// the partials of <r, r>, which the next step sums
 int bcg_launch_rp(int dt, void *R, const void *Q, void *P, void *D, int b, const BatchSeg &sg, const BatchCg &sc,
                   double *partials, hipStream_t s);
 int bcg_launch_coldot(int dt, const void *U, const void *V, int b, const BatchSeg &sg, const int32_t *mask,

@@ -6,7 +6,8 @@
 //   q = A p            augmented product with the fused dots <p, q> and <q, q>
 //   alpha, beta        per-column scalars (device FP64); beta from <r', r'> = alpha^2 <q, q> - rho,
 //                      which holds because q is A-orthogonal to the previous direction
-//   r -= a q, x += a p, p = r + b p   the whole vector update in one pass, with <r, r>
+//   r -= a q, x += a p, p = r + b p   the whole vector update in one pass, with <r, r>, whose
+//                      partials the next iteration's scalar kernel sums
 // The host reads the per-column "active" flags every few iterations.
 //
 // sell_cg:        FP64 throughout; convergence is confirmed on the true residual b - A x.
@@ -118,14 +119,18 @@ int cg_iterate(const sell_mat *A, int dt, sell_bv &X, sell_bv &R, sell_bv &P, se
     o.flags = SELL_SPMV_DOT_XY | SELL_SPMV_DOT_YY;
     *its = 0;
     bool any = true;
+    int G = 0;  // partials per column that the last vector pass left to sum
     if ((rc = any_active(S, b, s, &any))) return rc;
     while (any && *its < maxit) {
         int32_t nblk = 0;
         if ((rc = aug_impl(A, &P, &Q, nullptr, o, true, s, S.prod_parts, &nblk))) return rc;
-        if ((rc = cg_launch_step(S.prod_parts, nblk, b, S.dev(), s))) return rc;
-        if ((rc = cg_launch_rp(dt, R.ptr, Q.ptr, P.ptr, X.ptr, n, b, b, S.dev(), S.vec_parts, s))) return rc;
+        if ((rc = cg_launch_step(S.prod_parts, nblk, b, S.vec_parts, G, S.dev(), s))) return rc;
+        if ((rc = cg_launch_rp(dt, R.ptr, Q.ptr, P.ptr, X.ptr, n, b, b, S.dev(), S.vec_parts, &G, s))) return rc;
         ++*its;
-        if (*its % kCheckEvery == 0 && (rc = any_active(S, b, s, &any))) return rc;
+        if (*its % kCheckEvery == 0) {
+            if ((rc = cg_launch_rho(S.vec_parts, G, b, S.dev(), s)) || (rc = any_active(S, b, s, &any))) return rc;
+            G = 0;
+        }
     }
     return SELL_OK;
 }
@@ -312,14 +317,17 @@ int sell_cg_mixed(const sell_mat *A64, const sell_mat *Alo, const sell_bv *Bv, s
     sell_spmv_opts o = SELL_SPMV_OPTS_INIT;
     o.flags = SELL_SPMV_DOT_XY | SELL_SPMV_DOT_YY;
     int64_t since = 0;
+    int G = 0;  // partials per column that the last vector pass left to sum
     while (!done && st.iterations < maxit) {
         int32_t nblk = 0;
         if ((rc = aug_impl(Alo, &P, &Q, nullptr, o, true, s, S.prod_parts, &nblk))) return rc;
-        if ((rc = cg_launch_step(S.prod_parts, nblk, b, S.dev(), s))) return rc;
-        if ((rc = cg_launch_rp(SELL_F32, R.ptr, Q.ptr, P.ptr, D.ptr, n, b, b, S.dev(), S.vec_parts, s))) return rc;
+        if ((rc = cg_launch_step(S.prod_parts, nblk, b, S.vec_parts, G, S.dev(), s))) return rc;
+        if ((rc = cg_launch_rp(SELL_F32, R.ptr, Q.ptr, P.ptr, D.ptr, n, b, b, S.dev(), S.vec_parts, &G, s))) return rc;
         ++st.iterations;
         ++since;
         if (st.iterations % kCheckEvery == 0 || st.iterations == maxit) {
+            if ((rc = cg_launch_rho(S.vec_parts, G, b, S.dev(), s))) return rc;
+            G = 0;
             HIPCHK(hipMemcpyAsync(rho, S.rho, sizeof(double) * b, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             bool update = st.iterations == maxit || since >= inner_maxit;

@@ -502,3 +502,28 @@ def test_batch_index_batch_lengths_bit_identical(sc, dt):
         Bt.close()
         for M in Ms:
             M.close()
+
+
+@pytest.mark.parametrize("mode,b", [("f64", 33), ("f64", 64), ("bf16", 17), ("f32", 64)])
+def test_batch_cg_more_columns_than_waves(sc, mode, b):
+    """Systems that retire at different iterations, with more columns than the scalar kernel's waves:
+    every system meets the tolerance in the oracle's FP64 residual, with its own iteration count."""
+    import torch
+
+    mats = [synth.laplacian3d(3), synth.laplacian3d(9), synth.laplacian2d(6)]
+    A64 = sc.SellBatch([sc.SellMatrix.from_csr(A, C=32, sigma=1) for A in mats])
+    lo = None if mode == "f64" else sc.SellBatch([sc.SellMatrix.from_csr(A, C=32, sigma=1, dtype=mode) for A in mats])
+    Bm = [synth.block_vector(A.nrows, b, 200 + k) for k, A in enumerate(mats)]
+    Bd = torch.from_numpy(np.concatenate(Bm)).cuda()
+    X = torch.zeros_like(Bd)
+    st = sc.sell_batch_cg(A64, lo, Bd, X, tol=1e-10)
+    at = 0
+    for A, B, e in zip(mats, Bm, st):
+        assert e["converged"] and e["relres"] <= 1e-10
+        assert _oracle_relres(A, B, host(X[at:at + A.nrows])).max() <= 1.01e-10
+        at += A.nrows
+    if mode == "f64":
+        assert st[0]["iterations"] < st[1]["iterations"]
+    for Bt in (A64, lo):
+        if Bt is not None:
+            Bt.close()
