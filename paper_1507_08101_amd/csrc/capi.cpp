@@ -565,6 +565,10 @@ namespace sellcs {
 int ensure_update_maps(sell_mat *A, hipStream_t s) {
     if (A->d_rowptr) return SELL_OK;
     const HostSell &h = A->h;
+    // on the device; on the host where that is not possible (size, or device memory for its scratch)
+    int rd = device_row_maps(A, &A->d_rowptr, &A->d_rowslot, s);
+    if (rd != SELL_ERR_UNSUPPORTED && rd != SELL_ERR_OOM) return rd;
+    (void)hipGetLastError();
     std::vector<int32_t> rowslot(static_cast<size_t>(h.nrows));
     for (int64_t slot = 0; slot < h.nch * h.C; ++slot) {
         const int64_t row = h.has_perm ? h.perm[slot] : (slot < h.nrows ? slot : -1);
@@ -762,6 +766,13 @@ int check_aug_call(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, 
 int ensure_transpose(const sell_mat *A, hipStream_t s) {
     if (A->transpose) return SELL_OK;
     const HostSell &h = A->h;
+    if (A->on_device) {
+        sell_mat *M = const_cast<sell_mat *>(A);
+        int rd = ensure_update_maps(M, s);
+        if (rd == SELL_OK) rd = device_transpose(A, &M->transpose, &M->d_tpos, s);
+        if (rd != SELL_ERR_UNSUPPORTED && rd != SELL_ERR_OOM) return rd;
+        (void)hipGetLastError();  // too large, or no device memory for the scratch: on the host
+    }
     std::vector<int64_t> rp(size_t(h.nrows) + 1);
     std::vector<int32_t> col(static_cast<size_t>(h.nnz));
     std::vector<double> val(static_cast<size_t>(h.nnz));

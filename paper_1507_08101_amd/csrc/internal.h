@@ -90,6 +90,13 @@ namespace sellcs {
 int build_device_sell(sell_mat *M, int64_t nrows, int64_t ncols, const int64_t *rowptr, const int32_t *col,
                       const double *val, int32_t C, int64_t sigma, int vdt, hipStream_t s);
 
+// On the device, from the matrix's device arrays (devbuild.hip): the update maps (CSR row pointers
+// and row -> slot); the SELL copy of A^T with the position in it of each CSR entry (needs the maps).
+// Synchronous; on error nothing is left allocated. SELL_ERR_UNSUPPORTED: too large for the 32-bit
+// counts of the device steps (or empty).
+int device_row_maps(const sell_mat *A, int64_t **rowptr, int32_t **rowslot, hipStream_t s);
+int device_transpose(const sell_mat *A, sell_mat **T, int64_t **tpos, hipStream_t s);
+
 // Value conversion (round to nearest, ties to even, from the double).
 uint16_t f64_to_bf16_bits(double v);
 float bf16_bits_to_f32(uint16_t b);

@@ -129,3 +129,53 @@ def test_device_build_full_size_anderson128(sc):
             assert np.array_equal(eh[k], ed[k]), (sigma, k)
         Mh.close()
         Md.close()
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("shape,C,sigma", [("wide", 32, 1), ("tall", 12, 40), ("square", 32, 128)])
+def test_device_transpose_equals_host_transpose(sc, shape, C, sigma, dt):
+    """The update maps and the copy of A^T made on the device against the host's (which a failed
+    device allocation falls back to, whichever of them fails): transposed products before and after
+    a value update, and value gradients, bit for bit; empty rows and columns, duplicates, one long row
+    and one long column."""
+    import torch
+
+    nr, nc = {"wide": (90, 401), "tall": (530, 77), "square": (300, 300)}[shape]
+    A = synth.random_sparse(nr, nc, 0.03, 210, duplicates=True, empty_rows=7, long_row=60)
+    col = A.col.copy()
+    col[:: 5] = 3  # a long column; the columns it leaves empty stay so
+    A = synth.CSR(nr, nc, A.rowptr, col, A.val)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    b = 3
+    X = torch.from_numpy(synth.block_vector(nr, b, 211)).to("cuda:0", vt)
+    G = torch.from_numpy(synth.block_vector(nc, b, 212)).to("cuda:0", vt)
+    newv = torch.from_numpy(synth.uniform(213, A.nnz, -2, 2)).cuda()
+
+    def once(fail_at):
+        M = sc.SellMatrix.from_csr(A, C=C, sigma=sigma, dtype=dt)
+        outs = [torch.empty((nc, b), dtype=vt, device="cuda:0") for _ in range(2)]
+        dval = torch.empty(A.nnz, dtype=torch.float64, device="cuda:0")
+        sc.sell_debug_fail_alloc(fail_at)
+        try:
+            sc.sell_spmmv_T(M, X, outs[0])
+        finally:
+            sc.sell_debug_fail_alloc(0)
+        M.update_values(newv)
+        sc.sell_spmmv_T(M, X, outs[1])
+        sc.sell_grad_values(M, X, G, dval)
+        torch.cuda.synchronize()
+        rp, c, v = M.export_csr()
+        assert np.array_equal(rp, A.rowptr) and np.array_equal(c, A.col)
+        M.close()
+        return outs + [dval, torch.from_numpy(v)]
+
+    want = once(0)
+    ref = oracle.spmmv_T(A, X.double().cpu().numpy())
+    scale = oracle.spmmv_T(synth.CSR(nr, nc, A.rowptr, A.col, np.abs(A.val)), np.abs(X.double().cpu().numpy()))
+    tol = {"f64": 2.0 ** -46, "f32": 2.0 ** -17, "bf16": 2.0 ** -7}[dt]
+    assert (np.abs(want[0].double().cpu().numpy() - ref) <= tol * scale + 1e-300).all()
+    live = sc.sell_debug_live_allocs()
+    for k in range(1, 30):
+        got = once(k)
+        assert all(torch.equal(u, v) for u, v in zip(got, want)), k
+        assert sc.sell_debug_live_allocs() == live, k
