@@ -25,9 +25,9 @@
 using namespace sellcs;
 
 namespace sellcs {
-const void *batch_kernel_f64(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
-const void *batch_kernel_f32(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
-const void *batch_kernel_bf16(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags);
+const void *batch_kernel_f64(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags, bool keep);
+const void *batch_kernel_f32(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags, bool keep);
+const void *batch_kernel_bf16(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags, bool keep);
 const void *batch_mixed_kernel_f64(bool aug);
 const void *batch_mixed_kernel_f32(bool aug);
 const void *batch_mixed_kernel_bf16(bool aug);
@@ -301,9 +301,17 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
     const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     const int ub = B->batch_len, ubw = B->batch_len_wide;
     const uint32_t kflags = aug ? o.flags : 0u;  // every matrix of the launch has these flags
-    const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, path, ub, ubw, kflags)
-                       : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, path, ub, ubw, kflags)
-                                         : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags);
+    double mbytes = 0, vbytes = 0;  // of the launched matrices
+    for (int m = 0; m < K; ++m)
+        if (!host_active || host_active[m]) {
+            const HostSell &h = B->mats[size_t(m)]->h;
+            mbytes += double(h.stored) * (4 + dtype_bytes(h.vdt));
+            vbytes += double(h.ncols + h.nrows) * b * esize;
+        }
+    const int32_t keep = keep_in_cache(mbytes, vbytes);
+    const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, path, ub, ubw, kflags, keep != 0)
+                       : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, path, ub, ubw, kflags, keep != 0)
+                                         : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags, keep != 0);
     // workgroups per matrix: waves of the resident grid split so that the busiest workgroup
     // has as little work as possible
     const BatchShape shape = product_shape(B, kern, [&](int threads) {
@@ -345,6 +353,7 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
         const sell_mat *A = B->mats[size_t(m)];
         ProdArgs a;
         base_args(a, A);
+        a.keep = keep;
         a.nb = b;
         a.nblocks = blk[size_t(m) + 1] - blk[size_t(m)];
         a.threads = shape.threads;

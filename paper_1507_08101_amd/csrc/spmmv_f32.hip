@@ -9,9 +9,9 @@ int prod_f32(ProdArgs &a, bool aug, int path, hipStream_t s) {
 
 int transpose_f32(ProdArgs &a, hipStream_t s) { return dispatch_transpose<VK_F32F32>(a, s); }
 
-const void *batch_kernel_f32(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags) {
-    return aug ? batch_kernel_for<VK_F32F32, true>(b, vpt, path, ub, ubw, flags)
-               : batch_kernel_for<VK_F32F32, false>(b, vpt, path, ub, ubw, 0);
+const void *batch_kernel_f32(int b, int vpt, bool aug, int path, int ub, int ubw, uint32_t flags, bool keep) {
+    return aug ? batch_kernel_for<VK_F32F32, true>(b, vpt, path, ub, ubw, flags, keep)
+               : batch_kernel_for<VK_F32F32, false>(b, vpt, path, ub, ubw, 0, keep);
 }
 
 const void *batch_mixed_kernel_f32(bool aug) {

@@ -128,11 +128,12 @@ __device__ __forceinline__ void load_row(const SELL_GLOBAL X *p, int64_t cs, X (
     }
 }
 
-// Row stores are nontemporal: the product never reads its outputs again in the same launch. Not so
+// Row stores are nontemporal (NT): the product never reads its outputs again in the same launch. Not so
+// where the caller's next kernel finds them in the caches (ProdArgs::keep), and never
 // for kContig, whose pieces fill lines less well (96^3 Anderson matrix, FP64: b = 7 45.7 us
 // nontemporal, 43.3 ordinary; b = 12 with chain 131 and 127; from b = 33 on nontemporal would win,
 // 201 against 228).
-template <class X, int VPT, RowMode MODE>
+template <class X, int VPT, RowMode MODE, bool NT>
 __device__ __forceinline__ void store_row(SELL_GLOBAL X *p, int64_t cs, const X (&o)[VPT]) {
     constexpr int bytes = VPT * int(sizeof(X));
     if constexpr (MODE == kAligned && bytes % 16 == 0) {
@@ -140,12 +141,14 @@ __device__ __forceinline__ void store_row(SELL_GLOBAL X *p, int64_t cs, const X 
         for (int q = 0; q < bytes / 16; ++q) {
             u32x4 v;
             __builtin_memcpy(&v, reinterpret_cast<const char *>(o) + 16 * q, 16);
-            __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x4 *>(p) + q);
+            if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x4 *>(p) + q);
+            else reinterpret_cast<SELL_GLOBAL u32x4 *>(p)[q] = v;
         }
     } else if constexpr (MODE == kAligned && bytes == 8) {
         u32x2 v;
         __builtin_memcpy(&v, o, 8);
-        __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x2 *>(p));
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<SELL_GLOBAL u32x2 *>(p));
+        else *reinterpret_cast<SELL_GLOBAL u32x2 *>(p) = v;
     } else if constexpr (MODE == kContig) {
         SELL_GLOBAL char *b = reinterpret_cast<SELL_GLOBAL char *>(p);
 #pragma unroll
@@ -188,7 +191,7 @@ constexpr int kBatchDefault = 8;
 // The product over the tiles of workgroup `tile` (one of a.nblocks) of one matrix.
 // FL != 0: the augmentation flags are known at compile time (a.flags == FL), so the unused
 // parts of the epilogue take no registers.
-template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0>
+template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false>
 __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, const int vl) {
     using V = typename KTypes<VK>::V;
     using X = typename KTypes<VK>::X;
@@ -399,8 +402,8 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
                         // clamp to the row's last entry so every load is in bounds and unconditional
                         const int k = min(k0 + u, len - 1);
                         const int64_t at = base + int64_t(k) * C;
-                        const int cc = __builtin_nontemporal_load(col + at);
-                        const V v = __builtin_nontemporal_load(val + at);
+                        const int cc = KEEP ? col[at] : __builtin_nontemporal_load(col + at);
+                        const V v = KEEP ? val[at] : __builtin_nontemporal_load(val + at);
                         ci[u] = (k0 + u < len) ? cc : -1;
                         vv[u] = v;
                     }
@@ -438,11 +441,22 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
         SELL_GLOBAL X *scratch = scratch_base + size_t(tid) * VPT;
         SELL_GLOBAL X *ydst = live ? Yp + row * yrs + int64_t(jb) * ycs : scratch;
         const int64_t ysd = live ? ycs : 1;
+        auto store = [&](SELL_GLOBAL X *p, int64_t cs, const X (&o)[VPT]) {
+            if (GEN && !col_ok) return;
+            if (KEEP && a.keep > 1) {
+                // (the empty statements keep the compiler from merging the two branches' stores)
+                asm volatile("");
+                store_row<X, VPT, VEC, false>(p, cs, o);
+                asm volatile("");
+            } else {
+                store_row<X, VPT, VEC, true>(p, cs, o);
+            }
+        };
         X out[VPT];
         if (!AUG) {
 #pragma unroll
             for (int t = 0; t < VPT; ++t) out[t] = X(acc[t]);
-            if (!GEN || col_ok) store_row<X, VPT, VEC>(ydst, ysd, out);
+            store(ydst, ysd, out);
         } else {
             X zout[VPT];
 #pragma unroll
@@ -463,10 +477,10 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
                 if (read_z) z = delta * double(zin[t]) + z;
                 zout[t] = X(z);
             }
-            if (!GEN || col_ok) store_row<X, VPT, VEC>(ydst, ysd, out);
-            if (chain && (!GEN || col_ok)) {
+            store(ydst, ysd, out);
+            if (chain) {
                 SELL_GLOBAL X *zdst = live ? Zp + row * zrs + int64_t(jb) * zcs : scratch;
-                store_row<X, VPT, VEC>(zdst, live ? zcs : 1, zout);
+                store(zdst, live ? zcs : 1, zout);
             }
         }
     };
@@ -630,10 +644,10 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     }
 }
 
-template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0>
+template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false>
 __global__ void __launch_bounds__(kBlock) prod_kernel(ProdArgs a, int vl) {
     const int tile = a.xcd_map ? xcd_block(blockIdx.x, gridDim.x) : int(blockIdx.x);  // index in the partials
-    prod_body<VK, B, VPT, AUG, UB, STG, FL>(a, tile, vl);
+    prod_body<VK, B, VPT, AUG, UB, STG, FL, KEEP>(a, tile, vl);
 }
 
 // The flags of a step of the Chebyshev / KPM recurrence (y = alpha (A x - c x) - y with
@@ -654,7 +668,7 @@ constexpr uint32_t kCgFlags = SELL_SPMV_DOT_YY | SELL_SPMV_DOT_XY;
 // One launch over a batch of matrices: workgroups [blk_start[m], blk_start[m+1]) of the
 // (XCD-remapped) grid work on matrix m, whose launch arguments are table[m]. A matrix m with
 // active != null and active[m] == 0 is skipped (its dot partials are zeroed).
-template <int VK, int B, int VPT, bool AUG, int UB = 0, uint32_t FL = 0>
+template <int VK, int B, int VPT, bool AUG, int UB = 0, uint32_t FL = 0, bool KEEP = false>
 __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__restrict__ table,
                                                             const int32_t *__restrict__ blk_start, int K,
                                                             const int32_t *__restrict__ active, int vl) {
@@ -674,7 +688,7 @@ __global__ void __launch_bounds__(kBlock) prod_batch_kernel(const ProdArgs *__re
             for (int q = threadIdx.x; q < 3 * a.nb; q += blockDim.x) to_global(a.partials)[size_t(q) * a.nblocks + tile] = 0.0;
         return;
     }
-    prod_body<VK, B, VPT, AUG, UB, false, FL>(a, tile, vl);
+    prod_body<VK, B, VPT, AUG, UB, false, FL, KEEP>(a, tile, vl);
 }
 
 // A batch whose matrices have block widths of their own, in one launch: every workgroup runs
@@ -769,13 +783,14 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
                      (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0))
         a.stage = 0;
     auto k = a.stage ? prod_kernel<VK, B, VPT, AUG, UB, (B > 0)> : prod_kernel<VK, B, VPT, AUG, UB>;
-    if constexpr (AUG && VK == VK_F64F64 && B != 0) {
-        if (!a.stage && a.flags == kKpmFlags)
-            k = prod_kernel<VK, B, VPT, AUG, UB, false, kKpmFlags>;
-    }
-    if constexpr (AUG && VK != VK_F64F64 && B != 0) {
-        if (!a.stage && a.flags == kCgFlags)
-            k = prod_kernel<VK, B, VPT, AUG, UB, false, kCgFlags>;
+    if constexpr (B != 0) {
+        const bool keep = a.keep != 0 && !a.stage;
+        if (keep) k = prod_kernel<VK, B, VPT, AUG, UB, false, 0, true>;
+        if constexpr (AUG) {
+            constexpr uint32_t FL = VK == VK_F64F64 ? kKpmFlags : kCgFlags;
+            if (!a.stage && a.flags == FL)
+                k = keep ? prod_kernel<VK, B, VPT, AUG, UB, false, FL, true> : prod_kernel<VK, B, VPT, AUG, UB, false, FL>;
+        }
     }
     if (a.stage) {
         a.nblocks = a.st_nblocks;  // the launch the plan was made for (stride checked there)
@@ -870,9 +885,13 @@ int dispatch_prod(ProdArgs &a, hipStream_t s, int path) {
 }
 
 template <int VK, int B, int VPT, bool AUG, int UB = 0>
-inline const void *bk_u(bool cg) {
+inline const void *bk_u(bool cg, bool keep) {
     if constexpr (AUG && VK != VK_F64F64 && B != 0) {
+        if (cg && keep) return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB, kCgFlags, true>);
         if (cg) return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB, kCgFlags>);
+    }
+    if constexpr (B != 0) {
+        if (keep) return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB, 0, true>);
     }
     return reinterpret_cast<const void *>(prod_batch_kernel<VK, B, VPT, AUG, UB>);
 }
@@ -881,42 +900,42 @@ inline const void *bk_u(bool cg) {
 // lane; 5 or 7 where the width's default is 8, as for the single-matrix kernels; else the
 // default)
 template <int VK, int B, int VPT, bool AUG>
-inline const void *bk(int ub0, int ubw, bool cg) {
+inline const void *bk(int ub0, int ubw, bool cg, bool keep) {
     using X = typename KTypes<VK>::X;
     if constexpr (B != 0) {
         const int ub = VPT * sizeof(X) >= 32 ? ubw : ub0;
-        if (ub == 7) return bk_u<VK, B, VPT, AUG, 7>(cg);
-        if (ub == 5) return bk_u<VK, B, VPT, AUG, 5>(cg);
+        if (ub == 7) return bk_u<VK, B, VPT, AUG, 7>(cg, keep);
+        if (ub == 5) return bk_u<VK, B, VPT, AUG, 5>(cg, keep);
     }
-    return bk_u<VK, B, VPT, AUG>(cg);
+    return bk_u<VK, B, VPT, AUG>(cg, keep);
 }
 
 // The batched kernel for (width, columns per lane, index batch length); path as in
 // dispatch_prod.
 template <int VK, bool AUG>
-const void *batch_kernel_for(int b, int vpt, int path, int ub, int ubw, uint32_t flags) {
+const void *batch_kernel_for(int b, int vpt, int path, int ub, int ubw, uint32_t flags, bool keep) {
     const bool cg = flags == kCgFlags;
     if (path == kPathFixed) {
         switch (b) {
-            case 1: return bk<VK, 1, 1, AUG>(ub, ubw, cg);
-            case 2: return vpt >= 2 ? bk<VK, 2, 2, AUG>(ub, ubw, cg) : bk<VK, 2, 1, AUG>(ub, ubw, cg);
-            case 4: return vpt >= 4 ? bk<VK, 4, 4, AUG>(ub, ubw, cg) : vpt == 2 ? bk<VK, 4, 2, AUG>(ub, ubw, cg) : bk<VK, 4, 1, AUG>(ub, ubw, cg);
-            case 8: return vpt >= 4 ? bk<VK, 8, 4, AUG>(ub, ubw, cg) : vpt == 2 ? bk<VK, 8, 2, AUG>(ub, ubw, cg) : bk<VK, 8, 1, AUG>(ub, ubw, cg);
+            case 1: return bk<VK, 1, 1, AUG>(ub, ubw, cg, keep);
+            case 2: return vpt >= 2 ? bk<VK, 2, 2, AUG>(ub, ubw, cg, keep) : bk<VK, 2, 1, AUG>(ub, ubw, cg, keep);
+            case 4: return vpt >= 4 ? bk<VK, 4, 4, AUG>(ub, ubw, cg, keep) : vpt == 2 ? bk<VK, 4, 2, AUG>(ub, ubw, cg, keep) : bk<VK, 4, 1, AUG>(ub, ubw, cg, keep);
+            case 8: return vpt >= 4 ? bk<VK, 8, 4, AUG>(ub, ubw, cg, keep) : vpt == 2 ? bk<VK, 8, 2, AUG>(ub, ubw, cg, keep) : bk<VK, 8, 1, AUG>(ub, ubw, cg, keep);
             case 16:
-                return vpt >= 4 ? bk<VK, 16, 4, AUG>(ub, ubw, cg) : vpt == 2 ? bk<VK, 16, 2, AUG>(ub, ubw, cg) : bk<VK, 16, 1, AUG>(ub, ubw, cg);
+                return vpt >= 4 ? bk<VK, 16, 4, AUG>(ub, ubw, cg, keep) : vpt == 2 ? bk<VK, 16, 2, AUG>(ub, ubw, cg, keep) : bk<VK, 16, 1, AUG>(ub, ubw, cg, keep);
             case 32:
-                return vpt >= 4 ? bk<VK, 32, 4, AUG>(ub, ubw, cg) : vpt == 2 ? bk<VK, 32, 2, AUG>(ub, ubw, cg) : bk<VK, 32, 1, AUG>(ub, ubw, cg);
+                return vpt >= 4 ? bk<VK, 32, 4, AUG>(ub, ubw, cg, keep) : vpt == 2 ? bk<VK, 32, 2, AUG>(ub, ubw, cg, keep) : bk<VK, 32, 1, AUG>(ub, ubw, cg, keep);
             default: break;
         }
     }
     if (path == kPathContig) {
         switch (run_time_vpt(b)) {
-            case 2: return bk<VK, -1, 2, AUG>(ub, ubw, cg);
-            case 3: return bk<VK, -1, 3, AUG>(ub, ubw, cg);
-            default: return bk<VK, -1, 4, AUG>(ub, ubw, cg);
+            case 2: return bk<VK, -1, 2, AUG>(ub, ubw, cg, keep);
+            case 3: return bk<VK, -1, 3, AUG>(ub, ubw, cg, keep);
+            default: return bk<VK, -1, 4, AUG>(ub, ubw, cg, keep);
         }
     }
-    return bk<VK, 0, 1, AUG>(ub, ubw, cg);
+    return bk<VK, 0, 1, AUG>(ub, ubw, cg, keep);
 }
 
 template <int VK, bool AUG>

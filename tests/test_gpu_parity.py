@@ -586,3 +586,43 @@ def test_grids_of_several_waves_equal_one_wave(sc, dt, b, n):
         assert all(torch.equal(u, v) for u, v in zip(o[:3], outs[0][:3]))
         assert bool(((o[3] - outs[0][3]).abs() <= 2 * (n + 8) * 2.0 ** -53 * mag).all())
     M.close()
+
+
+@pytest.mark.parametrize("dt,n,widths", [("f64", 118, (1, 3, 8, 12)), ("f32", 134, (4, 12, 16))])
+def test_cache_policies_equal_general_kernel(sc, dt, n, widths):
+    """Matrices either side of the cache policy's line (by b): products, their chains and a batch of
+    two matrices against the general kernel over column-major operands, y and z bit for bit."""
+    import torch
+
+    A = synth.anderson3d(n)
+    small = synth.anderson3d(12)
+    M, S = (sc.SellMatrix.from_csr(m, C=32, sigma=1, dtype=dt) for m in (A, small))
+    B = sc.SellBatch([M, S])
+    vt = torch.float64 if dt == "f64" else torch.float32
+    N, T = A.nrows, A.nrows + small.nrows
+    for b in widths:
+        x, y0, z0 = (torch.randn((T, b), dtype=vt, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(s))
+                     for s in (200, 201, 202))
+        xc, yc, zc = (v.t().contiguous().t() if b > 1 else v.clone() for v in (x, y0, z0))
+        for flags in (sc.SHIFT | sc.SCALE | sc.AXPBY | sc.DOT_YY | sc.DOT_XY, sc.SHIFT | sc.AXPBY | sc.DOTS | sc.CHAIN):
+            kw = dict(flags=flags, alpha=0.5, beta=-1.0, gamma=0.3, delta=1.0, eta=0.5)
+            y, z, yg, zg, yb, zb = y0.clone(), z0.clone(), yc.clone(), zc.clone(), y0.clone(), z0.clone()
+            d = torch.zeros(3 * b, dtype=torch.float64, device="cuda:0")
+            db = torch.zeros(6 * b, dtype=torch.float64, device="cuda:0")
+            for m, lo, hi in ((M, 0, N), (S, N, T)):
+                sc.sell_spmmv_aug(m, x[lo:hi], y[lo:hi], z[lo:hi], dot=d, **kw)
+                g = [torch.empty((b, hi - lo), dtype=vt, device="cuda:0").t().copy_(v[lo:hi]) for v in (xc, yc, zc)]
+                sc.sell_spmmv_aug(m, *g, dot=d, **kw)
+                yg[lo:hi], zg[lo:hi] = g[1], g[2]
+            sc.sell_batch_spmmv_aug(B, x, yb, zb, dot=db, **kw)
+            assert torch.equal(y, yg) and torch.equal(z, zg)
+            assert torch.equal(y, yb) and torch.equal(z, zb)
+        p, pb = torch.empty_like(x), torch.empty_like(x)
+        pc = torch.empty((b, N), dtype=vt, device="cuda:0").t()
+        sc.sell_spmmv(M, x[:N], p[:N])
+        sc.sell_spmmv(S, x[N:], p[N:])
+        sc.sell_spmmv(M, torch.empty((b, N), dtype=vt, device="cuda:0").t().copy_(x[:N]), pc)
+        sc.sell_batch_spmmv_aug(B, x, pb)
+        assert torch.equal(p[:N], pc) and torch.equal(p, pb)
+    for o in (B, M, S):
+        o.close()
