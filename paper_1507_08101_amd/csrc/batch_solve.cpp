@@ -180,33 +180,32 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
     if ((rc = DB.alloc(&pr64, nv * sizeof(double))) || (rc = DB.alloc(&pr, nv * isz)) ||
         (rc = DB.alloc(&pd, nv * isz)) || (rc = DB.alloc(&pp, nv * isz)) || (rc = DB.alloc(&pq, nv * isz)))
         return rc;
-    // device scalars: rho alpha beta thresh2 bb rr(3Kb) | vec partials (b G) | int32 flags
+    // Device scalars, what the host reads at a check in one piece (rho0 .. sys_active) and what it
+    // writes in one piece (active .. mask at the end of an update, mask and vblkr at its start):
+    //   alpha beta thresh2 bb | rr (3Kb) | vec partials (b G) | rho0 rho | active sys_active
+    //   column mask | vblk | mask | vblkr | iters (int64)
     const size_t gmax = size_t(std::max(std::max(sg.G, 4 * kCgMaxGrid), K));
-    const size_t nd = 5 * Kb + 3 * Kb + size_t(b) * gmax;
-    // active, sys_active, mask | iters (int64) | column mask | iteration and update workgroup offsets
-    const size_t ni = Kb + 2 * size_t(K) + 2 * size_t(K) + 2 + Kb + 2 * (size_t(K) + 1);
-    if ((rc = DB.alloc(&pscal, nd * sizeof(double) + ni * sizeof(int32_t) + 16)))
-        return rc;
+    const size_t nd = 4 * Kb + 3 * Kb + size_t(b) * gmax + 2 * Kb;
+    const size_t iSys = Kb, iCols = iSys + size_t(K), iVblk = iCols + Kb, iMask = iVblk + size_t(K) + 1,
+                 iVblkr = iMask + size_t(K), ni = iVblkr + size_t(K) + 1;
+    if ((rc = DB.alloc(&pscal, nd * sizeof(double) + ni * sizeof(int32_t) + 8 + size_t(K) * sizeof(int64_t)))) return rc;
     double *d = static_cast<double *>(pscal);
     BatchCg sc;
-    sc.rho = d;
-    sc.alpha = d + Kb;
-    sc.beta = d + 2 * Kb;
-    sc.thresh2 = d + 3 * Kb;
-    double *bb_d = d + 4 * Kb;
-    double *rr_d = d + 5 * Kb;
-    double *vparts = d + 8 * Kb;
+    sc.alpha = d;
+    sc.beta = d + Kb;
+    sc.thresh2 = d + 2 * Kb;
+    double *bb_d = d + 3 * Kb;
+    double *rr_d = d + 4 * Kb;
+    double *vparts = d + 7 * Kb;
+    double *rho0_d = d + nd - 2 * Kb;  // rho of each system's last update
+    sc.rho = rho0_d + Kb;
     int32_t *ip = reinterpret_cast<int32_t *>(d + nd);
     sc.active = ip;
-    sc.sys_active = ip + Kb;
-    int32_t *mask_d = ip + Kb + K;
-    int64_t *iters_d = reinterpret_cast<int64_t *>(ip + Kb + 2 * size_t(K));
+    sc.sys_active = ip + iSys;
+    int32_t *colmask_d = ip + iCols, *vblk_d = ip + iVblk, *mask_d = ip + iMask, *vblkr_d = ip + iVblkr;
     // align the int64 counters
-    iters_d = reinterpret_cast<int64_t *>((reinterpret_cast<uintptr_t>(iters_d) + 7) & ~uintptr_t(7));
+    int64_t *iters_d = reinterpret_cast<int64_t *>((reinterpret_cast<uintptr_t>(ip + ni) + 7) & ~uintptr_t(7));
     sc.iters = iters_d;
-    int32_t *colmask_d = reinterpret_cast<int32_t *>(iters_d + K);
-    int32_t *vblk_d = colmask_d + Kb;
-    int32_t *vblkr_d = vblk_d + K + 1;
 
     sell_bv Bview = *Bv;
     sell_bv R64 = view(pr64, n, b, SELL_F64), R = view(pr, n, b, idt), D = view(pd, n, b, idt),
@@ -217,8 +216,18 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
     // ||b||^2 per system and column
     if ((rc = bcg_launch_coldot(SELL_F64, Bv->ptr, Bv->ptr, b, sg, nullptr, vparts, bb_d, nullptr, nullptr, 0.0, s)))
         return rc;
-    std::vector<double> bb(Kb), rr(3 * Kb), rho(Kb), rho_last(Kb, 0.0), relres(size_t(K), INFINITY);
-    std::vector<int32_t> act(Kb, 1), sysact(size_t(K), 0), conv(size_t(K), 0), mask(size_t(K), 0), reset(Kb, 0);
+    std::vector<double> bb(Kb), rr(3 * Kb), relres(size_t(K), INFINITY);
+    std::vector<int32_t> conv(size_t(K), 0);
+    // host copies: of what is written (laid out as on the device; rewritten only after a
+    // synchronisation that follows the copy) and of what a check reads
+    std::vector<int32_t> up(ni, 0);
+    int32_t *act = up.data(), *sysact = act + iSys, *reset = act + iCols, *vblk = act + iVblk, *mask = act + iMask,
+            *vblkr = act + iVblkr;
+    std::fill(act, act + Kb, 1);
+    const size_t down_ints = Kb + size_t(K);
+    std::vector<double> down(2 * Kb + (down_ints + 1) / 2, 0.0);
+    const double *rho_last = down.data(), *rho = rho_last + Kb;
+    const int32_t *act_now = reinterpret_cast<const int32_t *>(rho + Kb), *sys_now = act_now + Kb;
     std::vector<int64_t> since(size_t(K), 0), refine(size_t(K), 0), its(size_t(K), 0);
     HIPCHK(hipMemcpyAsync(bb.data(), bb_d, Kb * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -226,34 +235,43 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
     std::vector<double> wrows(static_cast<size_t>(K));
     for (int m = 0; m < K; ++m) wrows[size_t(m)] = double(batch_matrix(A64, m)->h.nrows);
     // Vector-kernel workgroups of the flagged systems, split by their rows.
-    auto split_rows = [&](const std::vector<int32_t> &flag, std::vector<int32_t> &blk) {
+    std::vector<int32_t> blk;
+    auto split_rows = [&](const int32_t *flag, int32_t *out) {
         std::vector<int64_t> cap(static_cast<size_t>(K));
         int64_t rows = 0;
         for (int m = 0; m < K; ++m) {
-            const int64_t nr = flag[size_t(m)] ? batch_matrix(A64, m)->h.nrows : 0;
+            const int64_t nr = flag[m] ? batch_matrix(A64, m)->h.nrows : 0;
             cap[size_t(m)] = nr > 0 ? std::max<int64_t>(1, (nr + 3) / 4) : 0;
             rows += nr;
         }
         apportion(wrows, cap, bcg_vector_grid(idt, rows, b), blk);
+        std::copy(blk.begin(), blk.end(), out);
     };
     // The workgroups of the update's vector kernels, split over the systems it updates (with the
     // batch's own split, an update of a few systems ran on their small share of the grid).
-    std::vector<int32_t> vblkr;
-    BatchSeg sgr = sg;
+    BatchSeg sgr = sg, sgi = sg;
     sgr.vblk = vblkr_d;
+    // The split of an iteration's launches over the systems that iterate (appo_active); changed:
+    // since it was last asked for
+    std::vector<int32_t> appo_active(static_cast<size_t>(K), -1);
+    sgi.vblk = vblk_d;
+    bool changed = false;
+    auto resplit = [&]() {
+        if (std::equal(appo_active.begin(), appo_active.end(), sysact)) return false;
+        appo_active.assign(sysact, sysact + K);
+        split_rows(sysact, vblk);
+        sgi.G = vblk[K];
+        changed = true;
+        return true;
+    };
 
     // Reliable update of the systems with mask[m] != 0: fold D into x, true residual in FP64,
     // restart the systems that have not converged from it.
     auto refresh = [&]() -> int {
         int r;
-        HIPCHK(hipMemcpyAsync(mask_d, mask.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        {
-            split_rows(mask, vblkr);
-            sgr.G = vblkr[size_t(K)];
-            // vblkr is not touched again before the synchronisation below
-            HIPCHK(hipMemcpyAsync(vblkr_d, vblkr.data(), (size_t(K) + 1) * sizeof(int32_t), hipMemcpyHostToDevice,
-                                  s));
-        }
+        split_rows(mask, vblkr);
+        sgr.G = vblkr[K];
+        HIPCHK(hipMemcpyAsync(mask_d, mask, (ni - iMask) * sizeof(int32_t), hipMemcpyHostToDevice, s));
         if ((r = bcg_launch_refresh_prep(idt, static_cast<double *>(X->ptr), pd, static_cast<double *>(pr64),
                                          static_cast<const double *>(Bv->ptr), b, sgr, mask_d, s)))
             return r;
@@ -262,13 +280,13 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         o.alpha = -1.0;
         o.beta = 1.0;
         o.dot = rr_d;
-        if ((r = batch_aug_impl(A64, X, &R64, nullptr, o, true, mask_d, mask.data(), true, s, nullptr, nullptr, false)))
+        if ((r = batch_aug_impl(A64, X, &R64, nullptr, o, true, mask_d, mask, true, s, nullptr, nullptr, false)))
             return r;
         HIPCHK(hipMemcpyAsync(rr.data(), rr_d, 3 * Kb * sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         bool restart = false;
         for (int m = 0; m < K; ++m) {
-            if (!mask[size_t(m)]) continue;
+            if (!mask[m]) continue;
             ++refine[size_t(m)];
             since[size_t(m)] = 0;
             double worst = 0.0;
@@ -283,13 +301,10 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
             }
             relres[size_t(m)] = worst;
             conv[size_t(m)] = all ? 1 : 0;
-            sysact[size_t(m)] = all ? 0 : 1;
-            if (all) mask[size_t(m)] = 0;  // nothing to restart
+            sysact[m] = all ? 0 : 1;
+            if (all) mask[m] = 0;  // nothing to restart
             restart = restart || !all;
         }
-        HIPCHK(hipMemcpyAsync(sc.active, act.data(), Kb * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(sc.sys_active, sysact.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        if (!restart) return SELL_OK;
         // columns whose recursion drifted from the true residual restart from p = r (rho holds
         // the recursive residuals of the last check; 0 before the first iteration)
         bool any_reset = false;
@@ -297,46 +312,26 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
             for (int j = 0; j < b; ++j) {
                 const size_t q = size_t(m) * b + j;
                 const double r2 = rr[size_t(m) * 3 * b + j];
-                reset[q] = (mask[size_t(m)] && act[q] && !(rho[q] >= 0.01 * r2)) ? 1 : 0;
+                reset[q] = (mask[m] && act[q] && !(rho[q] >= 0.01 * r2)) ? 1 : 0;
                 any_reset = any_reset || reset[q];
             }
-        HIPCHK(hipMemcpyAsync(mask_d, mask.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, s));
+        (void)resplit();
+        HIPCHK(hipMemcpyAsync(sc.active, up.data(), iVblkr * sizeof(int32_t), hipMemcpyHostToDevice, s));
+        if (!restart) return SELL_OK;
         // r = r64 in the iteration's precision, rho = <r, r>; the recursion retires a column
         // itself only in FP64 (thresh2 = tol^2 ||b||^2), in FP32 only the true residual does
         if ((r = bcg_launch_convert(idt, pr, static_cast<const double *>(pr64), b, sgr, mask_d, vparts, sc.rho,
-                                    sc.thresh2, bb_d, mixed ? 0.0 : tol * tol, s)))
+                                    rho0_d, sc.thresh2, bb_d, mixed ? 0.0 : tol * tol, s)))
             return r;
-        if (any_reset) {
-            HIPCHK(hipMemcpyAsync(colmask_d, reset.data(), Kb * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            if ((r = bcg_launch_copy(idt, pp, pr, b, sgr, colmask_d, s))) return r;
-        }
-        HIPCHK(hipMemcpyAsync(rho.data(), sc.rho, Kb * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (int m = 0; m < K; ++m)
-            if (mask[size_t(m)])
-                for (int j = 0; j < b; ++j) rho_last[size_t(m) * b + j] = rho[size_t(m) * b + j];
+        // (the next check reads rho0, no sooner)
+        if (any_reset) return bcg_launch_copy(idt, pp, pr, b, sgr, colmask_d, s);
         return SELL_OK;
     };
 
     // first update: every system, x0 = X (D = 0, P = 0); rho = 0 makes every active column
     // start from p = r
-    std::fill(mask.begin(), mask.end(), 1);
+    std::fill(mask, mask + K, 1);
     if ((rc = refresh())) return rc;
-
-    // the split of an iteration's launches over the systems that iterate (appo_active)
-    std::vector<int32_t> appo_active(static_cast<size_t>(K), -1), vblk;
-    BatchSeg sgi = sg;
-    sgi.vblk = vblk_d;
-    auto resplit = [&](bool *changed) -> int {
-        *changed = appo_active != sysact;
-        if (!*changed) return SELL_OK;
-        appo_active = sysact;
-        split_rows(sysact, vblk);
-        sgi.G = vblk[size_t(K)];
-        HIPCHK(hipMemcpyAsync(vblk_d, vblk.data(), (size_t(K) + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        HIPCHK(hipStreamSynchronize(s));  // vblk is reused by the next split
-        return SELL_OK;
-    };
 
     sell_spmv_opts po = SELL_SPMV_OPTS_INIT;
     po.flags = SELL_SPMV_DOT_XY | SELL_SPMV_DOT_YY;
@@ -372,11 +367,11 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
     // solve ran 0.677 s against 0.667 s without a graph. With 64 equal systems (3 changes in 33
     // runs) the graph runs 0.218 s against 0.225 s.
     int stable = 0;
-    std::vector<int32_t> act_now(Kb), sys_now(static_cast<size_t>(K));
     while (!done && it < maxit) {
-        bool changed = false;
-        if ((rc = resplit(&changed))) return rc;
+        if (resplit())
+            HIPCHK(hipMemcpyAsync(vblk_d, vblk, (size_t(K) + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
         if (changed) {
+            changed = false;
             stable = 0;
             if (graph.ge) (void)hipGraphExecDestroy(graph.ge);
             if (graph.g) (void)hipGraphDestroy(graph.g);
@@ -402,14 +397,13 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         ++stable;
         it += run;
         for (int m = 0; m < K; ++m)
-            if (sysact[size_t(m)]) since[size_t(m)] += run;
-        HIPCHK(hipMemcpyAsync(rho.data(), sc.rho, Kb * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(act_now.data(), sc.active, Kb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(sys_now.data(), sc.sys_active, K * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            if (sysact[m]) since[size_t(m)] += run;
+        HIPCHK(hipMemcpyAsync(down.data(), rho0_d, 2 * Kb * sizeof(double) + down_ints * sizeof(int32_t),
+                              hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         bool any = false;
         for (int m = 0; m < K; ++m) {
-            mask[size_t(m)] = 0;
+            mask[m] = 0;
             if (conv[size_t(m)]) continue;
             bool upd = it >= maxit || since[size_t(m)] >= inner_maxit;
             if (mixed) {
@@ -418,17 +412,17 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
                     if (act[q] && !(rho[q] > inner_tol * inner_tol * rho_last[q])) upd = true;  // NaN too
                 }
             } else {
-                upd = upd || !sys_now[size_t(m)];  // the recursion retired every column
+                upd = upd || !sys_now[m];  // the recursion retired every column
             }
             if (upd) {
-                mask[size_t(m)] = 1;
+                mask[m] = 1;
                 any = true;
             }
         }
         if (!mixed) {
             // keep the host's view of the column flags in step with the recursion's
             for (size_t q = 0; q < Kb; ++q) act[q] = act_now[q];
-            for (int m = 0; m < K; ++m) sysact[size_t(m)] = sys_now[size_t(m)];
+            for (int m = 0; m < K; ++m) sysact[m] = sys_now[m];
         }
         if (any && (rc = refresh())) return rc;
         done = std::all_of(conv.begin(), conv.end(), [](int32_t c) { return c != 0; });

@@ -257,25 +257,47 @@ __global__ void __launch_bounds__(kVT) coldot_finish_kernel(const double *partia
     }
 }
 
-// p = r in the columns with colmask[j] != 0 (one system)
-template <class T>
-__global__ void __launch_bounds__(kVT) copy_cols_kernel(T *P, const T *R, int64_t n, int b, int64_t ld,
-                                                        const int32_t *colmask) {
-    const int64_t N = n * b;
+// p = r in the columns whose bit of cols is set (one system)
+__global__ void __launch_bounds__(kVT) copy_cols_kernel(float *P, const float *R, int64_t n, int b, int bpad,
+                                                        uint64_t cols) {
+    const int j = threadIdx.x & (bpad - 1), rows_per = kVT / bpad;
+    if (j >= b || !(cols >> j & 1)) return;
+    for (int64_t i = int64_t(blockIdx.x) * rows_per + threadIdx.x / bpad; i < n; i += int64_t(gridDim.x) * rows_per)
+        P[i * b + j] = R[i * b + j];
+}
+
+// x += d, d = 0 (the FP32 correction folded into the FP64 solution)
+__global__ void __launch_bounds__(kVT) fold_kernel(double *X, float *D, int64_t N) {
     for (int64_t e = int64_t(blockIdx.x) * kVT + threadIdx.x; e < N; e += int64_t(gridDim.x) * kVT) {
-        const int64_t i = e / b;
-        const int j = int(e - i * b);
-        if (colmask[j]) P[i * ld + j] = R[i * ld + j];
+        X[e] += double(D[e]);
+        D[e] = 0.0f;
     }
 }
 
-// x += d (the FP32 correction folded into the FP64 solution)
-__global__ void __launch_bounds__(kVT) axpy_mixed_kernel(double *X, const float *D, int64_t n, int b, int64_t ld) {
-    const int64_t N = n * b;
-    for (int64_t e = int64_t(blockIdx.x) * kVT + threadIdx.x; e < N; e += int64_t(gridDim.x) * kVT) {
-        const int64_t i = e / b;
-        const int j = int(e - i * b);
-        X[i * ld + j] += double(D[i * ld + j]);
+// r = r64 (round to nearest) with the partials of <r, r>: one pass where a copy and a dot read r again
+// (and the flags come as launch arguments, without a copy from the host). With the correction cleared
+// as it is folded and b read in place, an update of 48^3 rows, b = 8 takes 5 launches instead of 9.
+__global__ void __launch_bounds__(kVT) restart_kernel(float *R, const double *R64, int64_t n, int b, int bpad,
+                                                      double *partials) {
+    const int j = threadIdx.x & (bpad - 1), rows_per = kVT / bpad;
+    double acc = 0.0;
+    if (j < b)
+        for (int64_t i = int64_t(blockIdx.x) * rows_per + threadIdx.x / bpad; i < n; i += int64_t(gridDim.x) * rows_per) {
+            const float r = float(R64[i * b + j]);
+            R[i * b + j] = r;
+            acc += double(r) * double(r);
+        }
+    colsum_store(acc, bpad, b, partials);
+}
+
+__global__ void __launch_bounds__(kVT) restart_finish_kernel(const double *partials, int G, CgDev sc, double *rho0,
+                                                             uint64_t active) {
+    const int j = blockIdx.x;
+    const double v = sum_partials(partials + size_t(j) * G, G);
+    if (threadIdx.x == 0) {
+        sc.rho[j] = rho0[j] = v;
+        sc.thresh2[j] = 0.0 * v;  // NaN for a residual that is not finite: the column stops
+        sc.active[j] = int32_t(active >> j & 1);
     }
 }
 
@@ -466,10 +488,10 @@ __global__ void __launch_bounds__(kVT) bcoldot_kernel(const T *U, const T *V, in
 }
 
 // result[m, j] = sum of the partials of system m, column j (systems with mask[m] != 0 only);
-// optionally thresh2[m, j] = f2 * (ref[m, j] or result[m, j]).
+// optionally thresh2[m, j] = f2 * (ref[m, j] or result[m, j]) and a second copy in result2.
 __global__ void __launch_bounds__(kVT) bcoldot_finish_kernel(const double *partials, int G, BatchSeg sg, int b,
-                                                             const int32_t *mask, double *result, double *thresh2,
-                                                             const double *ref, double f2) {
+                                                             const int32_t *mask, double *result, double *result2,
+                                                             double *thresh2, const double *ref, double f2) {
     const int m = blockIdx.x;
     if (mask && !mask[m]) return;
     const int v0 = sg.vblk[m], nv = sg.vblk[m + 1] - v0;
@@ -478,6 +500,7 @@ __global__ void __launch_bounds__(kVT) bcoldot_finish_kernel(const double *parti
         if (threadIdx.x == 0) {
             const int q = m * b + j;
             result[q] = v;
+            if (result2) result2[q] = v;
             if (thresh2) thresh2[q] = f2 * (ref ? ref[q] : v);
         }
     }
@@ -773,20 +796,24 @@ int cg_launch_coldot(int dt, const void *U, const void *V, int64_t n, int b, int
     return ok();
 }
 
-int cg_launch_copy_cols(int dt, void *P, const void *R, int64_t n, int b, int64_t ld, const int32_t *colmask,
-                        hipStream_t s) {
+int cg_launch_copy_cols(float *P, const float *R, int64_t n, int b, uint64_t cols, hipStream_t s) {
     if (n * b == 0) return SELL_OK;
-    if (dt == SELL_F64)
-        hipLaunchKernelGGL(copy_cols_kernel<double>, dim3(vgrid(n * b, 4096)), dim3(kVT), 0, s,
-                           static_cast<double *>(P), static_cast<const double *>(R), n, b, ld, colmask);
-    else
-        hipLaunchKernelGGL(copy_cols_kernel<float>, dim3(vgrid(n * b, 4096)), dim3(kVT), 0, s,
-                           static_cast<float *>(P), static_cast<const float *>(R), n, b, ld, colmask);
+    const int bpad = pow2_at_least(b);
+    hipLaunchKernelGGL(copy_cols_kernel, dim3(vgrid(n * bpad, 4096)), dim3(kVT), 0, s, P, R, n, b, bpad, cols);
     return ok();
 }
 
-int cg_launch_axpy_mixed(double *X, const float *D, int64_t n, int b, int64_t ld, hipStream_t s) {
-    hipLaunchKernelGGL(axpy_mixed_kernel, dim3(vgrid(n * b, 4096)), dim3(kVT), 0, s, X, D, n, b, ld);
+int cg_launch_fold(double *X, float *D, int64_t N, hipStream_t s) {
+    hipLaunchKernelGGL(fold_kernel, dim3(vgrid(N, 4096)), dim3(kVT), 0, s, X, D, N);
+    return ok();
+}
+
+int cg_launch_restart(float *R, const double *R64, int64_t n, int b, const CgDev &sc, double *rho0, uint64_t active,
+                      double *partials, hipStream_t s) {
+    const unsigned g = cg_reduce_grid(n, b);
+    hipLaunchKernelGGL(restart_kernel, dim3(g), dim3(kVT), 0, s, R, R64, n, b, pow2_at_least(b), partials);
+    if (ok() != SELL_OK) return SELL_ERR_HIP;
+    hipLaunchKernelGGL(restart_finish_kernel, dim3(b), dim3(kVT), 0, s, partials, int(g), sc, rho0, active);
     return ok();
 }
 
@@ -858,7 +885,7 @@ int bcg_launch_coldot(int dt, const void *U, const void *V, int b, const BatchSe
                            bpad, sg, mask, partials);
     if (ok() != SELL_OK) return SELL_ERR_HIP;
     hipLaunchKernelGGL(bcoldot_finish_kernel, dim3(sg.K), dim3(kVT), 0, s, partials, sg.G, sg, b, mask, result,
-                       thresh2, ref, f2);
+                       static_cast<double *>(nullptr), thresh2, ref, f2);
     return ok();
 }
 
@@ -920,7 +947,8 @@ int bcg_launch_refresh_prep(int dt, double *X, void *D, double *R64, const doubl
 }
 
 int bcg_launch_convert(int dt, void *R, const double *R64, int b, const BatchSeg &sg, const int32_t *mask,
-                       double *partials, double *rho, double *thresh2, const double *ref, double f2, hipStream_t s) {
+                       double *partials, double *rho, double *rho0, double *thresh2, const double *ref, double f2,
+                       hipStream_t s) {
     const int bpad = pow2_at_least(b);
     if (sg.G > 0 && !(dt == SELL_F64 ? blaunch_convert_pairs(tp<double>(R), R64, b, sg, mask, partials, s)
                                      : blaunch_convert_pairs(tp<float>(R), R64, b, sg, mask, partials, s))) {
@@ -934,7 +962,7 @@ int bcg_launch_convert(int dt, void *R, const double *R64, int b, const BatchSeg
         if (ok() != SELL_OK) return SELL_ERR_HIP;
     }
     hipLaunchKernelGGL(bcoldot_finish_kernel, dim3(sg.K), dim3(kVT), 0, s, partials, sg.G, sg, b, mask, rho,
-                       thresh2, ref, f2);
+                       rho0, thresh2, ref, f2);
     return ok();
 }
 

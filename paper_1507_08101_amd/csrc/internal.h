@@ -273,10 +273,13 @@ int cg_launch_rho(const double *rp_parts, int G, int b, const CgDev &sc, hipStre
 int cg_launch_coldot(int dt, const void *U, const void *V, int64_t n, int b, int64_t ld, double *result,
                      double *partials, double *thresh2, int32_t *active, const double *ref, double f2,
                      hipStream_t s);
-// P = R in the columns with colmask[j] != 0 (device flags)
-int cg_launch_copy_cols(int dt, void *P, const void *R, int64_t n, int b, int64_t ld, const int32_t *colmask,
-                        hipStream_t s);
-int cg_launch_axpy_mixed(double *X, const float *D, int64_t n, int b, int64_t ld, hipStream_t s);
+// P = R in the columns whose bit of cols is set
+int cg_launch_copy_cols(float *P, const float *R, int64_t n, int b, uint64_t cols, hipStream_t s);
+// X += D, D = 0 (N elements)
+int cg_launch_fold(double *X, float *D, int64_t N, hipStream_t s);
+// R = R64 rounded; rho = rho0 = <r, r>, thresh2 = 0 and the column flags from the bits of active
+int cg_launch_restart(float *R, const double *R64, int64_t n, int b, const CgDev &sc, double *rho0, uint64_t active,
+                      double *partials, hipStream_t s);
 
 // Batched CG (cg.hip): K systems stored one after another in the block vectors.
 struct BatchSeg {
@@ -307,7 +310,8 @@ int bcg_launch_coldot(int dt, const void *U, const void *V, int b, const BatchSe
 int bcg_launch_refresh_prep(int dt, double *X, void *D, double *R64, const double *Bv, int b, const BatchSeg &sg,
                             const int32_t *mask, hipStream_t s);
 int bcg_launch_convert(int dt, void *R, const double *R64, int b, const BatchSeg &sg, const int32_t *mask,
-                       double *partials, double *rho, double *thresh2, const double *ref, double f2, hipStream_t s);
+                       double *partials, double *rho, double *rho0, double *thresh2, const double *ref, double f2,
+                       hipStream_t s);
 // P = R in the columns with colmask[m * b + j] != 0
 int bcg_launch_copy(int dt, void *P, const void *R, int b, const BatchSeg &sg, const int32_t *colmask,
                     hipStream_t s);

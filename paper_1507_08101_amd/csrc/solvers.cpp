@@ -66,9 +66,9 @@ sell_bv view(void *p, int64_t n, int b, int dt) {
 }
 
 struct Scalars {
-    double *rho, *pq, *alpha, *beta, *thresh2, *bb, *rr, *thresh_out;
+    double *rho, *rho0;   // rho0: rho of the last reliable update, read together with rho
+    double *pq, *alpha, *beta, *thresh2, *bb, *rr, *thresh_out;
     int32_t *active;
-    int32_t *colmask;     // per-column flags handed to the device (b)
     double *prod_parts;   // tile partials of the product's dots (3 b ntiles)
     double *vec_parts;    // workgroup partials of the vector kernels (b kCgMaxGrid)
     int32_t prod_tiles;
@@ -82,15 +82,15 @@ int alloc_scalars(Buffers &B, Scalars &S, int b, int32_t max_tiles) {
     int rc = B.alloc(reinterpret_cast<void **>(&d), sizeof(double) * n);
     if (rc) return rc;
     S.rho = d;
-    S.pq = d + b;
+    S.rho0 = d + b;
     S.alpha = d + 2 * b;
     S.beta = d + 3 * b;
     S.thresh2 = d + 4 * b;
     S.bb = d + 5 * b;
     S.rr = d + 6 * b;         // 3b
     S.thresh_out = d + 9 * b;
+    S.pq = d + 10 * b;
     S.active = reinterpret_cast<int32_t *>(d + 11 * b);
-    S.colmask = reinterpret_cast<int32_t *>(d + 13 * b);
     S.prod_parts = d + 16 * b;
     S.vec_parts = S.prod_parts + 3 * size_t(b) * nt;
     S.prod_tiles = max_tiles;
@@ -135,24 +135,26 @@ int cg_iterate(const sell_mat *A, int dt, sell_bv &X, sell_bv &R, sell_bv &P, se
     return SELL_OK;
 }
 
-// r = b - A x in FP64 (b preloaded into R), <r, r> into S.rr[0..b)
+// r = b - A x in FP64 (the product reads b where its rows allow R's vector accesses; else a copy
+// of it in R), <r, r> into S.rr[0..b)
 int true_residual(const sell_mat *A64, const sell_bv *Bv, const sell_bv *X, sell_bv &R, const Scalars &S,
                   hipStream_t s) {
-    int rc = launch_copy(&R, Bv, s);
+    const bool in_place = (reinterpret_cast<uintptr_t>(Bv->ptr) & 15u) == 0;
+    int rc = in_place ? SELL_OK : launch_copy(&R, Bv, s);
     if (rc) return rc;
     sell_spmv_opts o = SELL_SPMV_OPTS_INIT;
     o.flags = SELL_SPMV_SCALE | SELL_SPMV_AXPBY | SELL_SPMV_DOT_YY;
     o.alpha = -1.0;
     o.beta = 1.0;
     o.dot = S.rr;
-    return aug_impl(A64, X, &R, nullptr, o, true, s);
+    return aug_impl(A64, X, &R, nullptr, o, true, s, nullptr, nullptr, nullptr, in_place ? Bv : nullptr);
 }
 
 int relres_host(const Scalars &S, int b, hipStream_t s, double *worst) {
-    double rr[64], bb[64];
-    HIPCHK(hipMemcpyAsync(rr, S.rr, sizeof(double) * b, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(bb, S.bb, sizeof(double) * b, hipMemcpyDeviceToHost, s));
+    double h[2 * 64];  // bb and, next to it, <y, y> of rr
+    HIPCHK(hipMemcpyAsync(h, S.bb, sizeof(double) * 2 * b, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const double *bb = h, *rr = h + b;
     *worst = 0.0;
     for (int j = 0; j < b; ++j) {
         const double r = bb[j] > 0 ? std::sqrt(rr[j] / bb[j]) : std::sqrt(rr[j]);
@@ -260,18 +262,17 @@ int sell_cg_mixed(const sell_mat *A64, const sell_mat *Alo, const sell_bv *Bv, s
     if ((rc = cg_launch_coldot(SELL_F64, Bv->ptr, Bv->ptr, n, b, b, S.bb, S.vec_parts, nullptr, nullptr, nullptr,
                                0.0, s)))
         return rc;
-    double bb[64], rr[64], rho[64], rho_last[64];
-    int32_t act[64], reset[64];
-    for (int j = 0; j < b; ++j) rho[j] = 0.0;
+    double bb[64], rr[64], rho2[2 * 64] = {};  // rho and, next to it, rho of the last update
+    const double *rho = rho2, *rho_last = rho2 + b;
+    bool act[64];
     HIPCHK(hipMemcpyAsync(bb, S.bb, sizeof(double) * b, hipMemcpyDeviceToHost, s));
 
-    // Reliable update: fold the FP32 correction into x (FP64), recompute the true residual
-    // r = b - A x in FP64, restart the FP32 recursion from it (the search direction is
+    // Reliable update: fold the FP32 correction into x (FP64) and clear it, recompute the true
+    // residual r = b - A x in FP64, restart the FP32 recursion from it (the search direction is
     // kept). Returns through *done whether every column meets the tolerance.
     auto reliable_update = [&](bool fold, bool *done) -> int {
         int r;
-        if (fold && (r = cg_launch_axpy_mixed(static_cast<double *>(X->ptr), static_cast<const float *>(D.ptr), n,
-                                              b, b, s)))
+        if (fold && (r = cg_launch_fold(static_cast<double *>(X->ptr), static_cast<float *>(D.ptr), n * b, s)))
             return r;
         if ((r = true_residual(A64, Bv, X, R64, S, s))) return r;
         HIPCHK(hipMemcpyAsync(rr, S.rr, sizeof(double) * b, hipMemcpyDeviceToHost, s));
@@ -281,38 +282,32 @@ int sell_cg_mixed(const sell_mat *A64, const sell_mat *Alo, const sell_bv *Bv, s
         for (int j = 0; j < b; ++j) {
             const double rel = bb[j] > 0 ? std::sqrt(rr[j] / bb[j]) : std::sqrt(rr[j]);
             if (!(rel <= worst)) worst = rel;
-            act[j] = rel <= tol ? 0 : 1;
+            act[j] = !(rel <= tol);
             all = all && !act[j];
         }
         st.relres = worst;
         *done = all;
         if (all) return SELL_OK;
-        bool any_reset = false;
+        uint64_t active = 0, reset = 0;  // bit per column
         for (int j = 0; j < b; ++j) {
-            reset[j] = (act[j] && !(rho[j] >= 0.01 * rr[j])) ? 1 : 0;  // recursion drifted (or first update)
-            any_reset = any_reset || reset[j];
+            active |= uint64_t(act[j] ? 1 : 0) << j;
+            // recursion drifted (or first update)
+            reset |= uint64_t(act[j] && !(rho[j] >= 0.01 * rr[j]) ? 1 : 0) << j;
         }
-        if ((r = launch_copy(&R, &R64, s))) return r;  // FP64 -> FP32, round to nearest
-        if ((r = launch_fill(D.ptr, SELL_F32, n, b, b, 1, 0.0, s))) return r;
-        // rho = <r32, r32>; thresh2 = 0 so the FP32 recursion never retires a column itself
-        if ((r = cg_launch_coldot(SELL_F32, R.ptr, R.ptr, n, b, b, S.rho, S.vec_parts, S.thresh2, S.active, nullptr,
-                                  0.0, s)))
+        // r = r64 (round to nearest), rho = <r, r>; thresh2 = 0 so the FP32 recursion never retires
+        // a column itself. rho is read at the next check, no sooner.
+        if ((r = cg_launch_restart(static_cast<float *>(R.ptr), static_cast<const double *>(R64.ptr), n, b, S.dev(),
+                                   S.rho0, active, S.vec_parts, s)))
             return r;
-        HIPCHK(hipMemcpyAsync(S.active, act, sizeof(int32_t) * b, hipMemcpyHostToDevice, s));
-        if (any_reset) {
-            HIPCHK(hipMemcpyAsync(S.colmask, reset, sizeof(int32_t) * b, hipMemcpyHostToDevice, s));
-            if ((r = cg_launch_copy_cols(SELL_F32, P.ptr, R.ptr, n, b, b, S.colmask, s))) return r;
-        }
-        HIPCHK(hipMemcpyAsync(rho_last, S.rho, sizeof(double) * b, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (int j = 0; j < b; ++j) rho[j] = rho_last[j];
+        if (reset) return cg_launch_copy_cols(static_cast<float *>(P.ptr), static_cast<const float *>(R.ptr), n, b, reset, s);
         return SELL_OK;
     };
 
     bool done = false;
     // p = 0 in every column (a converged column keeps it); the first update sets p = r in the
     // active columns (rho = 0 there marks the recursion as drifted)
-    if ((rc = launch_fill(P.ptr, SELL_F32, n, b, b, 1, 0.0, s))) return rc;
+    if ((rc = launch_fill(P.ptr, SELL_F32, n, b, b, 1, 0.0, s)) || (rc = launch_fill(D.ptr, SELL_F32, n, b, b, 1, 0.0, s)))
+        return rc;
     if ((rc = reliable_update(false, &done))) return rc;
     sell_spmv_opts o = SELL_SPMV_OPTS_INIT;
     o.flags = SELL_SPMV_DOT_XY | SELL_SPMV_DOT_YY;
@@ -328,7 +323,7 @@ int sell_cg_mixed(const sell_mat *A64, const sell_mat *Alo, const sell_bv *Bv, s
         if (st.iterations % kCheckEvery == 0 || st.iterations == maxit) {
             if ((rc = cg_launch_rho(S.vec_parts, G, b, S.dev(), s))) return rc;
             G = 0;
-            HIPCHK(hipMemcpyAsync(rho, S.rho, sizeof(double) * b, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipMemcpyAsync(rho2, S.rho, sizeof(double) * 2 * b, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             bool update = st.iterations == maxit || since >= inner_maxit;
             for (int j = 0; j < b; ++j)
