@@ -47,7 +47,6 @@ void free_device(sell_mat *A) {
     lib_free(A->d_cs);
     lib_free(A->d_perm);
     lib_free(A->d_tiles);
-    lib_free(A->d_rowslot);
     lib_free(A->d_rowptr);
     lib_free(A->d_tpos);
     A->d_tpos = nullptr;
@@ -67,7 +66,6 @@ void free_device(sell_mat *A) {
     A->d_cs = nullptr;
     A->d_perm = nullptr;
     A->d_tiles = nullptr;
-    A->d_rowslot = nullptr;
     A->d_rowptr = nullptr;
     if (A->device != cur) (void)hipSetDevice(cur);
 }
@@ -564,33 +562,23 @@ int sell_export_csr(const sell_mat *A, int64_t *rowptr, int32_t *col, double *va
 }  // extern "C"
 
 namespace sellcs {
-int ensure_update_maps(sell_mat *A, hipStream_t s) {
+int ensure_row_pointers(sell_mat *A, hipStream_t s) {
     if (A->d_rowptr) return SELL_OK;
     const HostSell &h = A->h;
     // on the device; on the host where that is not possible (size, or device memory for its scratch)
-    int rd = device_row_maps(A, &A->d_rowptr, &A->d_rowslot, s);
+    int rd = device_row_pointers(A, &A->d_rowptr, s);
     if (rd != SELL_ERR_UNSUPPORTED && rd != SELL_ERR_OOM) return rd;
     (void)hipGetLastError();
-    std::vector<int32_t> rowslot(static_cast<size_t>(h.nrows));
-    for (int64_t slot = 0; slot < h.nch * h.C; ++slot) {
-        const int64_t row = h.has_perm ? h.perm[slot] : (slot < h.nrows ? slot : -1);
-        if (row >= 0) rowslot[row] = int32_t(slot);
-    }
-    // both maps are built before either is published: d_rowptr marks them as present, so a
-    // failure half way must not leave it set
+    // published only when whole: d_rowptr marks the array as present
     int64_t *rp = nullptr;
-    int32_t *rs = nullptr;
     int rc = dev_upload(&rp, h.rowptr.data(), h.rowptr.size(), s);
-    if (!rc) rc = dev_upload(&rs, rowslot.data(), rowslot.size(), s);
     if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = SELL_ERR_HIP;
     if (rc) {
         (void)hipStreamSynchronize(s);
         (void)lib_free(rp);
-        (void)lib_free(rs);
         return rc;
     }
     A->d_rowptr = rp;
-    A->d_rowslot = rs;
     return SELL_OK;
 }
 }  // namespace sellcs
@@ -603,15 +591,12 @@ int sell_update_values_device(sell_mat *A, const double *val, void *stream) {
     if (!val && A->h.nnz > 0) return SELL_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     try {
-        if ((rc = ensure_update_maps(A, s))) return rc;
+        if ((rc = ensure_row_pointers(A, s))) return rc;
     } catch (const std::bad_alloc &) {
         return SELL_ERR_OOM;
     }
-    if ((rc = launch_update_values(A, val, s))) return rc;
-    // keep the SELL copy of A^T in step: every value goes straight to its slot there
-    if (A->transpose && A->h.nnz > 0)
-        rc = launch_scatter_values(val, A->d_tpos, A->h.nnz, A->transpose->h.vdt, A->transpose->d_val, s);
-    return rc;
+    // with the SELL copy of A^T kept in step
+    return launch_update_values(A, val, s);
 }
 
 int sell_update_values(sell_mat *A, const double *val, void *stream) {
@@ -770,8 +755,8 @@ int ensure_transpose(const sell_mat *A, hipStream_t s) {
     const HostSell &h = A->h;
     if (A->on_device) {
         sell_mat *M = const_cast<sell_mat *>(A);
-        int rd = ensure_update_maps(M, s);
-        if (rd == SELL_OK) rd = device_transpose(A, &M->transpose, &M->d_tpos, s);
+        int rd = ensure_row_pointers(M, s);
+        if (rd == SELL_OK) rd = device_transpose(A, &M->transpose, &M->d_tpos, &M->tpos_wide, s);
         if (rd != SELL_ERR_UNSUPPORTED && rd != SELL_ERR_OOM) return rd;
         (void)hipGetLastError();  // too large, or no device memory for the scratch: on the host
     }
@@ -824,14 +809,21 @@ int ensure_transpose(const sell_mat *A, hipStream_t s) {
         for (int64_t p = 0; p < h.nnz; ++p) tpos[p] = sell_of_q[tpos[p]];
     }
     sell_mat *M = const_cast<sell_mat *>(A);
-    rc = dev_upload(&M->d_tpos, tpos.data(), tpos.size(), s);
+    const bool wide = T->h.stored > INT32_MAX;
+    int64_t *p64 = nullptr;
+    int32_t *p32 = nullptr;
+    std::vector<int32_t> narrow;
+    if (!wide) narrow.assign(tpos.begin(), tpos.end());
+    rc = wide ? dev_upload(&p64, tpos.data(), tpos.size(), s) : dev_upload(&p32, narrow.data(), narrow.size(), s);
     if (rc == SELL_OK && hipStreamSynchronize(s) != hipSuccess) rc = SELL_ERR_HIP;
     if (rc) {
         sell_destroy(T);
-        lib_free(M->d_tpos);
-        M->d_tpos = nullptr;
+        lib_free(p64);
+        lib_free(p32);
         return rc;
     }
+    M->d_tpos = wide ? static_cast<void *>(p64) : static_cast<void *>(p32);
+    M->tpos_wide = wide;
     M->transpose = T;
     return SELL_OK;
 }

@@ -110,7 +110,7 @@ int sell_grad_values(const sell_mat *A, const sell_bv *G, const sell_bv *X, doub
     if (!dval && A->h.nnz > 0) return SELL_ERR_ARG;
     if (A->h.nnz == 0) return SELL_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((rc = ensure_update_maps(const_cast<sell_mat *>(A), s))) return rc;
+    if ((rc = ensure_row_pointers(const_cast<sell_mat *>(A), s))) return rc;
     GradPairs p;
     p.n = 1;
     p.g[0] = G->ptr;
@@ -227,7 +227,7 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
     if (n == 0) return SELL_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     try {
-        if ((rc = ensure_transpose(A, s)) || (rc = ensure_update_maps(const_cast<sell_mat *>(A), s))) return rc;
+        if ((rc = ensure_transpose(A, s)) || (rc = ensure_row_pointers(const_cast<sell_mat *>(A), s))) return rc;
     } catch (const std::bad_alloc &) {
         return SELL_ERR_OOM;
     }

@@ -119,11 +119,10 @@ __global__ void __launch_bounds__(kT) fill_kernel(const int64_t *rowptr, const i
     }
 }
 
-// One thread per slot: rowslot[row] = slot, len[row] = the row's entries (padding, column -1, only
-// follows them); len[nrows] = 0 for the prefix sum.
-__global__ void __launch_bounds__(kT) row_maps_kernel(const int32_t *col, const int32_t *cl, const int64_t *cs,
-                                                      const int32_t *perm, int64_t nrows, int32_t C, int32_t *rowslot,
-                                                      int64_t *len) {
+// One thread per slot: len[row] = the row's entries (padding, column -1, only follows them);
+// len[nrows] = 0 for the prefix sum.
+__global__ void __launch_bounds__(kT) row_lengths_kernel(const int32_t *col, const int32_t *cl, const int64_t *cs,
+                                                         const int32_t *perm, int64_t nrows, int32_t C, int64_t *len) {
     for (int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x; s <= nrows; s += int64_t(gridDim.x) * kT) {
         if (s == nrows) {
             len[nrows] = 0;
@@ -133,7 +132,6 @@ __global__ void __launch_bounds__(kT) row_maps_kernel(const int32_t *col, const 
         const int32_t m = cl[c];
         int32_t n = 0;
         while (n < m && col[base + int64_t(n) * C] >= 0) ++n;
-        rowslot[row] = int32_t(s);
         len[row] = n;
     }
 }
@@ -189,12 +187,13 @@ __global__ void __launch_bounds__(kT) inverse_kernel(const int32_t *perm, int64_
 }
 
 // tpos[p] = position in the SELL arrays of A^T of CSR entry p of A
+template <class P>
 __global__ void __launch_bounds__(kT) tpos_kernel(const uint32_t *key, const int32_t *pos, int64_t nnz,
                                                   const int64_t *trp, const int32_t *slot_of, const int64_t *cs,
-                                                  int32_t C, int64_t *tpos) {
+                                                  int32_t C, P *tpos) {
     for (int64_t q = int64_t(blockIdx.x) * kT + threadIdx.x; q < nnz; q += int64_t(gridDim.x) * kT) {
         const int64_t t = key[q], slot = slot_of ? int64_t(slot_of[t]) : t, c = slot / C;
-        tpos[pos[q]] = cs[c] + (q - trp[t]) * C + (slot - c * C);
+        tpos[pos[q]] = P(cs[c] + (q - trp[t]) * C + (slot - c * C));
     }
 }
 
@@ -367,17 +366,15 @@ int build_device_sell(sell_mat *M, int64_t nrows, int64_t ncols, const int64_t *
         if (e_ != hipSuccess) return herr(e_); \
     } while (0)
 
-int device_row_maps(const sell_mat *A, int64_t **rowptr, int32_t **rowslot, hipStream_t s) {
+int device_row_pointers(const sell_mat *A, int64_t **rowptr, hipStream_t s) {
     const HostSell &h = A->h;
     if (h.nrows + 1 > INT32_MAX) return SELL_ERR_UNSUPPORTED;  // the scan counts its items in 32 bits
     DevTemp T, keep;
     int64_t *len, *rp;
-    int32_t *rs;
     DCHK(keep.alloc(reinterpret_cast<void **>(&rp), sizeof(int64_t) * (size_t(h.nrows) + 1)));
-    DCHK(keep.alloc(reinterpret_cast<void **>(&rs), sizeof(int32_t) * size_t(std::max<int64_t>(h.nrows, 1))));
     DCHK(T.alloc(reinterpret_cast<void **>(&len), sizeof(int64_t) * (size_t(h.nrows) + 1)));
-    hipLaunchKernelGGL(row_maps_kernel, dim3(grid_for(h.nrows + 1)), dim3(kT), 0, s, A->d_col, A->d_cl, A->d_cs, A->d_perm,
-                       h.nrows, h.C, rs, len);
+    hipLaunchKernelGGL(row_lengths_kernel, dim3(grid_for(h.nrows + 1)), dim3(kT), 0, s, A->d_col, A->d_cl, A->d_cs, A->d_perm,
+                       h.nrows, h.C, len);
     DCHK(hipGetLastError());
     size_t bytes = 0;
     void *tmp = nullptr;
@@ -387,20 +384,19 @@ int device_row_maps(const sell_mat *A, int64_t **rowptr, int32_t **rowslot, hipS
     DCHK(hipStreamSynchronize(s));
     keep.p.clear();
     *rowptr = rp;
-    *rowslot = rs;
     return SELL_OK;
 }
 
-int device_transpose(const sell_mat *A, sell_mat **out, int64_t **out_tpos, hipStream_t s) {
+int device_transpose(const sell_mat *A, sell_mat **out, void **out_tpos, bool *wide, hipStream_t s) {
     const HostSell &h = A->h;
     if (h.nnz > INT32_MAX || h.nnz == 0) return SELL_ERR_UNSUPPORTED;  // positions are sorted as 32-bit payloads
     DevTemp T, keep;
     uint32_t *key, *key_s;
     int32_t *pos, *pos_s, *row_of, *tcol, *slot_of = nullptr;
     double *value, *tval;
-    int64_t *trp, *tpos;
+    int64_t *trp;
+    void *tpos = nullptr;
     const size_t nnz = size_t(h.nnz);
-    DCHK(keep.alloc(reinterpret_cast<void **>(&tpos), 8 * nnz));
     DCHK(T.alloc(reinterpret_cast<void **>(&key), 4 * nnz));
     DCHK(T.alloc(reinterpret_cast<void **>(&key_s), 4 * nnz));
     DCHK(T.alloc(reinterpret_cast<void **>(&pos), 4 * nnz));
@@ -437,16 +433,23 @@ int device_transpose(const sell_mat *A, sell_mat **out, int64_t **out_tpos, hipS
     int rc = SELL_ERR_OOM;
     try {
         rc = build_device_sell(M, h.ncols, h.nrows, trp, tcol, tval, h.C, h.sigma, h.vdt, s);
-        if (rc == SELL_OK && M->d_perm) {
-            const hipError_t e = T.alloc(reinterpret_cast<void **>(&slot_of), 4 * size_t(h.ncols));
-            if (e != hipSuccess) rc = herr(e);
-        }
+        *wide = M->h.stored > INT32_MAX;
+        hipError_t e = hipSuccess;
+        if (rc == SELL_OK) e = keep.alloc(&tpos, (*wide ? 8 : 4) * nnz);
+        if (rc == SELL_OK && e == hipSuccess && M->d_perm)
+            e = T.alloc(reinterpret_cast<void **>(&slot_of), 4 * size_t(h.ncols));
+        if (e != hipSuccess) rc = herr(e);
     } catch (const std::bad_alloc &) {
         rc = SELL_ERR_OOM;
     }
     if (rc == SELL_OK) {
         if (slot_of) hipLaunchKernelGGL(inverse_kernel, dim3(grid_for(h.ncols)), bl, 0, s, M->d_perm, h.ncols, slot_of);
-        hipLaunchKernelGGL(tpos_kernel, gz, bl, 0, s, key_s, pos_s, h.nnz, trp, slot_of, M->d_cs, h.C, tpos);
+        if (*wide)
+            hipLaunchKernelGGL(tpos_kernel<int64_t>, gz, bl, 0, s, key_s, pos_s, h.nnz, trp, slot_of, M->d_cs, h.C,
+                               static_cast<int64_t *>(tpos));
+        else
+            hipLaunchKernelGGL(tpos_kernel<int32_t>, gz, bl, 0, s, key_s, pos_s, h.nnz, trp, slot_of, M->d_cs, h.C,
+                               static_cast<int32_t *>(tpos));
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = SELL_ERR_HIP;
     }
     if (rc) {

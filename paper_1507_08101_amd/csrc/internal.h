@@ -90,12 +90,12 @@ namespace sellcs {
 int build_device_sell(sell_mat *M, int64_t nrows, int64_t ncols, const int64_t *rowptr, const int32_t *col,
                       const double *val, int32_t C, int64_t sigma, int vdt, hipStream_t s);
 
-// On the device, from the matrix's device arrays (devbuild.hip): the update maps (CSR row pointers
-// and row -> slot); the SELL copy of A^T with the position in it of each CSR entry (needs the maps).
+// On the device, from the matrix's device arrays (devbuild.hip): the CSR row pointers; the SELL copy
+// of A^T with the position in it of each CSR entry (needs the row pointers).
 // Synchronous; on error nothing is left allocated. SELL_ERR_UNSUPPORTED: too large for the 32-bit
 // counts of the device steps (or empty).
-int device_row_maps(const sell_mat *A, int64_t **rowptr, int32_t **rowslot, hipStream_t s);
-int device_transpose(const sell_mat *A, sell_mat **T, int64_t **tpos, hipStream_t s);
+int device_row_pointers(const sell_mat *A, int64_t **rowptr, hipStream_t s);
+int device_transpose(const sell_mat *A, sell_mat **T, void **tpos, bool *wide, hipStream_t s);
 
 // Value conversion (round to nearest, ties to even, from the double).
 uint16_t f64_to_bf16_bits(double v);
@@ -115,10 +115,10 @@ struct sell_mat {
     int64_t *d_cs = nullptr;
     int32_t *d_perm = nullptr;    // null when rows keep their order
     int32_t *d_tiles = nullptr;
-    int32_t *d_rowslot = nullptr; // row -> slot, built on first device value update
     int64_t *d_rowptr = nullptr;  // CSR row pointers, built on first device value update
     sell_mat *transpose = nullptr;  // SELL copy of A^T for the deterministic transpose
-    int64_t *d_tpos = nullptr;      // position in the SELL arrays of A^T of each CSR entry of A
+    void *d_tpos = nullptr;         // position in the SELL arrays of A^T of each CSR entry of A
+    bool tpos_wide = false;         // as int64_t (else int32_t: the copy has fewer than 2^31 entries)
     // LDS staging of x (built on first use, stage.hip): per tile the page count (0: not
     // staged), the sorted page list, the list position of the tile's own first row page (-1:
     // not all own rows listed); per stored entry the tile-local column index
@@ -369,7 +369,7 @@ int block_threads(const void *kernel, int32_t bpc_hint);
 int choose_vpt(int vk, int b, int hint = 0);
 
 // Lazily built device maps (row -> slot, CSR row pointers) and the SELL copy of A^T.
-int ensure_update_maps(sell_mat *A, hipStream_t s);
+int ensure_row_pointers(sell_mat *A, hipStream_t s);
 int ensure_transpose(const sell_mat *A, hipStream_t s);
 // Page lists and tile-local column indices for the LDS-staged product (stage.hip), over stage
 // tiles of `chunks` consecutive chunks; rebuilt when a different tile size is asked for.
@@ -391,7 +391,6 @@ int launch_grad(const sell_mat *A, const GradPairs &pairs, int64_t ldg, int64_t 
 int launch_axpby(int vec_dt, int64_t n, int32_t b, int64_t ld, double alpha, const void *x, double beta, void *y,
                  hipStream_t s);
 // dst[pos[p]] = convert(src[p]) for p < n, dst of storage type vdt
-int launch_scatter_values(const double *src, const int64_t *pos, int64_t n, int vdt, void *dst, hipStream_t s);
 
 // Device and pinned host allocations of the library (alloc.cpp): hipMalloc and friends with a
 // count of live allocations and a test hook that makes the k-th next allocation fail.

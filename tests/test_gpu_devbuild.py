@@ -179,3 +179,28 @@ def test_device_transpose_equals_host_transpose(sc, shape, C, sigma, dt):
         got = once(k)
         assert all(torch.equal(u, v) for u, v in zip(got, want)), k
         assert sc.sell_debug_live_allocs() == live, k
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n,per_row,sigma", [(1, 1, 1), (256, 8, 1), (257, 8, 1), (700, 3, 1), (700, 30, 1), (700, 3, 64), (5000, 20, 4096)])
+def test_value_update_equals_fresh_build(sc, n, per_row, sigma, dt):
+    """A value update (workgroups of few and of many entries, rows in order and sorted) against a matrix
+    built from the new values: its values, its product and that of its copy of A^T, bit for bit."""
+    import torch
+
+    A = synth.random_sparse(n, n, per_row / n, 214, empty_rows=min(5, n - 1), long_row=min(n, 400) if per_row > 8 else None)
+    newv = synth.uniform(215, A.nnz, -2, 2)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    X = torch.from_numpy(synth.block_vector(n, 2, 216)).to("cuda:0", vt)
+    outs = []
+    for first in (A.val, newv):
+        M = sc.SellMatrix.from_csr(synth.CSR(n, n, A.rowptr, A.col, first), C=32, sigma=sigma, dtype=dt)
+        Y, Z = torch.empty_like(X), torch.empty_like(X)
+        if first is A.val:
+            sc.sell_spmmv_T(M, X, Z)  # makes the copy of A^T, with the old values
+            M.update_values(torch.from_numpy(newv).cuda())
+        sc.sell_spmmv(M, X, Y)
+        sc.sell_spmmv_T(M, X, Z)
+        outs.append((Y, Z, torch.from_numpy(M.export_csr()[2])))
+        M.close()
+    assert all(torch.equal(u, v) for u, v in zip(*outs))
