@@ -67,6 +67,8 @@ struct sell_batch {
     void *h_slot[kSlots] = {};  // pinned staging copies (also the record of the slot content)
     hipEvent_t ev[kSlots] = {};
     bool valid[kSlots] = {};
+    bool pending[kSlots] = {};          // the slot's upload was queued on up[slot] and not waited for
+    hipStream_t up[kSlots] = {};
     int next = 0;
     std::vector<uint8_t> stage;
     double *partials = nullptr;
@@ -96,7 +98,7 @@ namespace sellcs {
 
 void batch_free(sell_batch *B) {
     for (int i = 0; i < kSlots; ++i) {
-        if (B->ev[i]) (void)hipEventSynchronize(B->ev[i]);
+        if (B->pending[i]) (void)hipEventSynchronize(B->ev[i]);
         if (B->ev[i]) (void)hipEventDestroy(B->ev[i]);
         if (B->d_slot[i]) (void)lib_free(B->d_slot[i]);
         if (B->h_slot[i]) (void)lib_host_free(B->h_slot[i]);
@@ -129,6 +131,13 @@ BatchSeg batch_seg(const sell_batch *B) {
     sg.G = B->vgrid;
     sg.rows = B->rows;
     return sg;
+}
+
+// The stream has finished and is about to be destroyed: no event recorded on it is waited for later
+// (the runtime looks the event's stream up).
+void batch_release_stream(sell_batch *B, hipStream_t s) {
+    for (int i = 0; i < kSlots; ++i)
+        if (B->up[i] == s) B->pending[i] = false;
 }
 
 // Splits G0 workgroups over K items so that the largest work per workgroup is as small as
@@ -250,12 +259,13 @@ int place_table(sell_batch *B, const std::vector<int32_t> &blk, bool reserved, h
             slot = B->next;
             B->next = (B->next + 1) % kRing;
         }
-        if (B->valid[slot]) HIPCHK(hipEventSynchronize(B->ev[slot]));  // its last upload has been read
-        B->valid[slot] = false;
+        if (B->pending[slot]) HIPCHK(hipEventSynchronize(B->ev[slot]));  // its last upload has been read
+        B->pending[slot] = B->valid[slot] = false;
         std::memcpy(B->h_slot[slot], B->stage.data(), B->table_bytes);
         HIPCHK(hipMemcpyAsync(B->d_slot[slot], B->h_slot[slot], B->table_bytes, hipMemcpyHostToDevice, s));
         HIPCHK(hipEventRecord(B->ev[slot], s));
-        B->valid[slot] = true;
+        B->valid[slot] = B->pending[slot] = true;
+        B->up[slot] = s;
     }
     *d_tab = static_cast<const ProdArgs *>(B->d_slot[slot]);
     *d_blk = reinterpret_cast<const int32_t *>(static_cast<const char *>(B->d_slot[slot]) + sizeof(ProdArgs) * size_t(K));

@@ -45,6 +45,7 @@ const sell_mat *batch_matrix(const sell_batch *B, int m);
 int32_t batch_count(const sell_batch *B);
 int64_t batch_rows(const sell_batch *B);
 int batch_vdt(const sell_batch *B);
+void batch_release_stream(sell_batch *B, hipStream_t s);
 BatchSeg batch_seg(const sell_batch *B);
 bool batch_ragged(const sell_batch *B, int b);
 }  // namespace sellcs
@@ -76,9 +77,12 @@ struct DevBuffers {
 struct OwnedStream {
     hipStream_t s = nullptr;
     bool owned = false;
+    sell_batch *used[2] = {};
     ~OwnedStream() {
         if (owned) {
             (void)hipStreamSynchronize(s);
+            for (sell_batch *B : used)
+                if (B) batch_release_stream(B, s);
             drop_workspace(s);
             (void)hipStreamDestroy(s);
         }
@@ -171,6 +175,8 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
     if (!os.s) {
         HIPCHK(hipStreamCreate(&os.s));
         os.owned = true;
+        os.used[0] = A64;
+        os.used[1] = Alo;
     }
     hipStream_t s = os.s;
 
@@ -381,6 +387,7 @@ int sell_batch_cg(sell_batch *A64, sell_batch *Alo, const sell_bv *Bv, sell_bv *
         const int64_t run = std::min<int64_t>(kCheckEvery, maxit - it);
         if (use_graph && run == kCheckEvery && stable >= 2) {
             if (!graph.ge) {
+                HIPCHK(hipStreamSynchronize(s));  // nothing of an update is in flight while it records
                 HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
                 const int r = run_iterations(run);
                 hipGraph_t g = nullptr;
