@@ -269,6 +269,7 @@ int build_host_sell(HostSell &h, int64_t nrows, int64_t ncols, const int64_t *ro
     h.batch = choose_batch_len(h.cl);
     h.batch_wide = choose_batch_len(h.cl, true);
     h.waves = choose_waves(h.cl);
+    h.ulen = uniform_chunk_len(h.cl);
     return SELL_OK;
 }
 

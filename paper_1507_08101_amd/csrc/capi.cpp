@@ -195,6 +195,7 @@ void base_args(ProdArgs &a, const sell_mat *A) {
     a.st_ntiles = A->stage_ntiles;
     a.st_chunks = A->stage_chunks;
     a.nch = A->h.nch;
+    a.ulen = A->h.ulen;
     a.st_np = A->d_stage_np;
     a.st_pages = A->d_stage_pages;
     a.st_own = A->d_stage_own;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <memory>
@@ -62,6 +63,7 @@ struct HostSell {
     std::vector<int64_t> rowptr;  // CSR row pointers of the input (for export and updates)
     int32_t batch = 8;            // index batch length suited to the chunk lengths (5, 7 or 8)
     int32_t batch_wide = 7;       // the same for the kernels gathering 32 bytes per lane (5 or 7)
+    int32_t ulen = 0;             // the length of every chunk when they are all the same (not 0), else 0
     int32_t waves = 1;            // default product grid in waves of resident workgroups (1 or 16)
 };
 
@@ -75,6 +77,11 @@ void make_tiles(const std::vector<int32_t> &cl, int32_t C, int32_t ntiles,
 // for the kernels whose lane gathers 32 bytes per entry, where 8-entry batches leave room for
 // two waves per SIMD instead of three: 5 or 7 only.
 int32_t choose_batch_len(const std::vector<int32_t> &cl, bool wide = false);
+// The length of every chunk when they are all the same, else 0.
+inline int32_t uniform_chunk_len(const std::vector<int32_t> &cl) {
+    const bool same = !cl.empty() && std::equal(cl.begin() + 1, cl.end(), cl.begin());
+    return same ? cl[0] : 0;
+}
 // Default product grid in waves of resident workgroups from the spread of the chunk lengths.
 int32_t choose_waves(const std::vector<int32_t> &cl);
 
@@ -170,6 +177,7 @@ struct ProdArgs {
     int32_t threads;       // threads per workgroup (kBlock, or half of it: block_threads)
     int32_t cshift;        // log2(C) when C is a power of two, else -1
     int32_t keep;          // cache policy of the matrix and of y and z (keep_in_cache)
+    int32_t ulen;          // the length of every chunk when they are all the same, else 0
     int32_t xcd_map;       // 1: give each XCD one contiguous range of tiles
     int32_t vpt_hint;      // columns per lane requested for the matrix (0: default)
     int32_t bpc_hint;      // workgroups per compute unit requested (0: occupancy limit)

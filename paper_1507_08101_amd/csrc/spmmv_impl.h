@@ -191,7 +191,7 @@ constexpr int kBatchDefault = 8;
 // The product over the tiles of workgroup `tile` (one of a.nblocks) of one matrix.
 // FL != 0: the augmentation flags are known at compile time (a.flags == FL), so the unused
 // parts of the epilogue take no registers.
-template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false>
+template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false, bool UNI = false>
 __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, const int vl) {
     using V = typename KTypes<VK>::V;
     using X = typename KTypes<VK>::X;
@@ -213,6 +213,7 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     const SELL_GLOBAL int64_t *__restrict__ csp = to_global(a.cs);
     const SELL_GLOBAL int32_t *__restrict__ tiles = to_global(a.tiles);
     const int64_t nrows = a.nrows;
+    const int ulen = UNI ? a.ulen : 0;
     // STG: the work units are the stage tiles (a.st_ntiles of a.st_chunks chunks), taken one at
     // a time: the contiguous range of units [t0, t1) of this workgroup, or with a unit stride S
     // the units Y + S k, k in [k0, k1), of column Y = tile % S one after another (on a matrix
@@ -331,6 +332,15 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     auto load_meta = [&](int64_t ss, int64_t se_, int &clv, int64_t &csv, int &pv) {
         const int64_t sc = ss < se_ ? ss : se_ - 1;
         const int64_t c = cshift >= 0 ? (sc >> cshift) : int64_t(uint32_t(sc) / uint32_t(C));
+        if constexpr (UNI) {
+            clv = ulen;
+            csv = c * C * ulen;
+            if (perm) pv = perm[sc];
+            // per lane, as if loaded: with a length that the compiler knows to be uniform the batches of the
+            // FP64 kernels came out slower (KPM product 128.4 us with loads, 127.3 uniform, 126.7 so)
+            if constexpr (VK == VK_F64F64) asm("" : "+v"(clv), "+v"(csv));
+            return;
+        }
         const SELL_GLOBAL int32_t *pp = perm ? perm + sc : clp + c;
         clv = clp[c];
         csv = csp[c];
@@ -486,9 +496,15 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     };
 
     if constexpr (!STG) {
-        const int64_t t0 = int64_t(tile) * a.ntiles / a.nblocks, t1 = int64_t(tile + 1) * a.ntiles / a.nblocks;
-        s_begin = int64_t(tiles[t0]) * C;
-        s_end = int64_t(tiles[t1]) * C;
+        if constexpr (UNI) {
+            const uint32_t n = uint32_t(a.nch), g = uint32_t(a.nblocks), q = n / g, r = n - q * g, t = uint32_t(tile);
+            s_begin = int64_t(t * q + min(t, r)) * C;
+            s_end = s_begin + int64_t(q + (t < r ? 1 : 0)) * C;
+        } else {
+            const int64_t t0 = int64_t(tile) * a.ntiles / a.nblocks, t1 = int64_t(tile + 1) * a.ntiles / a.nblocks;
+            s_begin = int64_t(tiles[t0]) * C;
+            s_end = int64_t(tiles[t1]) * C;
+        }
         int64_t s = s_begin + rslot;
         int cl_n = 0, pv_n = 0;
         int64_t cs_n = 0;
@@ -644,10 +660,10 @@ __device__ __forceinline__ void prod_body(const ProdArgs &a, const int tile, con
     }
 }
 
-template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false>
+template <int VK, int B, int VPT, bool AUG, int UB = 0, bool STG = false, uint32_t FL = 0, bool KEEP = false, bool UNI = false>
 __global__ void __launch_bounds__(kBlock) prod_kernel(ProdArgs a, int vl) {
     const int tile = a.xcd_map ? xcd_block(blockIdx.x, gridDim.x) : int(blockIdx.x);  // index in the partials
-    prod_body<VK, B, VPT, AUG, UB, STG, FL, KEEP>(a, tile, vl);
+    prod_body<VK, B, VPT, AUG, UB, STG, FL, KEEP, UNI>(a, tile, vl);
 }
 
 // The flags of a step of the Chebyshev / KPM recurrence (y = alpha (A x - c x) - y with
@@ -788,8 +804,21 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
         if (keep) k = prod_kernel<VK, B, VPT, AUG, UB, false, 0, true>;
         if constexpr (AUG) {
             constexpr uint32_t FL = VK == VK_F64F64 ? kKpmFlags : kCgFlags;
-            if (!a.stage && a.flags == FL)
-                k = keep ? prod_kernel<VK, B, VPT, AUG, UB, false, FL, true> : prod_kernel<VK, B, VPT, AUG, UB, false, FL>;
+            const bool fl = !a.stage && a.flags == FL;
+            if (fl) k = keep ? prod_kernel<VK, B, VPT, AUG, UB, false, FL, true> : prod_kernel<VK, B, VPT, AUG, UB, false, FL>;
+            // Chunks of one length (periodic stencils): tile bounds, lengths and starts are computed, two
+            // loads less in the chain that starts a workgroup and three per pass (64^3 Anderson matrix,
+            // degree-100 Chebyshev step 1,870 -> 1,780 us; 128^3, b = 8, 20 KPM steps 2,606 -> 2,552). A
+            // branch at run time instead made the other matrices' loads wait at its end (irregular 4 M rows
+            // 1,063 -> 1,153 us), so these are kernels of their own, for the default columns per lane.
+            constexpr bool kUni = VPT == (B < 0 || B > 4 ? 4 : B);
+            if constexpr (kUni) {
+                if (a.ulen > 0 && !a.stage)
+                    k = fl ? (keep ? prod_kernel<VK, B, VPT, AUG, UB, false, FL, true, true>
+                                   : prod_kernel<VK, B, VPT, AUG, UB, false, FL, false, true>)
+                           : (keep ? prod_kernel<VK, B, VPT, AUG, UB, false, 0, true, true>
+                                   : prod_kernel<VK, B, VPT, AUG, UB, false, 0, false, true>);
+            }
         }
     }
     if (a.stage) {

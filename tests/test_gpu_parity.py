@@ -626,3 +626,31 @@ def test_cache_policies_equal_general_kernel(sc, dt, n, widths):
         assert torch.equal(p[:N], pc) and torch.equal(p, pb)
     for o in (B, M, S):
         o.close()
+
+
+@pytest.mark.parametrize("C,sigma", [(32, 1), (32, 64), (12, 1), (1, 1)])
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+def test_chunks_of_one_length_equal_general_kernel(sc, dt, C, sigma):
+    """Augmented products of matrices whose chunks all have one length (bounds computed) against the
+    general kernel over column-major operands: y and z bit for bit, dots within a fixed-order sum's error."""
+    import torch
+
+    vt = torch.float64 if dt == "f64" else torch.float32
+    for A in (synth.anderson3d(3), synth.anderson3d(7), synth.anderson3d(33)):
+        n = A.nrows
+        M = sc.SellMatrix.from_csr(A, C=C, sigma=sigma, dtype=dt)
+        for b in (1, 2, 3, 8, 16, 33):
+            x, y0, z0 = (torch.from_numpy(synth.block_vector(n, b, s)).to("cuda:0", vt) for s in (203, 204, 205))
+            for flags in (sc.SHIFT | sc.SCALE | sc.AXPBY | sc.DOT_YY | sc.DOT_XY, sc.DOT_YY | sc.DOT_XY,
+                          sc.SHIFT | sc.AXPBY | sc.DOTS | sc.CHAIN):
+                kw = dict(flags=flags, alpha=0.5, beta=-1.0, gamma=0.3, delta=1.0, eta=0.5)
+                y, z = y0.clone(), z0.clone()
+                g = [torch.empty((b, n), dtype=vt, device="cuda:0").t().copy_(v) for v in (x, y0, z0)]
+                d, dg = (torch.zeros(3 * b, dtype=torch.float64, device="cuda:0") for _ in range(2))
+                sc.sell_spmmv_aug(M, x, y, z, dot=d, **kw)
+                sc.sell_spmmv_aug(M, *g, dot=dg, **kw)
+                assert torch.equal(y, g[1]) and torch.equal(z, g[2])
+                xd, yd = x.double(), y.double()
+                mag = torch.cat([(yd * yd).sum(0), (xd * yd).abs().sum(0), (xd * xd).sum(0)])
+                assert bool(((d - dg).abs() <= 2 * (n + 8) * 2.0 ** -53 * mag).all())
+        M.close()
