@@ -32,8 +32,9 @@
  *       SELLCS_BLOCKS_PER_CU=n     workgroups per compute unit of a resident grid (1..64;
  *                                  default from the kernel's occupancy)
  *       SELLCS_TILES=n             fine tiles of a matrix built afterwards (1..4096; default 4096)
- *       SELLCS_BATCH_WAVES=n       grid of a batched product in waves of resident workgroups
- *                                  (1..32; default 16)
+ *       SELLCS_BATCH_WAVES=n       largest grid of a batched product in waves of resident
+ *                                  workgroups (1..32; default 16; fewer where a workgroup
+ *                                  would have less than three passes of rows)
  *       SELLCS_XCD_MAP=0           plain workgroup-to-tile order instead of contiguous tile
  *                                  ranges per XCD
  *     The per-matrix setters (sell_set_launch, sell_set_waves, sell_set_batch, sell_set_slice)
@@ -429,7 +430,8 @@ int sell_set_launch(sell_mat *A, int32_t vpt, int32_t blocks_per_cu);
  * (coefficient of variation above 1/2), else one. Several waves let workgroups that finish early
  * take the next ones, which balances matrices whose tiles differ in speed (scattered gathers),
  * and keep the workgroups that run at the same time on neighbouring rows; the grid never
- * exceeds the matrix's fine tiles (at most 4096). Results per row are the same; dots may differ
+ * exceeds the matrix's fine tiles (at most 4096) nor leaves a workgroup without a pass of rows
+ * (two with dots). Results per row are the same; dots may differ
  * in the last bits. */
 int sell_set_waves(sell_mat *A, int32_t waves);
 
@@ -440,9 +442,9 @@ int sell_set_waves(sell_mat *A, int32_t waves);
  * Results per row are the same; dots may differ in the last bits. */
 int sell_set_slice(sell_mat *A, int32_t slice);
 
-/* Index batch length of the products of widths 1, 2, 4, 8, 16 and 32. A batched launch
+/* Index batch length of the products over row-major blocks. A batched launch
  * (sell_batch_spmmv_aug, sell_batch_cg) uses the length its matrices share, and 8 when they
- * differ (the length is taken when the batch is created); the run-time-width kernel, the
+ * differ (the length is taken when the batch is created); products over other strides, the
  * packed mixed-width launch and the atomic transposed product keep 8. A lane loads
  * the column indices and values of `batch` consecutive entries of its row, then all their x
  * rows, then sums them; a chunk of L entries (Sec. 5.1: all rows of a chunk are padded to the

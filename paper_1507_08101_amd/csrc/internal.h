@@ -376,7 +376,7 @@ int block_threads(const void *kernel, int32_t bpc_hint);
 // given, else 4 for b >= 4 and b otherwise.
 int choose_vpt(int vk, int b, int hint = 0);
 
-// Lazily built device maps (row -> slot, CSR row pointers) and the SELL copy of A^T.
+// Lazily built CSR row pointers on the device and the SELL copy of A^T.
 int ensure_row_pointers(sell_mat *A, hipStream_t s);
 int ensure_transpose(const sell_mat *A, hipStream_t s);
 // Page lists and tile-local column indices for the LDS-staged product (stage.hip), over stage
@@ -387,7 +387,7 @@ int ensure_stage(const sell_mat *A, int32_t chunks, hipStream_t s);
 int ensure_stage_plan(const sell_mat *A, int32_t nblk, int32_t stride, int32_t ns, hipStream_t s);
 
 // Value gradients (grad.hip): dval (+)= sum over the pairs of c_p times the pattern-restricted
-// outer product of G_p and X_p, in CSR order (needs the update maps).
+// outer product of G_p and X_p, in CSR order (needs the row pointers).
 constexpr int kGradPairs = 16;
 struct GradPairs {
     const void *g[kGradPairs], *x[kGradPairs];
