@@ -33,8 +33,8 @@
  *                                  default from the kernel's occupancy)
  *       SELLCS_TILES=n             fine tiles of a matrix built afterwards (1..4096; default 4096)
  *       SELLCS_BATCH_WAVES=n       largest grid of a batched product in waves of resident
- *                                  workgroups (1..32; default 16; fewer where a workgroup
- *                                  would have less than three passes of rows)
+ *                                  workgroups (1..32; default 16; down to one where a workgroup
+ *                                  would have less than three passes of rows of 8 entries)
  *       SELLCS_XCD_MAP=0           plain workgroup-to-tile order instead of contiguous tile
  *                                  ranges per XCD
  *     The per-matrix setters (sell_set_launch, sell_set_waves, sell_set_batch, sell_set_slice)

@@ -198,30 +198,53 @@ void apportion_products(const sell_batch *B, int32_t G0, const int32_t *host_act
 
 namespace {
 
-// The launch shape of a product with kernel kern over matrices of `passes` passes of kBlock
-// threads in all: 16 waves of the resident grid by default, but no workgroup with fewer than three
-// passes on average. A finer split than one wave balances uneven matrices better, since workgroups
-// that finish early take the next ones (64 Laplacians of edges 20..100 at b = 8: 1.42 ms with 16
-// waves, 1.68 ms with 2, 1.83 ms with 1; mixed widths 1..32: 2.85 ms against 4.06 ms with 2), until
-// a workgroup's start and end outweigh its rows: 16 Laplacians of edges 20..48, FP64 with two dots,
-// b = 1 58 us in 16 waves, 20 with three passes each (1: 22, 6: 22); b = 4 41 and 31.
-// Few passes each also make workgroups of half the size the better ones where only one of kBlock
+// The launch shape of a product with kernel kern over the matrices of a launch; rows_per_pass(m, t):
+// rows of matrix m that a workgroup of t threads has in work at once. Workgroups: batch_workgroups,
+// of 16 waves of the resident grid at most: a finer split than one wave balances uneven matrices
+// better, since workgroups that finish early take the next ones (64 Laplacians of edges 20..100 at
+// b = 8: 1.42 ms with 16 waves, 1.68 ms with 2, 1.83 ms with 1; mixed widths 1..32: 2.85 ms against
+// 4.06 ms with 2).
+// Few passes each make workgroups of half the size the better ones where only one of kBlock
 // threads fits a compute unit (64 Laplacians of edges 20..40, b = 8 with dots, 1.8 passes: 152 us
 // with 512 threads, 110 with 256; edges 20..100, 21 passes: 1,183 with 512, 1,199 with 256).
 struct BatchShape {
     int32_t G0;
     int threads;
 };
-BatchShape product_shape(const sell_batch *B, const void *kern, const std::function<int64_t(int)> &passes) {
+BatchShape product_shape(const sell_batch *B, const void *kern, const int32_t *host_active,
+                         const std::function<int32_t(int, int)> &rows_per_pass) {
     static const int32_t waves = [] {
         const char *e = std::getenv("SELLCS_BATCH_WAVES");
         const int v = e ? std::atoi(e) : 16;
         return int32_t(v >= 1 && v <= 32 ? v : 16);
     }();
     const int64_t one = resident_grid(kern, kBlock, int32_t(std::min<int64_t>(B->total_tiles, 1 << 30)), B->bpc_hint);
+    int64_t tiles = 0, passes = 0;
+    double work = 0.0;  // passes of one index batch per row
+    auto count = [&](int threads) {
+        tiles = passes = 0;
+        work = 0.0;
+        for (int m = 0; m < B->K; ++m) {
+            const HostSell &h = B->mats[size_t(m)]->h;
+            if ((host_active && !host_active[m]) || h.nrows == 0) continue;
+            const int32_t rows = rows_per_pass(m, threads);
+            const int64_t p = (h.nrows + rows - 1) / rows;
+            tiles += B->mats[size_t(m)]->ntiles;
+            passes += p;
+            work += double(p) * index_batches(h.stored, h.nrows);
+        }
+    };
     BatchShape sh;
-    sh.threads = passes(kBlock) < 8 * waves * one ? block_threads(kern, B->bpc_hint) : kBlock;
-    sh.G0 = int32_t(std::min<int64_t>(waves * one, std::max<int64_t>(1, passes(sh.threads) / 3)));
+    sh.threads = kBlock;
+    count(kBlock);
+    if (passes < 8 * waves * one) {
+        sh.threads = block_threads(kern, B->bpc_hint);
+        if (sh.threads != kBlock) count(sh.threads);
+    }
+    const int64_t resident =
+        sh.threads == kBlock ? std::min(one, tiles)
+                             : resident_grid(kern, sh.threads, int32_t(std::min<int64_t>(tiles, 1 << 30)), B->bpc_hint);
+    sh.G0 = batch_workgroups(tiles, resident, waves * one, work);
     return sh;
 }
 
@@ -341,13 +364,8 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
                                          : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags, keep != 0);
     // workgroups per matrix: waves of the resident grid split so that the busiest workgroup
     // has as little work as possible
-    const BatchShape shape = product_shape(B, kern, [&](int threads) {
-        const int32_t rows = pass_rows(b, vpt, path, threads);
-        int64_t n = 0;
-        for (int m = 0; m < K; ++m)
-            if (!host_active || host_active[m]) n += (B->mats[size_t(m)]->h.nrows + rows - 1) / rows;
-        return n;
-    });
+    const BatchShape shape =
+        product_shape(B, kern, host_active, [&](int, int threads) { return pass_rows(b, vpt, path, threads); });
     const int32_t G0 = shape.G0;
     const std::vector<int32_t> *pblk_h = nullptr;
     if (host_active) {
@@ -456,14 +474,9 @@ int batch_aug_packed_impl(sell_batch *B, const void *X, void *Y, void *Z, const 
     const void *kern = vk == VK_F64F64   ? batch_mixed_kernel_f64(aug)
                        : vk == VK_F32F32 ? batch_mixed_kernel_f32(aug)
                                          : batch_mixed_kernel_bf16(aug);
-    const BatchShape shape = product_shape(B, kern, [&](int threads) {
-        int64_t n = 0;
-        for (int m = 0; m < K; ++m) {
-            const int w = B->widths[size_t(m)];
-            const int32_t rows = pass_rows(w, w >= 4 ? 4 : w, fixed_width(w) ? kPathFixed : kPathAny, threads);
-            n += (B->mats[size_t(m)]->h.nrows + rows - 1) / rows;
-        }
-        return n;
+    const BatchShape shape = product_shape(B, kern, nullptr, [&](int m, int threads) {
+        const int w = B->widths[size_t(m)];
+        return pass_rows(w, w >= 4 ? 4 : w, fixed_width(w) ? kPathFixed : kPathAny, threads);
     });
     const int32_t G0 = shape.G0;
     auto hit = B->blk_cache_w.find(G0);

@@ -238,6 +238,24 @@ inline int32_t pass_rows(int b, int vpt, int path, int threads) {
     if (path == kPathFixed) return threads / (b / vpt);
     return path == kPathContig ? threads / 64 * (64 / run_time_lanes(b, true)) : threads >> run_time_lanes(b, false);
 }
+// Index batches (8 entries) of a row on average, one after another in its lanes: at least 1.
+inline double index_batches(int64_t stored, int64_t nrows) {
+    return std::max(1.0, double(stored) / (8.0 * double(nrows)));
+}
+// Workgroups of a batched product over `tiles` fine tiles in all, `resident` the grid that the device
+// holds at once and `most` an upper bound; work: passes of rows times their index batches. At least
+// three of those per workgroup, past which its start and end are small (16 Laplacians of edges
+// 20..48, FP64 with two dots, b = 1: 16 us, 18 with two, 20 with one, 52 on 16 resident grids; b = 4 27
+// and 32), but the whole device (16 matrices of 3,000 rows of 20, b = 16: 11 us, 15 without) and, where
+// it would be more than half the tiles, one workgroup per tile: some would have two tiles all the same,
+// and the launch takes as long as they do (64 matrices of 300 rows of 100, b = 8: 533 workgroups 26
+// us, 640 17). Rows are counted by their entries because long ones keep a pass busy: 8 matrices of 2,000
+// rows of 500, b = 1 (32 passes): 46 us, 320 on the 10 workgroups that have three passes each.
+inline int32_t batch_workgroups(int64_t tiles, int64_t resident, int64_t most, double work) {
+    int64_t G = std::max(resident, int64_t(std::min(work / 3, 1e9)));
+    if (2 * G > tiles) G = tiles;
+    return int32_t(std::max<int64_t>(1, std::min(G, most)));
+}
 int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s);
 int launch_transpose_atomic(ProdArgs &a, int vk, hipStream_t s);
 int launch_fill(void *p, int dt, int64_t nrows, int32_t ncols, int64_t rs, int64_t cs,

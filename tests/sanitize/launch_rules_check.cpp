@@ -1,0 +1,44 @@
+// The rules that size launches (internal.h), which need no device: exit status 0 when every case holds.
+#include <cstdio>
+
+#include "internal.h"
+
+using namespace sellcs;
+
+static int failures = 0;
+
+static void expect(bool ok, const char *what, int64_t a, int64_t b) {
+    if (ok) return;
+    std::fprintf(stderr, "FAIL %s (%lld, %lld)\n", what, (long long)a, (long long)b);
+    ++failures;
+}
+
+// `count` matrices of n rows of len entries, chunks of 32 rows, one tile per chunk, b columns (a power
+// of two from 4 on, or 1) on 256 compute units with one or two workgroups of 512 threads each
+static void batch(int count, int64_t n, int64_t len, int b, int per_cu) {
+    const int64_t tiles = count * ((n + 31) / 32), resident = 256 * per_cu;
+    const int32_t rows = pass_rows(b, b >= 4 ? 4 : b, kPathFixed, 512);
+    const int64_t passes = count * ((n + rows - 1) / rows);
+    const int64_t G = batch_workgroups(tiles, std::min(resident, tiles), 16 * resident, double(passes) * index_batches(n * len, n));
+    expect(G >= std::min(tiles, resident), "workgroups for the device", G, std::min(tiles, resident));
+    expect(G <= std::min(tiles, 16 * resident), "workgroups at most", G, tiles);
+    // no workgroup has more than three passes of one index batch per row, or one wave or one tile of work
+    const double each = double(passes) * index_batches(n * len, n) / double(G);
+    expect(each <= 6.0 || G == tiles || G == 16 * resident, "work per workgroup", int64_t(each), G);
+    // short rows in numbers: three passes each, not one tile each
+    if (len <= 8 && passes > 3 * resident && passes < 48 * resident)
+        expect(G <= passes / 3, "passes per workgroup", G, passes);
+}
+
+int main() {
+    for (int per_cu : {1, 2})
+        for (int b : {1, 4, 8, 16, 32})
+            for (int count : {1, 3, 8, 64, 1000})
+                for (int64_t n : {1, 31, 33, 500, 2000, 20000, 1000000})
+                    for (int64_t len : {1, 7, 9, 60, 500, 2000}) batch(count, n, len, b, per_cu);
+    expect(batch_workgroups(0, 0, 4096, 0.0) == 1, "empty batch", 0, 0);
+    expect(batch_workgroups(int64_t(1) << 40, 256, int64_t(1) << 20, 1e300) == 1 << 20, "bound", 0, 0);
+    if (failures) return 1;
+    std::puts("launch rules ok");
+    return 0;
+}
