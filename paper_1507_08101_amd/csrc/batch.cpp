@@ -347,17 +347,20 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
                       "4, 8, 16, 32, or rows that are not row-major and %d-byte aligned): the run-time-width "
                       "kernel runs",
                       b, align);
-    const bool contig = b > 1 && xcs == 1 && ycs == 1 && (!chain || zcs == 1);
-    const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     const int ub = B->batch_len, ubw = B->batch_len_wide;
     const uint32_t kflags = aug ? o.flags : 0u;  // every matrix of the launch has these flags
     double mbytes = 0, vbytes = 0;  // of the launched matrices
+    int64_t rows = 0, stored = 0;
     for (int m = 0; m < K; ++m)
         if (!host_active || host_active[m]) {
             const HostSell &h = B->mats[size_t(m)]->h;
             mbytes += double(h.stored) * (4 + dtype_bytes(h.vdt));
             vbytes += double(h.ncols + h.nrows) * b * esize;
+            rows += h.nrows;
+            stored += h.stored;
         }
+    const bool contig = b > 1 && xcs == 1 && ycs == 1 && (!chain || zcs == 1) && !few_long_rows(b, rows, stored);
+    const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     const int32_t keep = keep_in_cache(mbytes, vbytes);
     const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, path, ub, ubw, kflags, keep != 0)
                        : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, path, ub, ubw, kflags, keep != 0)

@@ -331,7 +331,7 @@ int aug_impl(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const 
             }
             if (dots) a.partials = partials_out ? partials_out : ws->partials;
         }
-        int rc = launch_product(a, vec_kind(A->h.vdt), aug, s);
+        int rc = launch_product(a, vec_kind(A->h.vdt), aug, A->h.stored, s);
         if (rc) return rc;
         if (nblocks_out) *nblocks_out = a.nblocks;
         if (dots && !partials_out) {

@@ -233,6 +233,15 @@ inline int run_time_lanes(int b, bool contig) {
     while ((1 << l) < b) ++l;
     return l;
 }
+// Contiguous rows of b >= 2 columns with the kernel for them, or one column per lane as for any strides?
+// The latter is ahead only where the lanes, not the memory, are short: fewer rows than there are lanes
+// with one chunk of 32 to a compute unit, each a long chain of batches, and 8 lanes a row at most (past
+// that it needs twice the lanes' loads). 2,000 rows of 300 entries, FP64: b = 2 (unaligned) 20 us against
+// 26, b = 3 22 and 31, b = 7 24 and 27, b = 9 41 and 31; 16,000 rows, b = 3 42 and 42, b = 7 57 and 47; 2,000
+// rows of 30 8.5 (the launch) either way, of 100, b = 3 10.2 and 12.6.
+inline bool few_long_rows(int b, int64_t nrows, int64_t stored) {
+    return b < 8 && nrows <= 8192 && stored >= 64 * nrows;
+}
 // Rows that a workgroup of a product works on at once (vpt: columns per lane of a fixed width).
 inline int32_t pass_rows(int b, int vpt, int path, int threads) {
     if (path == kPathFixed) return threads / (b / vpt);
@@ -256,7 +265,8 @@ inline int32_t batch_workgroups(int64_t tiles, int64_t resident, int64_t most, d
     if (2 * G > tiles) G = tiles;
     return int32_t(std::max<int64_t>(1, std::min(G, most)));
 }
-int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s);
+// stored: entries of the matrix, padding included
+int launch_product(ProdArgs &a, int vk, bool aug, int64_t stored, hipStream_t s);
 int launch_transpose_atomic(ProdArgs &a, int vk, hipStream_t s);
 int launch_fill(void *p, int dt, int64_t nrows, int32_t ncols, int64_t rs, int64_t cs,
                 double value, hipStream_t s);

@@ -69,7 +69,7 @@ static bool vec_ok(const void *p, int64_t rs, int64_t cs, int esize, int align) 
     return cs == 1 && (reinterpret_cast<uintptr_t>(p) % align) == 0 && ((rs * esize) % align) == 0;
 }
 
-int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s) {
+int launch_product(ProdArgs &a, int vk, bool aug, int64_t stored, hipStream_t s) {
     if (a.ntiles == 0) return SELL_OK;
     const int esize = vk == VK_F64F64 ? 8 : 4;
     const int vpt = choose_vpt(vk, a.nb, a.vpt_hint);
@@ -90,7 +90,8 @@ int launch_product(ProdArgs &a, int vk, bool aug, hipStream_t s) {
                           "strided or offset views): the run-time-width kernel runs",
                           align);
     }
-    const bool contig = a.nb > 1 && a.xcs == 1 && a.ycs == 1 && (!(aug && (a.flags & SELL_SPMV_CHAIN)) || a.zcs == 1);
+    const bool contig = a.nb > 1 && a.xcs == 1 && a.ycs == 1 && (!(aug && (a.flags & SELL_SPMV_CHAIN)) || a.zcs == 1) &&
+                        !few_long_rows(a.nb, a.nrows, stored);
     const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
     switch (vk) {
         case VK_F64F64: return prod_f64(a, aug, path, s);

@@ -38,6 +38,10 @@ int main() {
                     for (int64_t len : {1, 7, 9, 60, 500, 2000}) batch(count, n, len, b, per_cu);
     expect(batch_workgroups(0, 0, 4096, 0.0) == 1, "empty batch", 0, 0);
     expect(batch_workgroups(int64_t(1) << 40, 256, int64_t(1) << 20, 1e300) == 1 << 20, "bound", 0, 0);
+    // lanes per row of narrow products: columns of their own on few long rows only
+    expect(few_long_rows(3, 2000, 2000 * 300) && few_long_rows(7, 8192, 64 * 8192), "few long rows", 0, 0);
+    expect(!few_long_rows(8, 2000, 2000 * 300) && !few_long_rows(3, 8193, 8193 * 300) && !few_long_rows(3, 2000, 2000 * 64 - 1),
+           "few long rows", 1, 0);
     if (failures) return 1;
     std::puts("launch rules ok");
     return 0;

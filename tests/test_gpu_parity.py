@@ -654,3 +654,41 @@ def test_chunks_of_one_length_equal_general_kernel(sc, dt, C, sigma):
                 mag = torch.cat([(yd * yd).sum(0), (xd * yd).abs().sum(0), (xd * xd).sum(0)])
                 assert bool(((d - dg).abs() <= 2 * (n + 8) * 2.0 ** -53 * mag).all())
         M.close()
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n,length", [(1, 300), (33, 64), (200, 63), (200, 70), (8192, 66), (8193, 66)])
+def test_narrow_products_of_few_long_rows(sc, orc, dt, n, length):
+    """Matrices either side of the line between the narrow kernels (rows of 64 entries, 8,192 rows) at
+    widths without a compiled kernel and at unaligned ones, single and in a batch: on integer data y bit
+    for bit the oracle's, the dots exact, nothing written beside the block."""
+    import torch
+
+    m = 400
+    col = np.sort(synth.randint(220, n * length, 0, m - 1).reshape(n, length), axis=1).astype(np.int32).reshape(-1)
+    A = synth.CSR(n, m, np.arange(n + 1, dtype=np.int64) * length, col, synth.randint(221, n * length, -2, 2).astype(np.float64))
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1, dtype=dt)
+    B = sc.SellBatch([M, M])
+    vt = torch.float64 if dt == "f64" else torch.float32
+    for b in (2, 3, 5, 7, 9):
+        x = synth.int_block_vector(m, b, 222, -3, 3)
+        want = orc.spmmv(A, x)
+        buf = torch.full((m + n + 2, b + 1), 9.0, dtype=vt, device="cuda:0")
+        X, Y = buf[:m, 1:], buf[m:m + n, 1:]
+        X.copy_(torch.from_numpy(x))
+        sc.sell_spmmv(M, X, Y)
+        assert np.array_equal(Y.double().cpu().numpy(), want)
+        Y.fill_(0.0)
+        d = torch.zeros(3 * b, dtype=torch.float64, device="cuda:0")
+        sc.sell_spmmv_aug(M, X, Y, flags=sc.DOT_YY, dot=d)
+        assert np.array_equal(Y.double().cpu().numpy(), want)
+        assert np.array_equal(d[:b].cpu().numpy(), (want * want).sum(0))
+        assert bool((buf[:, 0] == 9.0).all()) and bool((buf[m + n:] == 9.0).all())
+        Xb = torch.from_numpy(np.concatenate([x, x])).to("cuda:0", vt)
+        Yb = torch.empty((2 * n, b), dtype=vt, device="cuda:0")
+        db = torch.zeros(6 * b, dtype=torch.float64, device="cuda:0")
+        sc.sell_batch_spmmv_aug(B, Xb, Yb, flags=sc.DOT_YY, dot=db)
+        assert np.array_equal(Yb.double().cpu().numpy(), np.concatenate([want, want]))
+        assert np.array_equal(db.view(2, 3, b)[:, 0].cpu().numpy(), np.stack([(want * want).sum(0)] * 2))
+    B.close()
+    M.close()
