@@ -361,7 +361,7 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
         }
     const bool contig = b > 1 && xcs == 1 && ycs == 1 && (!chain || zcs == 1) && !few_long_rows(b, rows, stored);
     const int path = fixed_ok ? kPathFixed : contig ? kPathContig : kPathAny;
-    const int32_t keep = keep_in_cache(mbytes, vbytes);
+    const int32_t keep = keep_in_cache(mbytes, vbytes, b, esize);
     const void *kern = vk == VK_F64F64   ? batch_kernel_f64(b, vpt, aug, path, ub, ubw, kflags, keep != 0)
                        : vk == VK_F32F32 ? batch_kernel_f32(b, vpt, aug, path, ub, ubw, kflags, keep != 0)
                                          : batch_kernel_bf16(b, vpt, aug, path, ub, ubw, kflags, keep != 0);

@@ -306,7 +306,7 @@ int aug_impl(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, const 
         if (Yin) a.yi_off = elem_ptr(Yin, 0, sl.first) - static_cast<char *>(a.Y);
         a.scratch = ws->scratch;
         a.keep = keep_in_cache(double(A->h.stored) * (4 + dtype_bytes(A->h.vdt)),
-                               double(A->h.ncols + A->h.nrows) * a.nb * dtype_bytes(X->dt));
+                               double(A->h.ncols + A->h.nrows) * a.nb * dtype_bytes(X->dt), a.nb, dtype_bytes(X->dt));
         a.stage = staged ? 1 : 0;
         if (staged) {
             a.tile_stride = st_stride;

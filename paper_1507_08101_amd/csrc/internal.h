@@ -377,20 +377,25 @@ int check_aug_call(const sell_mat *A, const sell_bv *X, sell_bv *Y, sell_bv *Z, 
 // kernel times the compute units), at most the number of fine tiles.
 // blocks_per_cu > 0 lowers the workgroups per compute unit to at most that many.
 int32_t resident_grid(const void *kernel, int threads, int32_t ntiles, int32_t blocks_per_cu = 0);
-// Cache policy of a launch that reads matrix_bytes of entries and vector_bytes of x and y: 0 streams
-// the entries past the caches (nontemporal), 1 reads them with ordinary loads, 2 also stores y and z
-// ordinarily. What the 256 MB infinity cache holds of a matrix until its next product comes from
-// there; a matrix that it cannot hold only evicts x. Plain products of periodic 7-point matrices in
-// turn, nontemporal against ordinary loads: 84 MB of entries, b = 8 51.9 and 44.7 us; 118 MB, b = 8
-// 75.1 and 66.8; 176 MB, b = 1 39.5 and 31.4, b = 4 62.4 and 50.2, b = 8 (444 MB in all) 101.5 and
-// 111.4; 88 MB (BF16), b = 16 99.1 and 63.7; irregular matrix, 250 MB, b = 1 203 and 181, 500 MB, b = 8
-// 573 and 585. Ordinary stores help where the next kernel of a solver reads y and all of it fits: the
+// Cache policy of a launch that reads matrix_bytes of entries and vector_bytes of x and y (b columns of
+// esize bytes): 0 streams the entries past the caches (nontemporal), 1 reads them with ordinary loads, 2
+// also stores y and z ordinarily. What the 256 MB infinity cache holds of a matrix until its next product
+// comes from there; a matrix that it cannot hold only evicts x. Plain products in turn, nontemporal against
+// ordinary loads, FP64, 7-point matrices: 84 MB of entries, b = 8 52.8 and 47.0 us, b = 16 (340 MB in all) 101
+// and 86, b = 32 (596 MB) 205 and 217; 112 MB, b = 8 72 and 65, b = 16 (453 MB) 137 and 135; 127 MB, b = 8 (322
+// MB) 83 and 74, b = 16 (516 MB) 153 and 173; 61 MB, b = 32 (434 MB) 147 and 129; 176 MB, b = 1 39.5 and 31.4,
+// b = 4 62.4 and 50.2, b = 8 (444 MB) 102 and 111; irregular, 250 MB, b = 1 203 and 181. FP32 vectors leave more
+// of the cache to the matrix: 117 MB, b = 16 (385 MB) 101 and 68, b = 32 (654 MB) 207 and 205; past 32
+// columns the slices' other kernel gains whatever the vectors hold (84 MB, b = 48 370 and 352).
+// Ordinary stores help where the next kernel of a solver reads y and all of it fits: the
 // degree-100 Chebyshev step (30 MB) 1,994 and 1,886 us, batched CG of 94 MB 16.9 and 15.9 ms; past
 // that they cost (148 MB: none to 4 %, 298 MB: 15 %).
-inline int32_t keep_in_cache(double matrix_bytes, double vector_bytes) {
+inline int32_t keep_in_cache(double matrix_bytes, double vector_bytes, int b, int esize) {
     constexpr double MB = 1e6;
     const double all = matrix_bytes + vector_bytes;
-    return all <= 96 * MB ? 2 : matrix_bytes <= 128 * MB || all <= 320 * MB ? 1 : 0;
+    if (all <= 96 * MB) return 2;
+    if (matrix_bytes > 128 * MB) return all <= 320 * MB ? 1 : 0;
+    return esize == 4 || b > 32 || matrix_bytes <= 64 * MB || all <= 345 * MB ? 1 : 0;
 }
 // Threads per workgroup of a product grid of several waves of workgroups: kBlock, or half of it for
 // a kernel whose registers let only one workgroup of kBlock threads onto a compute unit. Nothing

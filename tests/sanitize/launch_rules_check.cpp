@@ -42,6 +42,13 @@ int main() {
     expect(few_long_rows(3, 2000, 2000 * 300) && few_long_rows(7, 8192, 64 * 8192), "few long rows", 0, 0);
     expect(!few_long_rows(8, 2000, 2000 * 300) && !few_long_rows(3, 8193, 8193 * 300) && !few_long_rows(3, 2000, 2000 * 64 - 1),
            "few long rows", 1, 0);
+    // cache policy: (matrix MB, vectors MB, columns, bytes of a vector element) either side of its lines
+    const struct { double matrix, vectors; int b, esize, keep; } policy[] = {
+        {90, 5, 8, 8, 2}, {90, 7, 8, 8, 1}, {84, 256, 16, 8, 1}, {84, 512, 32, 8, 0}, {127, 195, 8, 8, 1}, {127, 389, 16, 8, 0},
+        {61, 373, 32, 8, 1}, {65, 373, 32, 8, 0}, {117, 268, 16, 4, 1}, {129, 268, 16, 4, 0}, {84, 768, 48, 8, 1},
+        {176, 140, 4, 8, 1}, {176, 150, 4, 8, 0}};
+    for (const auto &p : policy)
+        expect(keep_in_cache(p.matrix * 1e6, p.vectors * 1e6, p.b, p.esize) == p.keep, "cache policy", int64_t(p.matrix), p.b);
     if (failures) return 1;
     std::puts("launch rules ok");
     return 0;
