@@ -422,6 +422,13 @@ int ensure_stage_plan(const sell_mat *A, int32_t nblk, int32_t stride, int32_t n
 // Value gradients (grad.hip): dval (+)= sum over the pairs of c_p times the pattern-restricted
 // outer product of G_p and X_p, in CSR order (needs the row pointers).
 constexpr int kGradPairs = 16;
+// Workgroups of 256 threads over nrows rows, 256 >> ll of them at a time: one pass each up to a cap far
+// past any that the device holds, and far below the 2^32 threads at which a launch is refused (2^28 rows
+// of more than 32 columns). The workgroups stride over the rows beyond it.
+inline unsigned grad_grid(int64_t nrows, int ll) {
+    const int64_t per = 256 >> ll;
+    return unsigned(std::min<int64_t>((nrows + per - 1) / per, int64_t(1) << 18));
+}
 struct GradPairs {
     const void *g[kGradPairs], *x[kGradPairs];
     double c[kGradPairs];

@@ -49,6 +49,14 @@ int main() {
         {176, 140, 4, 8, 1}, {176, 150, 4, 8, 0}};
     for (const auto &p : policy)
         expect(keep_in_cache(p.matrix * 1e6, p.vectors * 1e6, p.b, p.esize) == p.keep, "cache policy", int64_t(p.matrix), p.b);
+    // the gradient's grid: a launch of fewer than 2^32 threads at any number of rows, all of them in one
+    // pass where they are few
+    for (int ll = 0; ll <= 4; ++ll)
+        for (int64_t n = 1; n <= int64_t(1) << 31; n = 2 * n + 1) {
+            const int64_t g = grad_grid(n, ll), per = 256 >> ll;
+            expect(g >= 1 && g * 256 < (int64_t(1) << 32), "gradient threads", g, n);
+            expect(n > per << 18 || (g * per >= n && (g - 1) * per < n), "gradient workgroups", g, n);
+        }
     if (failures) return 1;
     std::puts("launch rules ok");
     return 0;

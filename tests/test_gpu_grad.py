@@ -287,3 +287,23 @@ def test_chebyshev_degree100_anderson64(sc, dt):
             fd = float(np.sum((ys[0] - ys[1]) * (ys[0] + ys[1]))) / (2 * h)
             assert abs(fd - g[p]) <= 1e-6 * max(abs(fd), 1e-3 * np.abs(g).max()), p
     M.close()
+
+
+@pytest.mark.parametrize("n,b", [(262144 * 16 + 5, 33), (262144 * 16 * 2 + 17, 40)])
+def test_grad_values_past_one_pass_of_workgroups(sc, n, b):
+    """More rows than the gradient kernel's largest grid takes at once (16 a workgroup from 33 columns
+    on): one entry a row, each G[i] . X[col i], and exactly nothing beside the gradient."""
+    import torch
+
+    gen = torch.Generator("cuda:0").manual_seed(223)
+    rp = torch.arange(n + 1, dtype=torch.int64, device="cuda:0")
+    col = torch.randint(0, 5000, (n,), dtype=torch.int32, device="cuda:0", generator=gen)
+    M = sc.SellMatrix.from_device_csr(n, 5000, rp, col, torch.ones(n, dtype=torch.float64, device="cuda:0"), C=32, sigma=1,
+                                      dtype="f32")
+    G = torch.randint(-8, 9, (n, b), dtype=torch.int32, device="cuda:0", generator=gen).float()
+    X = torch.randint(-8, 9, (5000, b), dtype=torch.int32, device="cuda:0", generator=gen).float()
+    out = torch.full((n + 2,), 5.0, dtype=torch.float64, device="cuda:0")
+    sc.sell_grad_values(M, G, X, out[1:n + 1])
+    assert torch.equal(out[1:n + 1], (G * X[col.long()]).sum(1).double())
+    assert float(out[0]) == 5.0 and float(out[n + 1]) == 5.0
+    M.close()
