@@ -115,7 +115,8 @@ int sell_grad_values(const sell_mat *A, const sell_bv *G, const sell_bv *X, doub
     p.n = 1;
     p.g[0] = G->ptr;
     p.x[0] = X->ptr;
-    p.c[0] = alpha;
+    p.c[0] = 1.0;
+    p.scale = alpha;
     return launch_grad(A, p, G->ld, X->ld, G->dt, b, accumulate ? 1 : 0, dval, s);
 }
 
@@ -248,6 +249,7 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
     const char *ck = static_cast<const char *>(ckpt);
     GradPairs pairs;
     pairs.n = 0;
+    pairs.scale = (N > 1 ? 2.0 : 1.0) / scale;
     int written = 0;
     auto flush = [&]() -> int {
         if (pairs.n == 0) return SELL_OK;
@@ -273,7 +275,7 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
             const sell_bv w1 = m + 1 == N ? *G : w(m + 1), w2 = m + 2 == N ? *G : w(m + 2);
             pairs.g[pairs.n] = w1.ptr;
             pairs.x[pairs.n] = v(m).ptr;
-            pairs.c[pairs.n++] = (m > 0 ? 2.0 : 1.0) / scale;
+            pairs.c[pairs.n++] = m > 0 || N == 1 ? 1.0 : 0.5;
             if ((pairs.n == group || m == lo) && (rc = flush())) return rc;
             sell_bv out = m == 0 && !overlap(G->ptr, dX->ptr, vb) ? *dX : w(m);
             if ((rc = shifted_product(AT, w1, out, (m > 0 ? 2.0 : 1.0) / scale, c, m + 2 <= N ? &w2 : nullptr, s)))

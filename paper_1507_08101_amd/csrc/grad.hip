@@ -9,7 +9,7 @@
 
 namespace sellcs {
 
-// dval[rowptr[row] + k] (+)= sum_p c_p sum_j G_p[row, j] X_p[col(row, k), j] for every stored entry k
+// dval[rowptr[row] + k] (+)= scale sum_p c_p sum_j G_p[row, j] X_p[col(row, k), j] for every stored entry k
 // of every row, over the pairs (G_p, X_p) of the launch, written straight to the CSR order.
 //
 // L = 2^LL lanes serve one row slot, lane vg owning VPT consecutive columns of the row of G (in
@@ -99,6 +99,10 @@ __global__ void __launch_bounds__(256) grad_kernel(const int32_t *__restrict__ c
             }
             constexpr int left = (U >> LL) > 0 ? (U >> LL) : 1;
             double *d = dval + p0 + k0 + e0;
+            // (applied to the sums: with the rows of G scaled first, a factor and a row that are small or
+            // large together left the range of a double where their products with X do not)
+#pragma unroll
+            for (int i = 0; i < left; ++i) acc[i] *= pairs.scale;
             if (accumulate) {
                 double old[left];
 #pragma unroll

@@ -419,8 +419,8 @@ int ensure_stage(const sell_mat *A, int32_t chunks, hipStream_t s);
 // cache slots (stage.hip); rebuilt when any of them changes.
 int ensure_stage_plan(const sell_mat *A, int32_t nblk, int32_t stride, int32_t ns, hipStream_t s);
 
-// Value gradients (grad.hip): dval (+)= sum over the pairs of c_p times the pattern-restricted
-// outer product of G_p and X_p, in CSR order (needs the row pointers).
+// Value gradients (grad.hip): dval (+)= scale times the sum over the pairs of c_p times the
+// pattern-restricted outer product of G_p and X_p, in CSR order (needs the row pointers).
 constexpr int kGradPairs = 16;
 // Workgroups of 256 threads over nrows rows, 256 >> ll of them at a time: one pass each up to a cap far
 // past any that the device holds, and far below the 2^32 threads at which a launch is refused (2^28 rows
@@ -431,7 +431,8 @@ inline unsigned grad_grid(int64_t nrows, int ll) {
 }
 struct GradPairs {
     const void *g[kGradPairs], *x[kGradPairs];
-    double c[kGradPairs];
+    double c[kGradPairs];  // powers of two: exact
+    double scale;
     int32_t n;
 };
 int launch_grad(const sell_mat *A, const GradPairs &pairs, int64_t ldg, int64_t ldx, int vec_dt, int32_t b,

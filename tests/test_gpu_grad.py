@@ -307,3 +307,42 @@ def test_grad_values_past_one_pass_of_workgroups(sc, n, b):
     assert torch.equal(out[1:n + 1], (G * X[col.long()]).sum(1).double())
     assert float(out[0]) == 5.0 and float(out[n + 1]) == 5.0
     M.close()
+
+
+@pytest.mark.parametrize("b", [1, 3, 8, 33])
+@pytest.mark.parametrize("alpha,g,x", [(2.0 ** -600, 2.0 ** -600, 2.0 ** 900), (2.0 ** 600, 2.0 ** 600, 2.0 ** -900),
+                                       (2.0 ** -1000, 2.0 ** -60, 2.0 ** 500)])
+def test_grad_values_factor_leaves_the_range_in_order(sc, b, alpha, g, x):
+    """alpha times the outer products, not the outer products of scaled rows: factors that leave the
+    range of a double against G, but not against the sums, change nothing (exact, powers of two)."""
+    import torch
+
+    A = synth.random_sparse(60, 40, 0.1, 224, empty_rows=3)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1)
+    G, X = synth.int_block_vector(A.nrows, b, 225), synth.int_block_vector(A.ncols, b, 226)
+    dval = torch.zeros(A.nnz, dtype=torch.float64, device="cuda:0")
+    sc.sell_grad_values(M, dev(g * G), dev(x * X), dval, alpha=alpha)
+    assert np.array_equal(host(dval), alpha * (g * x * oracle.pattern_outer(A, G, X)))
+    M.close()
+
+
+@pytest.mark.parametrize("N", [1, 2, 7])
+def test_chebyshev_gradient_of_far_scales(sc, N):
+    """A matrix with its scale, the block and the incoming gradient taken far from one by powers of two:
+    the value gradient is the ordinary one, scaled."""
+    import torch
+
+    A, s, X = _anderson_case(6, 2, 227)
+    G = synth.block_vector(A.nrows, 2, 228)
+    outs = []
+    for fm, fx, fg in ((1.0, 1.0, 1.0), (2.0 ** -500, 2.0 ** -400, 2.0 ** 600)):
+        M = sc.SellMatrix.from_csr(synth.CSR(A.nrows, A.ncols, A.rowptr, A.col, fm * A.val), C=32, sigma=1)
+        ck = torch.empty(sc.cheb_ckpt_elems(A.nrows, 2, N, 3), dtype=torch.float64, device="cuda:0")
+        Xd, Gd = dev(fx * X), dev(fg * G)
+        Y, dX = torch.empty_like(Xd), torch.empty_like(Xd)
+        dval = torch.empty(A.nnz, dtype=torch.float64, device="cuda:0")
+        sc.sell_cheb_forward(M, Xd, Y, N, fm * s, 0.0, 3, ck)
+        sc.sell_cheb_backward(M, Gd, N, fm * s, 0.0, 3, ck, dX, dval)
+        outs.append(host(dval) * fm / fg / fx)
+        M.close()
+    assert np.array_equal(outs[0], outs[1])
