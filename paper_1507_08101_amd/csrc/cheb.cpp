@@ -239,12 +239,20 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
     const int64_t seglen = std::min<int64_t>(K, N);
     // outer products per launch: the steps that make up 16 columns. Past that the gradient's own
     // traffic is small beside the gathers, and the adjoint vectors kept for a launch would cost
-    // memory (they are at most 16 columns in all).
-    const int64_t group = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(seglen, N), kGradPairs / b));
-    const int64_t nw = group + 2;  // adjoint vectors: the group's, and the two that the next step reads
+    // memory: the group's (16 columns, or one vector where it is wider) and the two that the next step
+    // reads. Where there is no room for them a launch takes one step.
+    int64_t group = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(seglen, N), kGradPairs / b));
+    int64_t nw = group + 2;
     Temps T(s);
     void *pw, *pseg = nullptr;
-    if ((rc = T.alloc(&pw, vb * size_t(nw))) || (seglen > 2 && (rc = T.alloc(&pseg, vb * size_t(seglen - 2))))) return rc;
+    if (seglen > 2 && (rc = T.alloc(&pseg, vb * size_t(seglen - 2)))) return rc;
+    if ((rc = T.alloc(&pw, vb * size_t(nw))) == SELL_ERR_OOM && group > 1) {
+        (void)hipGetLastError();
+        group = 1;
+        nw = 3;
+        rc = T.alloc(&pw, vb * size_t(nw));
+    }
+    if (rc) return rc;
     auto w = [&](int64_t m) { return block(static_cast<char *>(pw) + size_t(m % nw) * vb, n, b, dt); };
     const char *ck = static_cast<const char *>(ckpt);
     GradPairs pairs;

@@ -346,3 +346,40 @@ def test_chebyshev_gradient_of_far_scales(sc, N):
         outs.append(host(dval) * fm / fg / fx)
         M.close()
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("N,K,b", [(9, 4, 1), (12, 2, 3), (40, 25, 1)])
+def test_chebyshev_backward_without_room_for_groups(sc, N, K, b):
+    """With no memory for the adjoint vectors of several steps the backward pass takes a step at a time;
+    the other allocations still fail as out of memory, and nothing is left behind either way."""
+    import torch
+
+    A, s, X = _anderson_case(7, b, 229)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1)
+    G = dev(synth.block_vector(A.nrows, b, 230))
+    ck = torch.empty(sc.cheb_ckpt_elems(A.nrows, b, N, K), dtype=torch.float64, device="cuda:0")
+    Y = torch.empty((A.nrows, b), dtype=torch.float64, device="cuda:0")
+    sc.sell_cheb_forward(M, dev(X), Y, N, s, 0.2, K, ck)
+
+    def backward():
+        dX, dval = torch.empty_like(G), torch.full((A.nnz,), float("nan"), dtype=torch.float64, device="cuda:0")
+        sc.sell_cheb_backward(M, G, N, s, 0.2, K, ck, dX, dval)
+        return host(dX), host(dval)
+
+    want = backward()
+    live = sc.sell_debug_live_allocs()
+    failed = 0
+    for k in range(1, 5):
+        sc.sell_debug_fail_alloc(k)
+        try:
+            dX, dval = backward()
+            assert np.array_equal(dX, want[0]) and _relnorm(dval, want[1]) <= 1e-13
+        except sc.SellError as e:
+            assert e.code == sc.SELL_ERR_OOM
+            failed += 1
+        finally:
+            sc.sell_debug_fail_alloc(0)
+        torch.cuda.synchronize()
+        assert sc.sell_debug_live_allocs() == live
+    assert failed == (1 if min(K, N) > 2 else 0)
+    M.close()
