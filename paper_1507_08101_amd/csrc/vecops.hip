@@ -218,8 +218,9 @@ int launch_copy(const sell_bv *dst, const sell_bv *src, hipStream_t s) {
 // XCD's L2 (irregular, 500 K rows, sigma = 4096: 229 us dealt over the XCDs). 100^3 Laplacian, FP32
 // with its transpose: 37 us; 41 without LDS, 26.8 + 29.9 with a launch for each copy, entry by entry,
 // and 64-bit positions. Irregular, 500 K rows, FP64 with its transpose: 312 us (sigma = 1) and 262 (4096),
-// 358 and 365 with two launches.
-template <class V, class P>
+// 358 and 365 with two launches. CUT: long rows are shared by gridDim.y workgroups (update_parts), which
+// take eight entries of each in turn (a kernel of its own: 4 % on those whose rows are not, BF16).
+template <class V, class P, bool CUT>
 __global__ void __launch_bounds__(256) update_values_kernel(V *__restrict__ sval, const double *__restrict__ csr_val,
                                                             const int64_t *__restrict__ rowptr,
                                                             const int32_t *__restrict__ perm,
@@ -233,6 +234,8 @@ __global__ void __launch_bounds__(256) update_values_kernel(V *__restrict__ sval
         const int64_t s = s0 + threadIdx.x;
         const int64_t e0 = rowptr[s0], n = rowptr[s0 + 256 < nrows ? s0 + 256 : nrows] - e0;
         const bool staged = !perm && n <= kCap;
+        const int part = CUT ? int(blockIdx.y) : 0, parts = CUT ? int(gridDim.y) : 1;
+        if (staged && part) continue;
         if (staged) {
             __syncthreads();
 #pragma unroll
@@ -246,7 +249,8 @@ __global__ void __launch_bounds__(256) update_values_kernel(V *__restrict__ sval
             __syncthreads();
         }
         if (!staged && tval)
-            for (int64_t e = e0 + threadIdx.x; e < e0 + n; e += 256) tval[tpos[e]] = Conv<V, double>::go(csr_val[e]);
+            for (int64_t e = e0 + 256 * part + int(threadIdx.x); e < e0 + n; e += 256 * parts)
+                tval[tpos[e]] = Conv<V, double>::go(csr_val[e]);
         if (s >= nrows) continue;
         const int64_t row = perm ? int64_t(perm[s]) : s;
         const int64_t c = int64_t(uint32_t(s) / uint32_t(C)), base = cs[c] + (s - c * C);
@@ -259,7 +263,7 @@ __global__ void __launch_bounds__(256) update_values_kernel(V *__restrict__ sval
             }
             continue;
         }
-        for (int64_t k0 = 0; k0 < len; k0 += U) {
+        for (int64_t k0 = int64_t(U) * part; k0 < len; k0 += int64_t(U) * parts) {
             double v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = csr_val[p0 + (k0 + u < len ? k0 + u : len - 1)];
@@ -270,19 +274,22 @@ __global__ void __launch_bounds__(256) update_values_kernel(V *__restrict__ sval
     }
 }
 
-template <class V>
+template <class V, class P>
 static void go_update_values(const sell_mat *A, const double *val_dev, hipStream_t s) {
     const int64_t n = A->h.nrows;
-    const unsigned g = grid_for(n, 256, 1u << 24);
-    V *tv = A->transpose ? static_cast<V *>(A->transpose->d_val) : nullptr;
+    const unsigned g = grid_for(n, 256, 1u << 24), parts = unsigned(update_parts(n, A->h.nnz, g));
+    auto kern = parts > 1 ? update_values_kernel<V, P, true> : update_values_kernel<V, P, false>;
+    hipLaunchKernelGGL(kern, dim3(g, parts), dim3(256), 0, s, static_cast<V *>(A->d_val), val_dev, A->d_rowptr,
+                       A->d_perm, A->d_cs, A->h.C, n, static_cast<const P *>(A->d_tpos),
+                       A->transpose ? static_cast<V *>(A->transpose->d_val) : nullptr);
+}
+
+template <class V>
+static void go_update_values(const sell_mat *A, const double *val_dev, hipStream_t s) {
     if (A->tpos_wide)
-        hipLaunchKernelGGL((update_values_kernel<V, int64_t>), dim3(g), dim3(256), 0, s,
-                           static_cast<V *>(A->d_val), val_dev, A->d_rowptr, A->d_perm, A->d_cs, A->h.C, n,
-                           static_cast<const int64_t *>(A->d_tpos), tv);
+        go_update_values<V, int64_t>(A, val_dev, s);
     else
-        hipLaunchKernelGGL((update_values_kernel<V, int32_t>), dim3(g), dim3(256), 0, s,
-                           static_cast<V *>(A->d_val), val_dev, A->d_rowptr, A->d_perm, A->d_cs, A->h.C, n,
-                           static_cast<const int32_t *>(A->d_tpos), tv);
+        go_update_values<V, int32_t>(A, val_dev, s);
 }
 
 int launch_update_values(const sell_mat *A, const double *val_dev, hipStream_t s) {

@@ -57,6 +57,14 @@ int main() {
             expect(g >= 1 && g * 256 < (int64_t(1) << 32), "gradient threads", g, n);
             expect(n > per << 18 || (g * per >= n && (g - 1) * per < n), "gradient workgroups", g, n);
         }
+    // value updates: long rows shared by workgroups until the device is busy, never more than their pieces
+    for (int64_t n : {1, 255, 2000, 300000, 100000000})
+        for (int64_t len : {0, 1, 8, 9, 100, 2000}) {
+            const int64_t g = (n + 255) / 256, parts = update_parts(n, n * len, g);
+            expect(parts >= 1 && parts <= std::max<int64_t>(1, (len + 7) / 8), "update parts", parts, len);
+            expect(parts == 1 || g * parts <= 1024, "update workgroups at most", parts, n);
+            expect(g * parts >= std::min<int64_t>(513, g * ((len + 7) / 8)), "update workgroups", parts, n);
+        }
     if (failures) return 1;
     std::puts("launch rules ok");
     return 0;

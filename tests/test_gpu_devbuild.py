@@ -204,3 +204,39 @@ def test_value_update_equals_fresh_build(sc, n, per_row, sigma, dt):
         outs.append((Y, Z, torch.from_numpy(M.export_csr()[2])))
         M.close()
     assert all(torch.equal(u, v) for u, v in zip(*outs))
+
+
+@pytest.mark.parametrize("dt", ["f64", "bf16"])
+@pytest.mark.parametrize("nr,nc,length,sigma", [(3, 900, 800, 1), (257, 400, 65, 1), (600, 700, 250, 64), (300, 80, 9, 1)])
+def test_value_update_of_long_rows(sc, nr, nc, length, sigma, dt):
+    """Rows shared by several workgroups (some of a workgroup's 256 rows short, so that it deals them out
+    through LDS): as a matrix built from the new values, and so its copy of A^T, bit for bit."""
+    import torch
+
+    A = synth.random_sparse(nr, nc, length / nc, 231, empty_rows=min(2, nr - 1))
+    if nr > 512:  # a workgroup of short rows among those of long ones
+        keep = np.ones(A.nnz, dtype=bool)
+        keep[A.rowptr[256] + 40:A.rowptr[512]] = False
+        rp = np.concatenate([[0], np.cumsum(np.add.reduceat(np.append(keep, 0).astype(np.int64), A.rowptr[:-1])
+                                            * (np.diff(A.rowptr) > 0))])
+        A = synth.CSR(nr, nc, rp, A.col[keep], A.val[keep])
+    newv = synth.uniform(232, A.nnz, -2, 2)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    X, Xt = (torch.from_numpy(synth.block_vector(m, 2, 233)).to("cuda:0", vt) for m in (nc, nr))
+    outs = []
+    for first in (A.val, newv):
+        M = sc.SellMatrix.from_csr(synth.CSR(nr, nc, A.rowptr, A.col, first), C=32, sigma=sigma, dtype=dt)
+        Y, Z = torch.empty_like(Xt), torch.empty_like(X)
+        if first is A.val:
+            M.update_values(torch.from_numpy(newv).cuda())  # no copy of A^T yet
+            sc.sell_spmmv(M, X, Y)
+            outs.append((Y.clone(),))
+            M.update_values(torch.from_numpy(A.val).cuda())
+            sc.sell_spmmv_T(M, Xt, Z)
+            M.update_values(torch.from_numpy(newv).cuda())
+        sc.sell_spmmv(M, X, Y)
+        sc.sell_spmmv_T(M, Xt, Z)
+        outs.append((Y, Z, torch.from_numpy(M.export_csr()[2])))
+        M.close()
+    assert torch.equal(outs[0][0], outs[1][0])
+    assert all(torch.equal(u, v) for u, v in zip(outs[1], outs[2]))
