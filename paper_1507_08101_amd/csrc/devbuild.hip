@@ -39,6 +39,16 @@ unsigned grid_for(int64_t n) {
     return unsigned(g);
 }
 
+// A grid of one thread per slot whose chunks' entries are shared by gridDim.y workgroups, 64 entries each at
+// least and 2^16 workgroups in all at most: a thread alone with a row of a third of the matrix keeps every
+// other one waiting (300,000 rows, one of them full, first transposed product 86 ms, now 3.4; from the host,
+// where the row is walked in the cache, 66; 20,000 rows 5.7, 0.5 and 1.6).
+dim3 grid_over_entries(int64_t nslots, const std::vector<int32_t> &cl) {
+    const int64_t longest = cl.empty() ? 0 : *std::max_element(cl.begin(), cl.end());
+    const unsigned gx = grid_for(nslots);
+    return dim3(gx, unsigned(std::max<int64_t>(1, std::min<int64_t>(longest / 64, 65536 / gx))));
+}
+
 // flags[0] = 1 when the row pointers decrease or a row is 2^31 entries or longer;
 // flags[1] = 1 when a column index is out of range. Plain stores of the same value.
 __global__ void __launch_bounds__(kT) check_kernel(const int64_t *rowptr, const int32_t *col, int64_t nrows,
@@ -111,7 +121,7 @@ __global__ void __launch_bounds__(kT) fill_kernel(const int64_t *rowptr, const i
         const int64_t p0 = row >= 0 ? rowptr[row] : 0;
         const int32_t m = cl[c];
         const int64_t base = cs[c] + r;
-        for (int32_t k = 0; k < m; ++k) {
+        for (int32_t k = int32_t(blockIdx.y); k < m; k += int32_t(gridDim.y)) {
             const bool real = k < n;
             col[base + int64_t(k) * C] = real ? col_in[p0 + k] : -1;
             val[base + int64_t(k) * C] = Conv<V, double>::go(real ? val_in[p0 + k] : 0.0);
@@ -119,8 +129,8 @@ __global__ void __launch_bounds__(kT) fill_kernel(const int64_t *rowptr, const i
     }
 }
 
-// One thread per slot: len[row] = the row's entries (padding, column -1, only follows them);
-// len[nrows] = 0 for the prefix sum.
+// One thread per slot: len[row] = the row's entries, by bisection (padding, column -1, only follows
+// them); len[nrows] = 0 for the prefix sum.
 __global__ void __launch_bounds__(kT) row_lengths_kernel(const int32_t *col, const int32_t *cl, const int64_t *cs,
                                                          const int32_t *perm, int64_t nrows, int32_t C, int64_t *len) {
     for (int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x; s <= nrows; s += int64_t(gridDim.x) * kT) {
@@ -129,9 +139,14 @@ __global__ void __launch_bounds__(kT) row_lengths_kernel(const int32_t *col, con
             continue;
         }
         const int64_t c = s / C, row = perm ? int64_t(perm[s]) : s, base = cs[c] + (s - c * C);
-        const int32_t m = cl[c];
-        int32_t n = 0;
-        while (n < m && col[base + int64_t(n) * C] >= 0) ++n;
+        int32_t n = 0, past = cl[c];
+        while (n < past) {
+            const int32_t mid = n + (past - n) / 2;
+            if (col[base + int64_t(mid) * C] >= 0)
+                n = mid + 1;
+            else
+                past = mid;
+        }
         len[row] = n;
     }
 }
@@ -146,7 +161,7 @@ __global__ void __launch_bounds__(kT) expand_kernel(const int32_t *col, const V 
     for (int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x; s < nrows; s += int64_t(gridDim.x) * kT) {
         const int64_t c = s / C, row = perm ? int64_t(perm[s]) : s, base = cs[c] + (s - c * C);
         const int64_t p0 = rowptr[row], n = rowptr[row + 1] - p0;
-        for (int64_t k = 0; k < n; ++k) {
+        for (int64_t k = blockIdx.y; k < n; k += gridDim.y) {
             const int64_t e = base + k * C;
             key[p0 + k] = uint32_t(col[e]);
             pos[p0 + k] = int32_t(p0 + k);
@@ -317,15 +332,16 @@ int build_device_sell(sell_mat *M, int64_t nrows, int64_t ncols, const int64_t *
     DCHK(lib_malloc(reinterpret_cast<void **>(&M->d_col), sizeof(int32_t) * size_t(std::max<int64_t>(stored, 1))));
     DCHK(lib_malloc(&M->d_val, size_t(vb) * size_t(std::max<int64_t>(stored, 1))));
     if (nslots > 0) {
+        const dim3 gf = grid_over_entries(nslots, h.cl);
         if (vdt == SELL_F64)
-            hipLaunchKernelGGL(fill_kernel<double>, dim3(grid_for(nslots)), dim3(kT), 0, s, rowptr, col, val, len,
+            hipLaunchKernelGGL(fill_kernel<double>, gf, dim3(kT), 0, s, rowptr, col, val, len,
                                slot_row, M->d_cl, M->d_cs, nrows, nslots, C, M->d_col,
                                static_cast<double *>(M->d_val));
         else if (vdt == SELL_F32)
-            hipLaunchKernelGGL(fill_kernel<float>, dim3(grid_for(nslots)), dim3(kT), 0, s, rowptr, col, val, len,
+            hipLaunchKernelGGL(fill_kernel<float>, gf, dim3(kT), 0, s, rowptr, col, val, len,
                                slot_row, M->d_cl, M->d_cs, nrows, nslots, C, M->d_col, static_cast<float *>(M->d_val));
         else
-            hipLaunchKernelGGL(fill_kernel<uint16_t>, dim3(grid_for(nslots)), dim3(kT), 0, s, rowptr, col, val, len,
+            hipLaunchKernelGGL(fill_kernel<uint16_t>, gf, dim3(kT), 0, s, rowptr, col, val, len,
                                slot_row, M->d_cl, M->d_cs, nrows, nslots, C, M->d_col,
                                static_cast<uint16_t *>(M->d_val));
         DCHK(hipGetLastError());
@@ -407,7 +423,7 @@ int device_transpose(const sell_mat *A, sell_mat **out, void **out_tpos, bool *w
     DCHK(T.alloc(reinterpret_cast<void **>(&value), 8 * nnz));
     DCHK(T.alloc(reinterpret_cast<void **>(&tval), 8 * nnz));
     DCHK(T.alloc(reinterpret_cast<void **>(&trp), 8 * (size_t(h.ncols) + 1)));
-    const dim3 gr(grid_for(h.nrows)), gz(grid_for(h.nnz)), bl(kT);
+    const dim3 gr = grid_over_entries(h.nrows, h.cl), gz(grid_for(h.nnz)), bl(kT);
     if (h.vdt == SELL_F64)
         hipLaunchKernelGGL(expand_kernel<double>, gr, bl, 0, s, A->d_col, static_cast<const double *>(A->d_val), A->d_cs,
                            A->d_perm, A->d_rowptr, h.nrows, h.C, key, pos, row_of, value);

@@ -240,3 +240,38 @@ def test_value_update_of_long_rows(sc, nr, nc, length, sigma, dt):
         M.close()
     assert torch.equal(outs[0][0], outs[1][0])
     assert all(torch.equal(u, v) for u, v in zip(outs[1], outs[2]))
+
+
+@pytest.mark.parametrize("dt", ["f64", "bf16"])
+@pytest.mark.parametrize("n,C,sigma", [(700, 32, 1), (700, 7, 64), (131, 32, 131)])
+def test_device_steps_on_full_rows_and_columns(sc, n, C, sigma, dt):
+    """A full row and a full column beside rows of one entry and empty ones (chunks whose entries several
+    workgroups share): the device-built matrix is the host-built one entry for entry, and the transposed
+    product, the row pointers (by the value gradient) and a value update hold."""
+    import torch
+
+    rows = np.concatenate([np.full(n - 2, 2), np.arange(n - 3)])
+    cols = np.concatenate([np.arange(n - 2), np.full(n - 3, 5)])
+    order = np.lexsort((cols, rows))
+    rp = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(rows, minlength=n), out=rp[1:])
+    A = synth.CSR(n, n, rp, cols[order].astype(np.int32), synth.randint(234, rows.size, -3, 3).astype(np.float64))
+    M = sc.SellMatrix.from_csr(A, C=C, sigma=sigma, dtype=dt)
+    D = sc.SellMatrix.from_device_csr(n, n, torch.from_numpy(A.rowptr).cuda(), torch.from_numpy(A.col).cuda(),
+                                      torch.from_numpy(A.val).cuda(), C=C, sigma=sigma, dtype=dt)
+    for u, v in zip(sc.sell_export_sell(M.handle), sc.sell_export_sell(D.handle)):
+        assert np.array_equal(u, v)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    x, g = synth.int_block_vector(n, 3, 235), synth.int_block_vector(n, 3, 236)
+    X, G = (torch.from_numpy(v).to("cuda:0", vt) for v in (x, g))
+    newv = synth.randint(237, rows.size, -3, 3).astype(np.float64)
+    Z, dval = torch.empty_like(X), torch.empty(A.nnz, dtype=torch.float64, device="cuda:0")
+    for B in (M, D):
+        sc.sell_spmmv_T(B, X, Z)
+        assert np.array_equal(Z.double().cpu().numpy(), oracle.spmmv_T(A, x))
+        sc.sell_grad_values(B, G, X, dval)
+        assert np.array_equal(dval.cpu().numpy(), oracle.pattern_outer(A, g, x))
+        B.update_values(torch.from_numpy(newv).cuda())
+        sc.sell_spmmv_T(B, X, Z)
+        assert np.array_equal(Z.double().cpu().numpy(), oracle.spmmv_T(synth.CSR(n, n, A.rowptr, A.col, newv), x))
+        B.close()
