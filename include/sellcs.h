@@ -538,7 +538,8 @@ int sell_batch_info(const sell_batch *B, int32_t *count, int64_t *rows, int64_t 
  * matrix: matrix m's group q (yy = 0, xy = 1, xx = 2), column j at dot[(3 m + q) b + j].
  * SELL_ERR_UNSUPPORTED while block widths other than b are set (sell_batch_set_widths).
  * Calls on one batch must be ordered (one stream, or synchronised): the launch tables are
- * reused. Asynchronous. */
+ * reused. A stream may be destroyed once its work is done; the batch may outlive it.
+ * Asynchronous. */
 int sell_batch_spmmv_aug(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z,
                          const sell_spmv_opts *opts, void *stream);
 

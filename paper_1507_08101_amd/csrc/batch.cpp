@@ -67,7 +67,7 @@ struct sell_batch {
     void *h_slot[kSlots] = {};  // pinned staging copies (also the record of the slot content)
     hipEvent_t ev[kSlots] = {};
     bool valid[kSlots] = {};
-    bool pending[kSlots] = {};          // the slot's upload was queued on up[slot] and not waited for
+    bool pending[kSlots] = {};          // the slot's upload was queued on up[slot] (which may be gone)
     hipStream_t up[kSlots] = {};
     int next = 0;
     std::vector<uint8_t> stage;
@@ -97,8 +97,9 @@ struct sell_batch {
 namespace sellcs {
 
 void batch_free(sell_batch *B) {
+    // (not by the uploads' events: the streams they were recorded on may be gone)
+    if (std::any_of(B->pending, B->pending + kSlots, [](bool p) { return p; })) (void)hipDeviceSynchronize();
     for (int i = 0; i < kSlots; ++i) {
-        if (B->pending[i]) (void)hipEventSynchronize(B->ev[i]);
         if (B->ev[i]) (void)hipEventDestroy(B->ev[i]);
         if (B->d_slot[i]) (void)lib_free(B->d_slot[i]);
         if (B->h_slot[i]) (void)lib_host_free(B->h_slot[i]);
@@ -282,7 +283,16 @@ int place_table(sell_batch *B, const std::vector<int32_t> &blk, bool reserved, h
             slot = B->next;
             B->next = (B->next + 1) % kRing;
         }
-        if (B->pending[slot]) HIPCHK(hipEventSynchronize(B->ev[slot]));  // its last upload has been read
+        // The slot's last upload has to be read before the staging copy changes. An event is waited for only
+        // on the stream it was recorded on: the runtime looks that stream up, and a caller may have destroyed
+        // another one since. Calls on a batch are ordered, so what has been queued on this stream comes after
+        // whatever an earlier call queued on another. (A stream that is recorded cannot be waited for.)
+        if (B->pending[slot]) {
+            hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+            if (B->up[slot] != s) HIPCHK(hipStreamIsCapturing(s, &st));
+            HIPCHK(B->up[slot] == s || st != hipStreamCaptureStatusNone ? hipEventSynchronize(B->ev[slot])
+                                                                        : hipStreamSynchronize(s));
+        }
         B->pending[slot] = B->valid[slot] = false;
         std::memcpy(B->h_slot[slot], B->stage.data(), B->table_bytes);
         HIPCHK(hipMemcpyAsync(B->d_slot[slot], B->h_slot[slot], B->table_bytes, hipMemcpyHostToDevice, s));

@@ -527,3 +527,52 @@ def test_batch_cg_more_columns_than_waves(sc, mode, b):
     for Bt in (A64, lo):
         if Bt is not None:
             Bt.close()
+
+
+def test_batch_outlives_the_streams_it_was_used_on(sc):
+    """Products on streams that the caller destroys afterwards, then more tables than the batch keeps on
+    another stream, and a batch destroyed after its last stream: results bit for bit those of one stream."""
+    import ctypes as ct
+
+    import torch
+
+    hip = ct.CDLL("libamdhip64.so")
+
+    def stream():
+        h = ct.c_void_p()
+        assert hip.hipStreamCreate(ct.byref(h)) == 0
+        return h.value
+
+    def destroy(h):
+        assert hip.hipStreamSynchronize(ct.c_void_p(h)) == 0 and hip.hipStreamDestroy(ct.c_void_p(h)) == 0
+
+    mats = [synth.laplacian3d(5), synth.laplacian2d(9)]
+    Ms = [sc.SellMatrix.from_csr(A, C=32, sigma=1) for A in mats]
+    n, b = sum(A.nrows for A in mats), 4
+    X = torch.from_numpy(synth.block_vector(n, b, 230)).cuda()
+    ref = sc.SellBatch(Ms)
+    want = [torch.empty_like(X) for _ in range(12)]
+    for k, Y in enumerate(want):
+        sc.sell_batch_spmmv_aug(ref, X, Y, flags=sc.SCALE, alpha=1.0 + k)
+    ref.close()
+    torch.cuda.synchronize()
+    Bt = sc.SellBatch(Ms)
+    got = [torch.empty_like(X) for _ in want]
+    dead = [stream(), stream()]
+    for k in range(4):  # fills the table slots from two streams
+        sc.sell_batch_spmmv_aug(Bt, X, got[k], flags=sc.SCALE, alpha=1.0 + k, stream=dead[k // 2])
+        torch.cuda.synchronize()
+    for h in dead:
+        destroy(h)
+    for k in range(4, 10):  # on the current stream, every slot twice
+        sc.sell_batch_spmmv_aug(Bt, X, got[k], flags=sc.SCALE, alpha=1.0 + k)
+    torch.cuda.synchronize()
+    last = stream()
+    for k in range(10, 12):
+        sc.sell_batch_spmmv_aug(Bt, X, got[k], flags=sc.SCALE, alpha=1.0 + k, stream=last)
+    destroy(last)
+    Bt.close()
+    for u, v in zip(got, want):
+        assert torch.equal(u, v)
+    for M in Ms:
+        M.close()
