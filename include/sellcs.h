@@ -92,11 +92,15 @@ int sell_version(void);
 
 /* Test hooks for the error paths (not for production use). sell_debug_fail_alloc(k): the k-th
  * device or pinned host allocation the library makes from now on fails as out of memory
- * (k >= 1; 0 clears; the hook is process-wide). sell_debug_live_allocs: the number of device
+ * (k >= 1; 0 clears; the hook is process-wide). sell_debug_fail_allocs(k, then, forced): the same,
+ * and the then-th allocation after that one fails too (0: none), for calls that go on another way
+ * after a failure; *forced (may be NULL) receives the failures forced since either was last
+ * called. sell_debug_live_allocs: the number of device
  * and pinned host allocations the library holds (its workspaces and the objects alive), so that
- * a test can check that a failed call left nothing behind. Errors: SELL_ERR_ARG for k < 0 or a
- * NULL count. */
+ * a test can check that a failed call left nothing behind. Errors: SELL_ERR_ARG for k < 0, then < 0
+ * or a NULL count. */
 int sell_debug_fail_alloc(int64_t k);
+int sell_debug_fail_allocs(int64_t k, int64_t then, int64_t *forced);
 int sell_debug_live_allocs(int64_t *count);
 
 /* ------------------------------------------------------------------------------------ */

@@ -99,6 +99,7 @@ _SIGNATURES = {
     "sell_probe_bandwidth": ([_I, _P, _P, _I64, _P], _I),
     "sell_probe_stream": ([_I, _I, _I, _I, _I, _P, _P, _I64, _P], _I),
     "sell_debug_fail_alloc": ([_I64], _I),
+    "sell_debug_fail_allocs": ([_I64, _I64, ct.POINTER(_I64)], _I),
     "sell_debug_live_allocs": ([ct.POINTER(_I64)], _I),
     "sell_probe_gather": ([_P, _I64, _I32, _P, _I64, _P, _P], _I),
     "sell_kpm_dos": ([_P, _I64, _I32, _I32, _D, _D, _P, _I64, _P, _P], _I),
@@ -691,6 +692,14 @@ def sell_batch_cg(A64, Alo, B, X, tol=1e-10, maxit=100000, inner_tol=0.1, inner_
 def sell_debug_fail_alloc(k):
     """Test hook: the k-th next allocation of the library fails as out of memory (0 clears)."""
     _ok(lib().sell_debug_fail_alloc(int(k)), "sell_debug_fail_alloc")
+
+
+def sell_debug_fail_allocs(k, then=0):
+    """Test hook: the k-th next allocation fails, and the then-th after it (0: none); returns the
+    failures forced since the hook was last set."""
+    n = _I64()
+    _ok(lib().sell_debug_fail_allocs(int(k), int(then), ct.byref(n)), "sell_debug_fail_allocs")
+    return n.value
 
 
 def sell_debug_live_allocs():

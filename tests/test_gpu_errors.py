@@ -157,3 +157,62 @@ def test_hook_arguments(sc):
         sc.sell_debug_fail_alloc(-1)
     sc.sell_debug_fail_alloc(0)
     assert sc.sell_debug_live_allocs() >= 0
+
+
+@pytest.mark.parametrize("sigma", [1, 64])
+def test_first_use_of_the_transpose_with_two_failures(sc, sigma):
+    """The row pointers and the copy of A^T fall back to the host when the device steps find no memory:
+    every single failure, and after each every failure of the way that follows, gives the results or
+    SELL_ERR_OOM, leaves nothing behind, and the matrix does its work afterwards."""
+    import torch
+
+    A = synth.random_sparse(300, 260, 0.03, 240, empty_rows=5, long_row=120)
+    X = dev(synth.block_vector(A.nrows, 2, 241))
+    G = dev(synth.block_vector(A.ncols, 2, 242))
+    newv = torch.from_numpy(synth.uniform(243, A.nnz, -2, 2)).cuda()
+
+    def op(M):
+        Z, W = torch.empty_like(G), torch.empty_like(G)
+        dval = torch.empty(A.nnz, dtype=torch.float64, device="cuda:0")
+        sc.sell_spmmv_T(M, X, Z)
+        sc.sell_grad_values(M, X, G, dval)
+        M.update_values(newv)
+        sc.sell_spmmv_T(M, X, W)
+        M.update_values(torch.from_numpy(A.val).cuda())
+        return [Z, dval, W]
+
+    def fresh():
+        return sc.SellMatrix.from_csr(A, C=32, sigma=sigma)
+
+    M = fresh()
+    want = op(M)
+    M.close()
+    torch.cuda.synchronize()
+    base = sc.sell_debug_live_allocs()
+    sc.sell_debug_fail_allocs(0)
+    outcomes = {True: 0, False: 0}
+    for k in range(1, 60):
+        for then in range(60):
+            M = fresh()
+            sc.sell_debug_fail_allocs(k, then)
+            ok = True
+            try:
+                got = op(M)
+            except sc.SellError as e:
+                assert e.code == sc.SELL_ERR_OOM, (k, then, str(e))
+                ok = False
+            forced = sc.sell_debug_fail_allocs(0)
+            assert not ok or all(torch.equal(u, v) for u, v in zip(got, want)), (k, then)
+            assert all(torch.equal(u, v) for u, v in zip(op(M), want)), (k, then)
+            M.close()
+            torch.cuda.synchronize()
+            assert sc.sell_debug_live_allocs() == base, (k, then)
+            outcomes[ok] += forced > 0
+            if forced < 1 + (then > 0):
+                break
+        if forced == 0:
+            break
+    assert forced == 0 and k > 20, k  # past the last allocation: the device steps make some 25
+    assert outcomes[True] > 20 and outcomes[False] > 10, outcomes
+    with pytest.raises(sc.SellError):
+        sc.sell_debug_fail_allocs(1, -1)
