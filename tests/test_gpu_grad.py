@@ -383,3 +383,46 @@ def test_chebyshev_backward_without_room_for_groups(sc, N, K, b):
         assert sc.sell_debug_live_allocs() == live
     assert failed == (1 if min(K, N) > 2 else 0)
     M.close()
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("b", [1, 2, 4, 8, 12])
+def test_chebyshev_of_operands_aligned_to_an_element(sc, b, dt):
+    """The Chebyshev calls with every operand one element into a larger buffer (rows that the
+    compiled widths' vector accesses may not touch): bit for bit the aligned calls, the inputs unchanged,
+    nothing written beside the outputs."""
+    import torch
+
+    A, s, X0 = _anderson_case(7, b, 244)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1, dtype=dt)
+    vt = torch.float64 if dt == "f64" else torch.float32
+    n, N, K = A.nrows, 7, 3
+    G0 = synth.block_vector(n, b, 245)
+    elems = sc.cheb_ckpt_elems(n, b, N, K)
+    coef = np.linspace(1.0, 0.2, N + 1)
+    outs = []
+    for off in (0, 1):
+        bufs = []
+
+        def buf(count, init=None):
+            t = torch.full((count + 2,), 9.0, dtype=vt, device="cuda:0")
+            bufs.append((t, count))
+            v = t[off:off + count]
+            if init is not None:
+                v.copy_(torch.from_numpy(init).reshape(-1))
+            return v
+
+        X, G = buf(n * b, X0).view(n, b), buf(n * b, G0).view(n, b)
+        Xc, Gc = X.clone(), G.clone()
+        Y, dX, Z = (buf(n * b).view(n, b) for _ in range(3))
+        ck = buf(elems)
+        dval = torch.empty(A.nnz, dtype=torch.float64, device="cuda:0")
+        sc.sell_cheb_forward(M, X, Y, N, s, 0.2, K, ck)
+        sc.sell_cheb_backward(M, G, N, s, 0.2, K, ck, dX, dval)
+        sc.sell_cheb_filter(M, X, coef, s, 0.2, Z=Z)
+        assert torch.equal(X, Xc) and torch.equal(G, Gc)
+        for t, count in bufs:
+            assert bool((t[:off] == 9.0).all()) and bool((t[off + count:] == 9.0).all())
+        outs.append([v.clone() for v in (Y, dX, Z, ck, dval)])
+    assert all(torch.equal(u, v) for u, v in zip(*outs))
+    M.close()
