@@ -91,10 +91,34 @@ int shifted_product(const sell_mat *M, const sell_bv &x, sell_bv &y, double alph
     return aug_impl(M, &x, &y, nullptr, o, true, s, nullptr, nullptr, nullptr, w);
 }
 
-bool overlap(const void *p, const void *q, size_t bytes) {
+bool overlap(const void *p, size_t pbytes, const void *q, size_t qbytes) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
-    return a < b + bytes && b < a + bytes;
+    return a < b + qbytes && b < a + pbytes;
 }
+
+// The array that a value gradient is computed in: dval itself, or where it overlaps what is still read (or
+// written) meanwhile a temporary, which finish() copies to it.
+struct GradTarget {
+    double *dval, *work;
+    size_t bytes;
+    hipStream_t s;
+    int init(Temps &T, double *d, size_t nnz, bool apart, bool accumulate) {
+        dval = work = d;
+        bytes = nnz * sizeof(double);
+        s = T.s;
+        if (apart) return SELL_OK;
+        void *p;
+        const int rc = T.alloc(&p, bytes);
+        if (rc) return rc;
+        work = static_cast<double *>(p);
+        if (accumulate) HIPCHK(hipMemcpyAsync(work, dval, bytes, hipMemcpyDeviceToDevice, s));
+        return SELL_OK;
+    }
+    int finish() {
+        if (work != dval) HIPCHK(hipMemcpyAsync(dval, work, bytes, hipMemcpyDeviceToDevice, s));
+        return SELL_OK;
+    }
+};
 
 }  // namespace
 
@@ -117,7 +141,16 @@ int sell_grad_values(const sell_mat *A, const sell_bv *G, const sell_bv *X, doub
     p.x[0] = X->ptr;
     p.c[0] = 1.0;
     p.scale = alpha;
-    return launch_grad(A, p, G->ld, X->ld, G->dt, b, accumulate ? 1 : 0, dval, s);
+    const size_t row = size_t(b) * dtype_bytes(G->dt), bytes = size_t(A->h.nnz) * sizeof(double);
+    Temps T(s);
+    GradTarget d;
+    if ((rc = d.init(T, dval, size_t(A->h.nnz),
+                     !overlap(dval, bytes, G->ptr, size_t(A->h.nrows) * row) &&
+                         !overlap(dval, bytes, X->ptr, size_t(A->h.ncols) * row),
+                     accumulate != 0)) ||
+        (rc = launch_grad(A, p, G->ld, X->ld, G->dt, b, accumulate ? 1 : 0, d.work, s)))
+        return rc;
+    return d.finish();
 }
 
 int sell_cheb_forward(const sell_mat *A, const sell_bv *X, sell_bv *Y, int64_t N, double scale, double c,
@@ -136,10 +169,19 @@ int sell_cheb_forward(const sell_mat *A, const sell_bv *X, sell_bv *Y, int64_t N
     const int dt = vec_dt_of(A);
     const size_t vb = size_t(n) * b * (dt == SELL_F64 ? 8 : 4);
     Temps T(s);
-    void *p0, *p1;
+    void *p0, *p1, *px;
     if ((rc = T.alloc(&p0, vb)) || (rc = T.alloc(&p1, vb))) return rc;
     char *ck = static_cast<char *>(ckpt);
     const int64_t nseg = (N + K - 1) / K;
+    // operands inside the checkpoints: X from a copy, v_N to Y last
+    auto in_ckpt = [&](const void *p) { return ck && overlap(p, vb, ck, 2 * size_t(nseg) * vb); };
+    const bool y_last = in_ckpt(Y->ptr);
+    sell_bv V0 = *X;
+    if (in_ckpt(X->ptr)) {
+        if ((rc = T.alloc(&px, vb))) return rc;
+        V0 = block(px, n, b, dt);
+        if ((rc = launch_copy(&V0, X, s))) return rc;
+    }
     // the block of v_i in the checkpoints (-1: none); with K = 1 also v_i as the second of the pair before
     auto first = [&](int64_t i) { return ck && i % K == 0 && i / K < nseg ? 2 * (i / K) : int64_t(-1); };
     auto second = [&](int64_t i) {
@@ -148,20 +190,21 @@ int sell_cheb_forward(const sell_mat *A, const sell_bv *X, sell_bv *Y, int64_t N
     auto at = [&](int64_t slot) { return block(ck + size_t(slot) * vb, n, b, dt); };
     if (first(0) >= 0) {
         sell_bv c0 = at(first(0));
-        if ((rc = launch_copy(&c0, X, s))) return rc;
+        if ((rc = launch_copy(&c0, &V0, s))) return rc;
     }
     // v_i goes to its checkpoint block, v_N to Y (where a checkpoint does not want it, and X is not
     // in its way), every other v_i to the work block that does not hold v_i-1; v_i-2, which the
     // step reads element by element as it writes v_i, may be in that one
-    sell_bv prev = *X, cur = *X;
+    sell_bv prev = V0, cur = V0;
     for (int64_t i = 1; i <= N; ++i) {
         const int64_t sl = first(i) >= 0 ? first(i) : second(i);
-        sell_bv out = sl >= 0                                       ? at(sl)
-                      : i == N && !overlap(X->ptr, Y->ptr, vb) ? *Y
-                                                                    : block(cur.ptr == p0 ? p1 : p0, n, b, dt);
+        const bool last = i == N && y_last;
+        sell_bv out = sl >= 0 && !last                                    ? at(sl)
+                      : i == N && !last && !overlap(X->ptr, vb, Y->ptr, vb) ? *Y
+                                                                            : block(cur.ptr == p0 ? p1 : p0, n, b, dt);
         if ((rc = shifted_product(A, cur, out, (i == 1 ? 1.0 : 2.0) / scale, c, i == 1 ? nullptr : &prev, s))) return rc;
-        if (first(i) >= 0 && second(i) >= 0) {
-            sell_bv again = at(second(i));
+        if (sl >= 0 && (last || (first(i) >= 0 && second(i) >= 0))) {  // (v_N is never the first of a pair)
+            sell_bv again = at(last ? sl : second(i));
             if ((rc = launch_copy(&again, &out, s))) return rc;
         }
         prev = cur;
@@ -255,13 +298,20 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
     if (rc) return rc;
     auto w = [&](int64_t m) { return block(static_cast<char *>(pw) + size_t(m % nw) * vb, n, b, dt); };
     const char *ck = static_cast<const char *>(ckpt);
+    GradTarget target;
+    const size_t dvb = size_t(A->h.nnz) * sizeof(double);
+    if ((rc = target.init(T, dval, size_t(A->h.nnz),
+                          !overlap(dval, dvb, ck, 2 * size_t(nseg) * vb) && !overlap(dval, dvb, G->ptr, vb) &&
+                              !overlap(dval, dvb, dX->ptr, vb),
+                          false)))
+        return rc;
     GradPairs pairs;
     pairs.n = 0;
     pairs.scale = (N > 1 ? 2.0 : 1.0) / scale;
     int written = 0;
     auto flush = [&]() -> int {
         if (pairs.n == 0) return SELL_OK;
-        const int r = launch_grad(A, pairs, b, b, dt, b, written, dval, s);
+        const int r = launch_grad(A, pairs, b, b, dt, b, written, target.work, s);
         pairs.n = 0;
         written = 1;
         return r;
@@ -285,14 +335,16 @@ int sell_cheb_backward(const sell_mat *A, const sell_bv *G, int64_t N, double sc
             pairs.x[pairs.n] = v(m).ptr;
             pairs.c[pairs.n++] = m > 0 || N == 1 ? 1.0 : 0.5;
             if ((pairs.n == group || m == lo) && (rc = flush())) return rc;
-            sell_bv out = m == 0 && !overlap(G->ptr, dX->ptr, vb) ? *dX : w(m);
+            sell_bv out = m == 0 && !overlap(G->ptr, vb, dX->ptr, vb) ? *dX : w(m);
             if ((rc = shifted_product(AT, w1, out, (m > 0 ? 2.0 : 1.0) / scale, c, m + 2 <= N ? &w2 : nullptr, s)))
                 return rc;
         }
     }
-    if (!overlap(G->ptr, dX->ptr, vb)) return SELL_OK;
-    const sell_bv w0 = w(0);
-    return launch_copy(dX, &w0, s);
+    if (overlap(G->ptr, vb, dX->ptr, vb)) {
+        const sell_bv w0 = w(0);
+        if ((rc = launch_copy(dX, &w0, s))) return rc;
+    }
+    return target.finish();
 }
 
 }  // extern "C"

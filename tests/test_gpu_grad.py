@@ -426,3 +426,65 @@ def test_chebyshev_of_operands_aligned_to_an_element(sc, b, dt):
         outs.append([v.clone() for v in (Y, dX, Z, ck, dval)])
     assert all(torch.equal(u, v) for u, v in zip(*outs))
     M.close()
+
+
+@pytest.mark.parametrize("N,K,b", [(1, 1, 1), (5, 1, 2), (6, 3, 1), (8, 3, 4)])
+def test_chebyshev_operands_inside_the_checkpoints(sc, N, K, b):
+    """X, then Y, anywhere in the checkpoint buffer (whole blocks and across two): the results and the
+    checkpoints of separate buffers, the final Y over them."""
+    import torch
+
+    A, s, X0 = _anderson_case(6, b, 246)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1)
+    n = A.nrows
+    elems, vb = sc.cheb_ckpt_elems(n, b, N, K), n * b
+    X, Y, ck = dev(X0), torch.empty((n, b), dtype=torch.float64, device="cuda:0"), torch.empty(elems, dtype=torch.float64, device="cuda:0")
+    sc.sell_cheb_forward(M, X, Y, N, s, 0.2, K, ck)
+    for at in sorted({0, vb, vb // 2 * 2, elems - vb, max(0, elems - vb - vb // 2)}):
+        c = torch.zeros(elems, dtype=torch.float64, device="cuda:0")
+        xin, y = c[at:at + vb].view(n, b), torch.empty_like(Y)
+        xin.copy_(X)
+        sc.sell_cheb_forward(M, xin, y, N, s, 0.2, K, c)
+        assert torch.equal(y, Y) and torch.equal(c, ck)
+        c, want = torch.zeros_like(c), ck.clone()
+        sc.sell_cheb_forward(M, X, c[at:at + vb].view(n, b), N, s, 0.2, K, c)
+        want[at:at + vb] = Y.reshape(-1)
+        assert torch.equal(c, want)
+    M.close()
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_value_gradient_over_its_inputs(sc, accumulate):
+    """dval over G, over X, and over the checkpoints or the incoming gradient of a Chebyshev step: as
+    into a buffer of its own."""
+    import torch
+
+    A, s, X0 = _anderson_case(6, 3, 247)
+    M = sc.SellMatrix.from_csr(A, C=32, sigma=1)
+    n, b, N, K = A.nrows, 3, 6, 2
+    G0 = synth.block_vector(n, b, 248)
+    size = max(A.nnz, sc.cheb_ckpt_elems(n, b, N, K)) + 8
+    for which in ("G", "X"):
+        buf = torch.zeros(size, dtype=torch.float64, device="cuda:0")
+        v = buf[3:3 + n * b].view(n, b)
+        v.copy_(torch.from_numpy(G0 if which == "G" else X0))
+        other = dev(X0 if which == "G" else G0)
+        want = buf[:A.nnz].clone()
+        args = (v, other) if which == "G" else (other, v)
+        sc.sell_grad_values(M, *(t.clone() for t in args), want, alpha=0.5, accumulate=accumulate)
+        sc.sell_grad_values(M, *args, buf[:A.nnz], alpha=0.5, accumulate=accumulate)
+        assert torch.equal(buf[:A.nnz], want)
+    Y, dX = torch.empty((n, b), dtype=torch.float64, device="cuda:0"), torch.empty((n, b), dtype=torch.float64, device="cuda:0")
+    ck, want = (torch.zeros(size, dtype=torch.float64, device="cuda:0") for _ in range(2))
+    sc.sell_cheb_forward(M, dev(X0), Y, N, s, 0.2, K, ck)
+    sc.sell_cheb_backward(M, dev(G0), N, s, 0.2, K, ck, dX, want)
+    c = ck.clone()
+    dX2 = torch.empty_like(dX)
+    sc.sell_cheb_backward(M, dev(G0), N, s, 0.2, K, c, dX2, c)
+    assert torch.equal(c[:A.nnz], want[:A.nnz]) and torch.equal(dX2, dX)
+    buf = torch.zeros(size, dtype=torch.float64, device="cuda:0")
+    g = buf[5:5 + n * b].view(n, b)
+    g.copy_(torch.from_numpy(G0))
+    sc.sell_cheb_backward(M, g, N, s, 0.2, K, ck, dX2, buf)
+    assert torch.equal(buf[:A.nnz], want[:A.nnz]) and torch.equal(dX2, dX)
+    M.close()
