@@ -463,7 +463,12 @@ static bool mfma_vtw(int m, int k, bool vec) { return 2 * m * k > (vec ? 16 : 11
 // <= 2) on they are at least level (4 x 6: 78 against 67; 12 x 2 97 against 91) and then ahead:
 // 8 x 8 104 against 94, 16 x 16 121 against 87, 32 x 32 191 against 92, 64 x 64 392 against 134. In
 // place: m = 6 61 against 64, m = 8 78 against 73, m = 32 178 against 77, m = 64 365 against 115.
-static bool mfma_vx(int m, int k) { return m >= 2 && m + k >= 10 && (k > 2 || m >= 12); }
+// With beta a row of W costs a second load and two columns of it leave the LDS kernel, whose rows of V then
+// conflict in no bank unless 16 divides m, little else: n = 600 K, k = 1, m = 12 16.3 against 17.1, 17 19.8 and
+// 21.6, 16 26.7 and 19.7, 20 23.2 and 22.4.
+static bool mfma_vx(int m, int k, double beta) {
+    return m >= 2 && m + k >= 10 && (k > 2 || (beta != 0.0 ? m >= 20 || m == 16 : m >= 12));
+}
 static bool mfma_vx_inplace(int m) { return m >= 7; }
 
 // W = alpha V X + beta W (W may be V) on the matrix cores, m >= 2
@@ -517,7 +522,7 @@ int launch_tsmttsm(const double *V, int64_t ldv, const double *W, int64_t ldw, i
 int launch_tsmm(const double *V, int64_t ldv, const double *X, int64_t ldx, int m, int k, int64_t n, double alpha,
                 double beta, double *W, int64_t ldw, hipStream_t s) {
     if (n == 0) return SELL_OK;
-    if (mfma_vx(m, k)) return go_tsmm_mfma(V, ldv, X, ldx, m, k, n, alpha, beta, W, ldw, s);
+    if (mfma_vx(m, k, beta)) return go_tsmm_mfma(V, ldv, X, ldx, m, k, n, alpha, beta, W, ldw, s);
     const int R = tsmm_rows(m, k);
     const size_t lds = size_t(m * k + R * m) * sizeof(double);
     hipLaunchKernelGGL(tsmm_kernel, dim3(tgrid((n + R - 1) / R * kTT, 8192)), dim3(kTT), lds, s, V, ldv, X, ldx, m,

@@ -172,3 +172,17 @@ def test_matrix_core_blocks_keep_nonfinite_entries_in_their_places(sc):
     want = np.zeros((n, k), bool)
     want[41, :] = True
     assert np.array_equal(bad, want)
+
+
+@pytest.mark.parametrize("m", [9, 12, 15, 16, 17, 19, 20])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_narrow_update_either_side_of_the_matrix_cores(sc, m, k):
+    """V X + beta W of one to three columns, where beta moves the line between the kernels: element by
+    element within the bound of a sum of FP64 products, with and without beta."""
+    n = 1000
+    V, W, X = synth.block_vector(n, m, 178), synth.block_vector(n, k, 179), synth.block_vector(m, k, 180)
+    for beta in (0.0, -0.5):
+        Wd = dev(W)
+        sc.sell_tsmm(dev(V), dev(X), Wd, alpha=1.5, beta=beta)
+        bound = 2 * (m + 6) * 2.0 ** -53 * (1.5 * np.abs(V) @ np.abs(X) + abs(beta) * np.abs(W))
+        assert (np.abs(host(Wd) - oracle.tsmm(V, X, 1.5, beta, W)) <= bound).all()
