@@ -21,10 +21,10 @@ namespace sellcs {
 // consecutive in dval, so a wave's stores fill whole lines of it.
 //
 // What bounds it: the gathers of X (a row of b elements per stored entry) through the CU's vector
-// memory path. 100^3 Laplacian, FP32 vectors, b = 8: 40.7 us (147 MB that it cannot do without,
-// 3.6 TB/s) against 285 us for one lane per row with element loads, added into a zeroed array in the
+// memory path. 100^3 Laplacian, FP32 vectors, b = 8: 34.9 us (147 MB that it cannot do without,
+// 4.2 TB/s) against 285 us for one lane per row with element loads, added into a zeroed array in the
 // SELL order that two more kernels cleared and mapped to CSR. 64^3 Anderson matrix, FP64, b = 1, ten
-// pairs in a launch: 24.0 us against 10 x 12.1.
+// pairs in a launch: 21.9 us against 10 x 12.1.
 // RAG: b is not VPT * L; the last lanes' pieces are shifted back to end at column b - 1 and the
 // columns that a lane shares with its neighbour are left to the neighbour.
 constexpr int kGradU = 8;
@@ -32,88 +32,86 @@ constexpr int kGradU = 8;
 template <class TX, int VPT, int LL, bool RAG>
 __global__ void __launch_bounds__(256) grad_kernel(const int32_t *__restrict__ col, const int64_t *__restrict__ cs,
                                                    const int32_t *__restrict__ perm,
-                                                   const int64_t *__restrict__ rowptr, int64_t nrows, int32_t C,
-                                                   int32_t cshift, int32_t b, GradPairs pairs, int64_t ldg,
+                                                   const int64_t *__restrict__ rowptr, int64_t row0, int64_t nrows,
+                                                   int32_t C, int32_t cshift, int32_t b, GradPairs pairs, int64_t ldg,
                                                    int64_t ldx, int accumulate, double *__restrict__ dval) {
     constexpr int L = 1 << LL, U = kGradU;
+    const int64_t s = row0 + int64_t(xcd_block(blockIdx.x, gridDim.x)) * (256 / L) + (threadIdx.x >> LL);
+    if (s >= nrows) return;  // the whole lane group
     const int vg = threadIdx.x & (L - 1);
+    const int64_t c = cshift >= 0 ? (s >> cshift) : s / C;
+    const int64_t row = perm ? int64_t(perm[s]) : s;
+    const int64_t base = cs[c] + (s - c * C);
+    const int64_t p0 = rowptr[row];
+    const int len = int(rowptr[row + 1] - p0);
     const int jb = RAG ? min(vg * VPT, b - VPT) : vg * VPT;
     const int skip = RAG ? vg * VPT - jb : 0;  // leading columns that belong to the neighbour
-    // (the lanes of a group take the same rows, so they leave the loop together)
-    const int64_t step = int64_t(gridDim.x) * (256 / L);
-    for (int64_t s = int64_t(xcd_block(blockIdx.x, gridDim.x)) * (256 / L) + (threadIdx.x >> LL); s < nrows; s += step) {
-        const int64_t c = cshift >= 0 ? (s >> cshift) : s / C;
-        const int64_t row = perm ? int64_t(perm[s]) : s;
-        const int64_t base = cs[c] + (s - c * C);
-        const int64_t p0 = rowptr[row];
-        const int len = int(rowptr[row + 1] - p0);
-        for (int k0 = 0; k0 < len; k0 += U) {
-            int64_t xo[U];
-            double acc[U];
+    for (int k0 = 0; k0 < len; k0 += U) {
+        int64_t xo[U];
+        double acc[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = min(k0 + u, len - 1);
-                xo[u] = int64_t(col[base + int64_t(k) * C]) * ldx + jb;
-                acc[u] = 0.0;
-            }
-            for (int q = 0; q < pairs.n; ++q) {
-                const TX *gp = static_cast<const TX *>(pairs.g[q]) + row * ldg + jb;
-                const TX *xp = static_cast<const TX *>(pairs.x[q]);
-                const double cq = pairs.c[q];
-                double g[VPT];
-                TX x[U][VPT];
-#pragma unroll
-                for (int t = 0; t < VPT; ++t) g[t] = cq * double(gp[t]);
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int t = 0; t < VPT; ++t) x[u][t] = xp[xo[u] + t];
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int t = 0; t < VPT; ++t) {
-                        const double f = fma(g[t], double(x[u][t]), acc[u]);
-                        acc[u] = !RAG || t >= skip ? f : acc[u];
-                    }
-            }
-            // reduce over the lane group, scattering the entries over its lanes
-            int e0 = 0;       // first entry of the batch that this lane ends up with
-            bool own = true;  // false: another lane holds the same sum
-#pragma unroll
-            for (int st = 0; st < LL; ++st) {
-                const int m = L >> (st + 1), cnt = U >> st;
-                const bool up = (vg & m) != 0;
-                if (cnt > 1) {
-                    const int half = cnt / 2;
-#pragma unroll
-                    for (int i = 0; i < half; ++i) {
-                        const double send = up ? acc[i] : acc[i + half];
-                        const double keep = up ? acc[i + half] : acc[i];
-                        acc[i] = keep + __shfl_xor(send, m, 64);
-                    }
-                    e0 += up ? half : 0;
-                } else {
-                    acc[0] += __shfl_xor(acc[0], m, 64);
-                    own = own && !up;
-                }
-            }
-            constexpr int left = (U >> LL) > 0 ? (U >> LL) : 1;
-            double *d = dval + p0 + k0 + e0;
-            // (applied to the sums: with the rows of G scaled first, a factor and a row that are small or
-            // large together left the range of a double where their products with X do not)
-#pragma unroll
-            for (int i = 0; i < left; ++i) acc[i] *= pairs.scale;
-            if (accumulate) {
-                double old[left];
-#pragma unroll
-                for (int i = 0; i < left; ++i) old[i] = own && k0 + e0 + i < len ? d[i] : 0.0;
-#pragma unroll
-                for (int i = 0; i < left; ++i) acc[i] += old[i];
-            }
-#pragma unroll
-            for (int i = 0; i < left; ++i)
-                if (own && k0 + e0 + i < len) d[i] = acc[i];
+        for (int u = 0; u < U; ++u) {
+            const int k = min(k0 + u, len - 1);
+            xo[u] = int64_t(col[base + int64_t(k) * C]) * ldx + jb;
+            acc[u] = 0.0;
         }
+        for (int q = 0; q < pairs.n; ++q) {
+            const TX *gp = static_cast<const TX *>(pairs.g[q]) + row * ldg + jb;
+            const TX *xp = static_cast<const TX *>(pairs.x[q]);
+            const double cq = pairs.c[q];
+            double g[VPT];
+            TX x[U][VPT];
+#pragma unroll
+            for (int t = 0; t < VPT; ++t) g[t] = cq * double(gp[t]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < VPT; ++t) x[u][t] = xp[xo[u] + t];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < VPT; ++t) {
+                    const double f = fma(g[t], double(x[u][t]), acc[u]);
+                    acc[u] = !RAG || t >= skip ? f : acc[u];
+                }
+        }
+        // reduce over the lane group, scattering the entries over its lanes
+        int e0 = 0;       // first entry of the batch that this lane ends up with
+        bool own = true;  // false: another lane holds the same sum
+#pragma unroll
+        for (int st = 0; st < LL; ++st) {
+            const int m = L >> (st + 1), cnt = U >> st;
+            const bool up = (vg & m) != 0;
+            if (cnt > 1) {
+                const int half = cnt / 2;
+#pragma unroll
+                for (int i = 0; i < half; ++i) {
+                    const double send = up ? acc[i] : acc[i + half];
+                    const double keep = up ? acc[i + half] : acc[i];
+                    acc[i] = keep + __shfl_xor(send, m, 64);
+                }
+                e0 += up ? half : 0;
+            } else {
+                acc[0] += __shfl_xor(acc[0], m, 64);
+                own = own && !up;
+            }
+        }
+        constexpr int left = (U >> LL) > 0 ? (U >> LL) : 1;
+        double *d = dval + p0 + k0 + e0;
+        // (applied to the sums: with the rows of G scaled first, a factor and a row that are small or
+        // large together left the range of a double where their products with X do not)
+#pragma unroll
+        for (int i = 0; i < left; ++i) acc[i] *= pairs.scale;
+        if (accumulate) {
+            double old[left];
+#pragma unroll
+            for (int i = 0; i < left; ++i) old[i] = own && k0 + e0 + i < len ? d[i] : 0.0;
+#pragma unroll
+            for (int i = 0; i < left; ++i) acc[i] += old[i];
+        }
+#pragma unroll
+        for (int i = 0; i < left; ++i)
+            if (own && k0 + e0 + i < len) d[i] = acc[i];
     }
 }
 
@@ -144,9 +142,9 @@ void go_grad(const sell_mat *A, const GradPairs &p, int64_t ldg, int64_t ldx, in
              hipStream_t s) {
     const HostSell &h = A->h;
     const int32_t cshift = (h.C & (h.C - 1)) == 0 ? __builtin_ctz(unsigned(h.C)) : -1;
-    hipLaunchKernelGGL((grad_kernel<TX, VPT, LL, RAG>), dim3(grad_grid(h.nrows, LL)), dim3(256), 0, s,
-                       A->d_col, A->d_cs, A->d_perm, A->d_rowptr, h.nrows, h.C, cshift, b, p, ldg, ldx, accumulate,
-                       dval);
+    for (int64_t row0 = 0; row0 < h.nrows; row0 += kGradGrid * (256 >> LL))
+        hipLaunchKernelGGL((grad_kernel<TX, VPT, LL, RAG>), dim3(grad_grid(h.nrows - row0, LL)), dim3(256), 0, s, A->d_col,
+                           A->d_cs, A->d_perm, A->d_rowptr, row0, h.nrows, h.C, cshift, b, p, ldg, ldx, accumulate, dval);
 }
 
 // Lanes per row for b columns: one up to b = 4 (VPT = b), else the power of two that holds
