@@ -568,6 +568,8 @@ int sell_batch_packed_sizes(const sell_batch *B, int64_t *x_elems, int64_t *y_el
  * values, else F32), aligned to the element size. opts as for sell_spmmv_aug, applied to every
  * matrix (gamma_v: at least max w_m entries, matrix m uses the first w_m); opts->dot receives
  * matrix m's dots packed at dot + 3 sum_{k<m} w_k, as [yy (w_m) | xy (w_m) | xx (w_m)].
+ * One launch, not the fastest way where several will do: 64 Laplacians with widths 1 to 32 take
+ * 2.74 ms, as 64 single products 2.24 ms, as one batch per width 1.78 ms.
  * Every workgroup runs the kernel body compiled for its matrix's width (run-time width for
  * widths outside 1, 2, 4, 8, 16, 32 or rows not aligned for 16-byte accesses); the workgroups
  * are split by each matrix's bytes at its own width. Asynchronous; calls on one batch must be

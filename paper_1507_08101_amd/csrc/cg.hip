@@ -372,14 +372,14 @@ __device__ __forceinline__ void seg_rows(const BatchSeg &sg, int m, int bpad, F 
 //   t npm, npm = pblk[m+1] - pblk[m]; <q, q> is quantity j, <p, q> quantity b + j): alpha and beta, as
 //   cg_step_kernel computes them. Both in one launch inside a run of iterations (a system that
 //   retires in it has had one product more, and its vector pass is skipped).
-// 16 Laplacians, b = 4: 5.1 us per iteration against 13.7 for a launch each, with the columns one
+// 16 Laplacians, b = 4: 4.6 us per iteration against 13.7 for a launch each, with the columns one
 // after another in the first.
 constexpr int kST = 1024;
 
 __global__ void __launch_bounds__(kST) bcg_step_kernel(const double *pparts, const int32_t *pblk, const double *vparts,
                                                        int G, const int32_t *vblk, int b, BatchCg sc) {
     // As in cg_step_kernel everything a column needs is loaded before any of it is used: two waits for
-    // memory (offsets, then partials and scalars) instead of six (16 systems, b = 4: 5.3 us, now 4.6).
+    // memory (offsets, then partials and scalars) instead of six (16 systems, b = 4: 5.3 us without, 4.6 with).
     __shared__ int any;
     const int m = blockIdx.x, lane = threadIdx.x & 63;
     const int on = sc.sys_active[m];

@@ -7,13 +7,13 @@
 //   row lengths; inside each window of sigma rows a stable sort by descending length (a stable
 //   radix sort of the 64-bit keys (window, 2^31 - 1 - length), which keeps equal keys in row
 //   order); chunk lengths as the maximum over the chunk's slots; chunk starts as an exclusive
-//   prefix sum of C * length; one thread per slot writes its row's entries and its padding
-//   (column -1, value 0), converted to the storage type.
+//   prefix sum of C * length; a thread per slot (several where chunks are long) writes its row's
+//   entries and its padding (column -1, value 0), converted to the storage type.
 // The small per-chunk arrays, the permutation and the row pointers are copied back to the host
 // (the matrix keeps them there, as a host-built one does), where the work partition is made.
 //
-// The maps that value updates need (row -> slot, CSR row pointers) and the SELL copy of A^T (a stable
-// sort of the entries by column, then the steps above) are made here too, from the matrix's own
+// The CSR row pointers that value updates need and the SELL copy of A^T (a stable sort of the entries by
+// column, then the steps above), with the place in it of each entry, are made here too, from the matrix's own
 // device arrays. On the host, from an export of the matrix, the first backward pass over the 100^3
 // Laplacian (FP32, b = 8) took 99 to 118 ms; with the device steps, which are bound by their
 // allocations and copies of metadata, 5.1 ms.

@@ -18,9 +18,9 @@
 //     entry k of consecutive rows are adjacent) stream coalesced.
 //   * The chunk loop takes batches of U entries (8, or 7 and 5 for rows of that length),
 //     issuing all index/value loads of a batch before its gathers, to keep enough loads in
-//     flight. Batch slots past the chunk length are clamped to its last entry and skipped in
-//     the arithmetic; padding entries inside it (value 0 and the row's last real column) are
-//     gathered and multiplied like the others, which keeps the loop free of branches.
+//     flight. Batch slots past the chunk length are clamped to its last entry; they and the
+//     padding entries inside it (column -1) gather row 0 of x, which the arithmetic leaves out,
+//     so the loop is free of branches and nothing of x reaches a row that does not hold it.
 //   * What bounds the kernel is the bytes its gathers carry through each CU's vector memory
 //     path (texture address and data units), more than HBM or where the gathers hit. So lanes
 //     that gather 32 bytes per entry run one workgroup per CU by default, and the KPM step's
@@ -131,8 +131,9 @@ __device__ __forceinline__ void load_row(const SELL_GLOBAL X *p, int64_t cs, X (
 // Row stores are nontemporal (NT): the product never reads its outputs again in the same launch. Not so
 // where the caller's next kernel finds them in the caches (ProdArgs::keep), and never
 // for kContig, whose pieces fill lines less well (96^3 Anderson matrix, FP64: b = 7 45.7 us
-// nontemporal, 43.3 ordinary; b = 12 with chain 131 and 127; from b = 33 on nontemporal would win,
-// 201 against 228).
+// nontemporal, 43.3 ordinary; b = 12 with chain 131 and 127). From b = 33 on nontemporal stores measured 5
+// to 12 % faster (201 against 228), but not as a choice at run time, which the compiler merges into
+// ordinary stores: it would take kernels of their own.
 template <class X, int VPT, RowMode MODE, bool NT>
 __device__ __forceinline__ void store_row(SELL_GLOBAL X *p, int64_t cs, const X (&o)[VPT]) {
     constexpr int bytes = VPT * int(sizeof(X));
@@ -810,7 +811,9 @@ inline int go_prod_u(ProdArgs &a, hipStream_t s) {
             // loads less in the chain that starts a workgroup and three per pass (64^3 Anderson matrix,
             // degree-100 Chebyshev step 1,870 -> 1,780 us; 128^3, b = 8, 20 KPM steps 2,606 -> 2,552). A
             // branch at run time instead made the other matrices' loads wait at its end (irregular 4 M rows
-            // 1,063 -> 1,153 us), so these are kernels of their own, for the default columns per lane.
+            // 1,063 -> 1,153 us), so these are kernels of their own, for the default columns per lane and for
+            // augmented products, whose solvers repeat them; plain and batched products were not measured
+            // with them and load their bounds.
             constexpr bool kUni = VPT == (B < 0 || B > 4 ? 4 : B);
             if constexpr (kUni) {
                 if (a.ulen > 0 && !a.stage)

@@ -251,8 +251,8 @@ struct TsmCols {
 // 16 rows at a time (four per instruction) and keeps the whole m x k result (MB x KB blocks of
 // 16 x 16) in registers, so every element of V and W is loaded once. The waves' results are added
 // in wave order through LDS; entry (l, j) lands in partials[g m k + l k + j]. The next rows' loads are
-// in flight during the products (up to 8 KB per wave). Bound by HBM up to 32 x 32 (n = 937,500: 94.7
-// us, 5.07 TB/s), by the partial results that fit the workspace (192 workgroups) at 64 x 64 (n =
+// in flight during the products (up to 8 KB per wave). Bound by HBM up to 32 x 32 (n = 937,500 again
+// and again: 94.7 us, 5.07 TB/s; n = 1,000,000 after a kernel that wrote V: 128 us, 4.0 TB/s), by the partial results that fit the workspace (192 workgroups) at 64 x 64 (n =
 // 468,750: 175 us, 2.74 TB/s, 22 TFLOP/s).
 __host__ __device__ constexpr int tsm_vtw_u(int blocks) { return blocks <= 2 ? 8 : blocks <= 4 ? 4 : 2; }
 
