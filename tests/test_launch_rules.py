@@ -1,5 +1,5 @@
-"""CPU test of the rules that size launches (internal.h): compiled for the host and checked over small and
-large operands, among them ones that no device memory of a test box would hold."""
+"""CPU test of the rules that choose and size launches (internal.h): compiled for the host and checked over
+small and large operands, among them ones larger than any device memory."""
 import os
 import shutil
 import subprocess
