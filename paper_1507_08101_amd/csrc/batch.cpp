@@ -73,6 +73,7 @@ struct sell_batch {
     std::vector<uint8_t> stage;
     double *partials = nullptr;
     size_t partials_cap = 0;  // doubles
+    std::vector<double *> retired;  // earlier, smaller partials (ensure_partials)
     int64_t *d_row_off = nullptr;  // device copy of row_off (for the batched solvers)
     int32_t *d_vblk = nullptr;     // vector-kernel workgroup offsets (for the batched solvers)
     int32_t vgrid = 0;
@@ -105,6 +106,7 @@ void batch_free(sell_batch *B) {
         if (B->h_slot[i]) (void)lib_host_free(B->h_slot[i]);
     }
     if (B->partials) (void)lib_free(B->partials);
+    for (double *p : B->retired) (void)lib_free(p);
     if (B->d_row_off) (void)lib_free(B->d_row_off);
     if (B->d_vblk) (void)lib_free(B->d_vblk);
     if (B->d_widths) (void)lib_free(B->d_widths);
@@ -209,7 +211,7 @@ namespace {
 // threads fits a compute unit (64 Laplacians of edges 20..40, b = 8 with dots, 1.8 passes: 152 us
 // with 512 threads, 110 with 256; edges 20..100, 21 passes: 1,183 with 512, 1,199 with 256).
 struct BatchShape {
-    int32_t G0;
+    int32_t G0, most;  // workgroups, and those of any other choice of the matrices at most
     int threads;
 };
 BatchShape product_shape(const sell_batch *B, const void *kern, const int32_t *host_active,
@@ -245,20 +247,23 @@ BatchShape product_shape(const sell_batch *B, const void *kern, const int32_t *h
     const int64_t resident =
         sh.threads == kBlock ? std::min(one, tiles)
                              : resident_grid(kern, sh.threads, int32_t(std::min<int64_t>(tiles, 1 << 30)), B->bpc_hint);
+    sh.most = int32_t(waves * one);
     sh.G0 = batch_workgroups(tiles, resident, waves * one, work);
     return sh;
 }
 
-// Room for 3 * kMaxSliceCols partials per workgroup of any split of this grid, so that later
-// calls (possibly captured in a graph) never move the buffer.
-int ensure_partials(sell_batch *B, int32_t G, int32_t G0) {
-    const size_t need = size_t(3) * kMaxSliceCols * size_t(std::max<int64_t>(std::max(G, G0), B->K));
+// Room for 3 * kMaxSliceCols partials per workgroup of any split of up to `most` workgroups (the largest
+// grid of the launch's kernel over any of the matrices). A buffer that has become too small (a kernel of
+// higher occupancy) is kept until the batch is destroyed: a graph that was captured with it, a caller's or
+// the solver's, may be replayed after calls of other shapes. There are few such sizes.
+int ensure_partials(sell_batch *B, int32_t G, int32_t most) {
+    const size_t need = size_t(3) * kMaxSliceCols * size_t(std::max<int64_t>(std::max(G, most), B->K));
     if (need <= B->partials_cap) return SELL_OK;
-    // grows outside any steady state (the first call of a shape)
-    if (B->partials) HIPCHK(lib_free(B->partials));
-    B->partials = nullptr;
-    B->partials_cap = 0;
-    HIPCHK(lib_malloc(&B->partials, need * sizeof(double)));
+    double *p = nullptr;
+    B->retired.reserve(B->retired.size() + 1);
+    HIPCHK(lib_malloc(&p, need * sizeof(double)));
+    if (B->partials) B->retired.push_back(B->partials);
+    B->partials = p;
     B->partials_cap = need;
     return SELL_OK;
 }
@@ -403,7 +408,7 @@ int batch_aug_impl(sell_batch *B, const sell_bv *X, sell_bv *Y, sell_bv *Z, cons
     const std::vector<int32_t> &blk = *pblk_h;
     const int32_t G = blk[size_t(K)];
     const bool dots = aug && (o.flags & SELL_SPMV_DOTS);
-    if (dots && (rc = ensure_partials(B, G, G0))) return rc;
+    if (dots && (rc = ensure_partials(B, G, shape.most))) return rc;
     // the table
     B->stage.assign(B->table_bytes, 0);
     ProdArgs *tab = reinterpret_cast<ProdArgs *>(B->stage.data());
@@ -509,7 +514,7 @@ int batch_aug_packed_impl(sell_batch *B, const void *X, void *Y, void *Z, const 
     const std::vector<int32_t> &blk = hit->second;
     const int32_t G = blk[size_t(K)];
     const bool dots = aug && (o.flags & SELL_SPMV_DOTS);
-    if (dots && (rc = ensure_partials(B, G, G0))) return rc;
+    if (dots && (rc = ensure_partials(B, G, shape.most))) return rc;
     const char *xb = static_cast<const char *>(X);
     char *yb = static_cast<char *>(Y), *zb = static_cast<char *>(Z);
     B->stage.assign(B->table_bytes, 0);

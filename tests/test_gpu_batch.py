@@ -576,3 +576,74 @@ def test_batch_outlives_the_streams_it_was_used_on(sc):
         assert torch.equal(u, v)
     for M in Ms:
         M.close()
+
+
+def test_captured_batch_product_survives_calls_of_other_shapes(sc):
+    """A batched product with dots captured in a caller's graph, then calls whose grids and kernels
+    need other room for their partial sums: every replay gives the eager result, as do the calls between."""
+    import torch
+
+    mats = [synth.laplacian3d(e) for e in (20, 28, 34)]
+    Ms = [sc.SellMatrix.from_csr(A, C=32, sigma=1) for A in mats]
+    Bt = sc.SellBatch(Ms)
+    n, flags = sum(A.nrows for A in mats), sc.DOT_XY | sc.DOT_YY
+
+    def operands(b, seed):
+        X = torch.from_numpy(synth.block_vector(n, b, seed)).cuda()
+        return X, torch.empty_like(X), torch.zeros(3 * b * len(mats), dtype=torch.float64, device="cuda:0")
+
+    def call(ops):
+        sc.sell_batch_spmmv_aug(Bt, ops[0], ops[1], flags=flags, dot=ops[2])
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    first, others = operands(1, 250), [operands(8, 251), operands(32, 252)]
+    with torch.cuda.stream(s):
+        call(first)
+        torch.cuda.synchronize()
+        want = [t.clone() for t in first[1:]]
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            call(first)
+        wants = []
+        for rep in range(4):
+            for o in others:
+                call(o)
+            wants.append([t.clone() for o in others for t in o[1:]])
+            first[1].fill_(-1.0)
+            first[2].fill_(-1.0)
+            g.replay()
+            torch.cuda.synchronize()
+            mask = want[1] != 0.0  # (dots that were not asked for are left as they are)
+            assert torch.equal(first[1], want[0]) and torch.equal(first[2][mask], want[1][mask]), rep
+        assert all(torch.equal(u, v) for w in wants[1:] for u, v in zip(w, wants[0]))
+    del g
+    Bt.close()
+    for M in Ms:
+        M.close()
+
+
+@pytest.mark.parametrize("mode", ["f64", "bf16"])
+def test_batch_cg_graph_across_updates_of_some_systems(sc, mode):
+    """Uneven systems whose residuals are updated every 24 iterations without any of them leaving: the
+    updates' products over all and over some of the systems between replays of one graph; results and
+    statistics of the solve without a graph."""
+    import torch
+
+    mats = [synth.laplacian3d(e) for e in (30, 8, 12, 26)] + [synth.laplacian2d(40)]
+    b = 4
+    M64 = [sc.SellMatrix.from_csr(A, C=32, sigma=1) for A in mats]
+    Mlo = [sc.SellMatrix.from_csr(A, C=32, sigma=1, dtype=mode) for A in mats] if mode != "f64" else []
+    B64, Blo = sc.SellBatch(M64), sc.SellBatch(Mlo) if Mlo else None
+    Bs = dev(_stack([synth.block_vector(A.nrows, b, 260 + k) for k, A in enumerate(mats)], b))
+    outs = []
+    for graph in (False, True, True):
+        X = torch.zeros_like(Bs)
+        st = sc.sell_batch_cg(B64, Blo, Bs, X, tol=1e-10, maxit=2000, inner_maxit=24, graph=graph)
+        assert all(e["converged"] for e in st), st
+        outs.append((host(X), st))
+    for X, st in outs[1:]:
+        assert np.array_equal(X, outs[0][0]) and st == outs[0][1]
+    for obj in [B64, Blo] + M64 + Mlo:
+        if obj is not None:
+            obj.close()
